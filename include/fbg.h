@@ -238,7 +238,7 @@ fbg_status fbg_count(const fbg_program *p, uint64_t *d_count, void *stream);
  *   d_total   device pointer to one uint64; receives the total number of
  *             models (also when it exceeds capacity).
  * Allocates temporary device memory on `stream` (stream-ordered) for the
- * per-tile counts and offsets.
+ * per-tile counts and the list of the tiles that hold models.
  */
 fbg_status fbg_enumerate(const fbg_program *p, uint64_t *d_idx, uint64_t capacity, uint64_t *d_total,
                          void *stream);
@@ -324,8 +324,8 @@ fbg_status fbg_count_batch(const fbg_program *const *ps, int32_t np, uint64_t *d
  * fbg_enumerate_noalloc -- fbg_enumerate for callers that cannot allocate
  * device memory: code under HIP graph capture, tight serving loops, hosts
  * that forbid hipMalloc.  Same arguments, outputs, order and errors as
- * fbg_enumerate, same kernels; the temporaries (per-tile model counts, their
- * exclusive scan, block sums) live in a static device array of
+ * fbg_enumerate, same kernels; the temporaries (per-tile model counts, the
+ * list of the tiles that hold models) live in a static device array of
  * FBG_NOALLOC_SCRATCH_BYTES on each device (held until the process ends)
  * instead of a stream-ordered allocation, so the call allocates nothing.
  * FBG_E_RANGE when the program has more than FBG_NOALLOC_MAX_TILES tiles at

@@ -1,7 +1,7 @@
 // batch.hip -- the batched kernels' launches and occupancy queries: the
 // persistent work-queue evaluator k_batch (counts; counts and DNF vectors),
 // the direct batched DNF write-out k_batch_direct with k_sum_tile_counts,
-// and the batched enumeration's k_list_tiles / k_batch_compact.
+// and the batched enumeration's k_batch_compact.
 #define FBG_DEVICE_BATCH_KERNELS
 #include "fbg_device.h"
 
@@ -90,11 +90,6 @@ hipError_t launch_batch_direct(int log2w, const BatchArgs &a, int grid, int bloc
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(dev::k_sum_tile_counts, dim3(a.nitems, (unsigned)sum_blocks), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_list_tiles(const BatchEnumArgs &a, int grid, hipStream_t s) {
-  hipLaunchKernelGGL(dev::k_list_tiles, dim3(grid), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -210,9 +210,9 @@ struct fbg_batch {
   uint64_t total_tiles = 0;
   uint32_t *d_tile_counts = nullptr;
   uint32_t *d_chunk_counts = nullptr;     // XCD-local write-out: counts per 4 KiB piece
-  uint64_t *d_offsets = nullptr;
-  uint64_t *d_scan_blk = nullptr;
-  uint32_t *d_tile_list = nullptr;        // tiles holding models, then their number
+  uint64_t *d_tile_list = nullptr;        // tiles holding models (TileListArgs)
+  fbg::TilePair *d_list_sums = nullptr;
+  uint64_t *d_list_base = nullptr;        // per block, then the length of the list, then per program
   fbg::EnumProg *d_enum = nullptr;
   uint32_t *d_head = nullptr;             // kHeadWords of queue heads per plan (at most 4 plans)
   // captured graph of (zero fill, persistent kernels) for one counts pointer
@@ -379,58 +379,122 @@ fbg::BatchProg batch_prog(const fbg_program *p, int l) {
   return b;
 }
 
-// Bytes of the enumeration temporaries for nt tiles: per-tile uint32 counts,
-// their uint64 exclusive scan and the scan's block sums (each part 256-byte
-// aligned).
-size_t enum_temp_bytes(uint64_t nt, size_t *bytes_cnt, size_t *bytes_off) {
-  *bytes_cnt = ((nt * 4 + 255) / 256) * 256;
-  *bytes_off = ((nt * 8 + 255) / 256) * 256;
-  return *bytes_cnt + *bytes_off + (fbg::scan_block_count(nt) + 1) * 8;
+// Programs and vectors of at most this many tiles are enumerated in two
+// launches: the tile counts, then compaction blocks that add up the counts of
+// the tiles before them themselves (a block reads at most 64 KiB of them from
+// L2).  Beyond it the tiles that hold models are listed first
+// (launch_tile_list), which also spreads them evenly over the waves when few
+// tiles of many hold models.  8192 tiles of 1024 words each holding models
+// (triangle-free graphs, n = 28): 3 launches fewer, see k_tile_list for theirs.
+constexpr uint64_t kDirectEnumTiles = 16384;
+
+// The enumeration temporaries for nt tiles, each part 256-byte aligned:
+// per-tile uint32 counts and, beyond kDirectEnumTiles, the list of the tiles
+// that hold models (TileListArgs).
+struct EnumTemp {
+  size_t list = 0, sums = 0, base = 0, nlist = 0, bytes = 0;  // offsets, and the size of all
+};
+
+EnumTemp enum_temp(uint64_t nt) {
+  auto up = [](size_t b) { return (b + 255) / 256 * 256; };
+  EnumTemp t;
+  t.list = up(nt * 4);
+  t.bytes = t.list;
+  if (nt <= kDirectEnumTiles) return t;
+  const uint64_t nb = fbg::tile_list_blocks(nt);
+  t.sums = t.list + up(nt * 8);
+  t.base = t.sums + up(nb * sizeof(fbg::TilePair));
+  t.nlist = t.base + up(nb * 8);
+  t.bytes = t.nlist + 256;
+  return t;
 }
 
+// Blocks of a compaction pass.
+struct EnumShape {
+  int wpb, resident;  // waves per block; blocks that fill the device
+};
+
 // Two-pass enumeration given the pass launcher and the temporaries `tmp`
-// (enum_temp_bytes(a.ntiles) bytes of device memory): counts -> scan ->
-// compaction.  Every temporary word is written before it is read.  With
-// zero_counts (the uniform-cofactor passes, which write the counts of live
-// tiles only) a fill kernel clears the tile counts first, in one coalesced
-// sweep instead of a scattered write per dead tile.
+// (enum_temp(a.ntiles).bytes of device memory): tile counts, the list of the
+// tiles that hold models unless there are few tiles, compaction.  Every
+// temporary word is written before it is read.  With zero_counts (the
+// uniform-cofactor passes, which write the counts of live tiles only) a fill
+// kernel clears the tile counts first, in one coalesced sweep instead of a
+// scattered write per dead tile.
 template <typename Pass>
-hipError_t enumerate_passes(fbg::EvalArgs a, char *tmp, uint64_t *d_idx, uint64_t capacity, uint64_t *d_total,
-                            hipStream_t s, bool zero_counts, Pass pass) {
+hipError_t enumerate_passes(fbg::EvalArgs a, const EnumShape &sh, char *tmp, uint64_t *d_idx, uint64_t capacity,
+                            uint64_t *d_total, hipStream_t s, bool zero_counts, Pass pass) {
   const uint64_t nt = a.ntiles;
-  size_t bytes_cnt, bytes_off;
-  enum_temp_bytes(nt, &bytes_cnt, &bytes_off);
+  const EnumTemp t = enum_temp(nt);
   uint32_t *cnt = (uint32_t *)tmp;
-  uint64_t *off = (uint64_t *)(tmp + bytes_cnt);
-  uint64_t *blk = (uint64_t *)(tmp + bytes_cnt + bytes_off);
   a.tile_counts = cnt;
-  hipError_t e = zero_counts ? fbg::launch_zero((uint64_t *)cnt, bytes_cnt / 8, nullptr, 0, s) : hipSuccess;
-  if (e == hipSuccess) e = pass(fbg::EVAL_TILECNT, a);
-  if (e == hipSuccess) e = fbg::launch_scan(cnt, nt, off, blk, d_total, s);
-  if (e == hipSuccess && capacity > 0) {
-    a.tile_offsets = off;
-    a.out_idx = d_idx;
-    a.capacity = capacity;
-    e = pass(fbg::EVAL_ENUM, a);
+  hipError_t e = zero_counts ? fbg::launch_zero((uint64_t *)cnt, t.list / 8, nullptr, 0, s) : hipSuccess;
+  if (e == hipSuccess) e = pass(fbg::EVAL_TILECNT, a, 0);
+  if (e != hipSuccess) return e;
+  a.out_idx = d_idx;
+  a.capacity = capacity;
+  if (nt <= kDirectEnumTiles) {
+    // a multiple of 4 tiles per block, over about the blocks that fill the device
+    const uint64_t per = (nt + 4 * (uint64_t)sh.resident - 1) / (4 * (uint64_t)sh.resident);
+    a.tiles_per_block = (uint32_t)(4 * std::min<uint64_t>(per, 16));
+    a.out_count = d_total;
+    return pass(fbg::EVAL_ENUM, a, (int)((nt + a.tiles_per_block - 1) / a.tiles_per_block));
   }
-  return e;
+  fbg::TileListArgs l;
+  l.counts = cnt;
+  l.n = nt;
+  l.list = (uint64_t *)(tmp + t.list);
+  l.sums = (fbg::TilePair *)(tmp + t.sums);
+  l.list_base = (uint64_t *)(tmp + t.base);
+  l.nlist = (uint64_t *)(tmp + t.nlist);
+  l.total = d_total;
+  e = fbg::launch_tile_list(l, s);
+  if (e != hipSuccess || capacity == 0) return e;
+  a.tiles_per_block = 0;
+  a.list = l.list;
+  a.list_base = l.list_base;
+  a.nlist = l.nlist;
+  return pass(fbg::EVAL_ENUM, a, sh.resident);
 }
 
 // The same with the temporaries allocated on the stream and freed after.
 template <typename Pass>
-fbg_status enumerate_with(fbg::EvalArgs a, uint64_t *d_idx, uint64_t capacity, uint64_t *d_total, hipStream_t s,
-                          bool zero_counts, Pass pass) {
-  size_t bytes_cnt, bytes_off;
-  const size_t bytes = enum_temp_bytes(a.ntiles, &bytes_cnt, &bytes_off);
+fbg_status enumerate_with(fbg::EvalArgs a, const EnumShape &sh, uint64_t *d_idx, uint64_t capacity,
+                          uint64_t *d_total, hipStream_t s, bool zero_counts, Pass pass) {
+  const size_t bytes = enum_temp(a.ntiles).bytes;
   char *tmp = nullptr;
   hipError_t e = hipMallocAsync((void **)&tmp, bytes, s);
   if (e != hipSuccess) return fail(FBG_E_NOMEM, "hipMallocAsync of %zu bytes: %s", bytes, hipGetErrorString(e));
-  e = enumerate_passes(a, tmp, d_idx, capacity, d_total, s, zero_counts, pass);
+  e = enumerate_passes(a, sh, tmp, d_idx, capacity, d_total, s, zero_counts, pass);
   hipError_t e2 = hipFreeAsync(tmp, s);
   if (e != hipSuccess) return hip_fail(e, "launch of an enumeration kernel");
   if (e2 != hipSuccess) return hip_fail(e2, "hipFreeAsync");
   return FBG_OK;
 }
+
+// The passes of enumerating a program: the counts on geometry g, the
+// compaction (grid > 0 blocks, the same block size) with kStageWords of LDS per
+// wave at least.  (The compaction needs no cofactor variant: its tiles hold models.)
+struct EvalPasses {
+  const fbg_program *p;
+  Geometry g;
+  int var;
+  hipStream_t s;
+  EnumShape shape() const {
+    const int wpb = g.block / 64;
+    const int occ = fbg::eval_blocks_per_cu(fbg::EVAL_ENUM, g.log2w, var & 1, g.block, enum_lds());
+    return {wpb, cu_count(p->device) * occ};
+  }
+  size_t wave_lds() const {
+    return std::max(lds_per_wave((uint32_t)p->c.nregs, g.log2w), (size_t)fbg::kStageWords * 4);
+  }
+  size_t enum_lds() const { return wave_lds() * (size_t)(g.block / 64); }
+  hipError_t operator()(int mode, fbg::EvalArgs a, int grid) const {
+    if (mode != fbg::EVAL_ENUM) return fbg::launch_eval(mode, g.log2w, var, a, g.grid, g.block, g.lds, s);
+    a.lds_stride = (uint32_t)(wave_lds() / 4);
+    return fbg::launch_eval(mode, g.log2w, var & 1, a, grid, g.block, enum_lds(), s);
+  }
+};
 
 }  // namespace
 
@@ -694,12 +758,9 @@ fbg_status fbg_enumerate(const fbg_program *p, uint64_t *d_idx, uint64_t capacit
     return fail(FBG_E_INVAL, "d_idx is NULL with capacity %llu", (unsigned long long)capacity);
   Geometry g;
   if ((st = geometry(p, nullptr, fbg::EVAL_TILECNT, g))) return st;
-  hipStream_t s = (hipStream_t)stream;
-  const int var = p->variant(nullptr);
-  return enumerate_with(base_args(p, g.log2w), d_idx, capacity, d_total, s, (var & 2) != 0,
-                        [&](int mode, const fbg::EvalArgs &a) {
-                          return fbg::launch_eval(mode, g.log2w, var, a, g.grid, g.block, g.lds, s);
-                        });
+  const EvalPasses pass{p, g, p->variant(nullptr), (hipStream_t)stream};
+  return enumerate_with(base_args(p, g.log2w), pass.shape(), d_idx, capacity, d_total, pass.s, (pass.var & 2) != 0,
+                        pass);
 }
 
 fbg_status fbg_enumerate_noalloc(const fbg_program *p, uint64_t *d_idx, uint64_t capacity, uint64_t *d_total,
@@ -712,8 +773,7 @@ fbg_status fbg_enumerate_noalloc(const fbg_program *p, uint64_t *d_idx, uint64_t
   Geometry g;
   if ((st = geometry(p, nullptr, fbg::EVAL_TILECNT, g))) return st;
   const fbg::EvalArgs a = base_args(p, g.log2w);
-  size_t bytes_cnt, bytes_off;
-  const size_t bytes = enum_temp_bytes(a.ntiles, &bytes_cnt, &bytes_off);
+  const size_t bytes = enum_temp(a.ntiles).bytes;
   if (a.ntiles > fbg::kNoallocMaxTiles || bytes > fbg::kNoallocScratchBytes)
     return fail(FBG_E_RANGE,
                 "fbg_enumerate_noalloc: %llu tiles at %d words per lane need %zu bytes of scratch; the static "
@@ -723,12 +783,8 @@ fbg_status fbg_enumerate_noalloc(const fbg_program *p, uint64_t *d_idx, uint64_t
   void *scratch = nullptr;
   hipError_t e = fbg::noalloc_scratch(&scratch);
   if (e != hipSuccess) return hip_fail(e, "address of the static scratch");
-  hipStream_t s = (hipStream_t)stream;
-  const int var = p->variant(nullptr);
-  e = enumerate_passes(a, (char *)scratch, d_idx, capacity, d_total, s, (var & 2) != 0,
-                       [&](int mode, const fbg::EvalArgs &aa) {
-    return fbg::launch_eval(mode, g.log2w, var, aa, g.grid, g.block, g.lds, s);
-  });
+  const EvalPasses pass{p, g, p->variant(nullptr), (hipStream_t)stream};
+  e = enumerate_passes(a, pass.shape(), (char *)scratch, d_idx, capacity, d_total, pass.s, (pass.var & 2) != 0, pass);
   return e == hipSuccess ? FBG_OK : hip_fail(e, "launch of an enumeration kernel");
 }
 
@@ -750,9 +806,10 @@ fbg_status fbg_enumerate_dnf(const uint64_t *d_dnf, int32_t n_vars, uint64_t *d_
   const uint64_t blocks = (a.ntiles + kWavesPerBlock - 1) / kWavesPerBlock;
   const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>(blocks, (uint64_t)cu_count(dev) * 8));
   hipStream_t s = (hipStream_t)stream;
-  return enumerate_with(a, d_idx, capacity, d_total, s, false, [&](int mode, const fbg::EvalArgs &aa) {
-    return fbg::launch_dnf_scan(mode, aa, grid, 64 * kWavesPerBlock, s);
-  });
+  return enumerate_with(a, {kWavesPerBlock, cu_count(dev) * 8}, d_idx, capacity, d_total, s, false,
+                        [&](int mode, const fbg::EvalArgs &aa, int g) {
+                          return fbg::launch_dnf_scan(mode, aa, g > 0 ? g : grid, 64 * kWavesPerBlock, s);
+                        });
 }
 
 // ------------------------------------------------------------------ batches
@@ -1089,12 +1146,12 @@ fbg_status fbg_batch_set_enum_outputs(fbg_batch *b, uint64_t *const *d_idx, cons
     if (total >= (1ull << 32)) return fail(FBG_E_RANGE, "%llu tiles: batched enumeration lists tiles in 32 bits",
                                            (unsigned long long)total);
     b->total_tiles = total;
-    const uint64_t nb = fbg::scan_block_count(total);
+    const uint64_t nb = std::max<uint64_t>(fbg::tile_list_blocks(total), 1);
     e = hipMalloc((void **)&b->d_tile_counts, std::max<uint64_t>(total, 1) * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipMalloc((void **)&b->d_offsets, std::max<uint64_t>(total, 1) * sizeof(uint64_t));
-    if (e == hipSuccess) e = hipMalloc((void **)&b->d_scan_blk, (nb + 2) * sizeof(uint64_t));
+    if (e == hipSuccess) e = hipMalloc((void **)&b->d_tile_list, std::max<uint64_t>(total, 1) * sizeof(uint64_t));
+    if (e == hipSuccess) e = hipMalloc((void **)&b->d_list_sums, nb * sizeof(fbg::TilePair));
+    if (e == hipSuccess) e = hipMalloc((void **)&b->d_list_base, (nb + 1 + (uint64_t)b->np) * sizeof(uint64_t));
     if (e == hipSuccess) e = hipMalloc((void **)&b->d_enum, (size_t)b->np * sizeof(fbg::EnumProg));
-    if (e == hipSuccess) e = hipMalloc((void **)&b->d_tile_list, (std::max<uint64_t>(total, 1) + 64) * sizeof(uint32_t));
     if (e == hipSuccess && chunks) e = hipMalloc((void **)&b->d_chunk_counts, chunks * sizeof(uint32_t));
     if (e != hipSuccess) return fail(FBG_E_NOMEM, "enumeration buffers: %s", hipGetErrorString(e));
   }
@@ -1131,22 +1188,28 @@ fbg_status fbg_batch_enumerate(fbg_batch *b, void *stream) {
   fbg_status st = check_device(b->device);
   if (st) return st;
   hipStream_t s = (hipStream_t)stream;
-  const uint64_t nb = fbg::scan_block_count(b->total_tiles);
-  hipError_t e = fbg::launch_scan(b->d_tile_counts, b->total_tiles, b->d_offsets, b->d_scan_blk,
-                                  b->d_scan_blk + nb + 1, s);
-  if (e != hipSuccess) return hip_fail(e, "launch of the tile-count scan");
+  const uint64_t nb = fbg::tile_list_blocks(b->total_tiles);
+  fbg::TileListArgs l;
+  l.counts = b->d_tile_counts;
+  l.n = b->total_tiles;
+  l.sums = b->d_list_sums;
+  l.list = b->d_tile_list;
+  l.list_base = b->d_list_base;
+  l.nlist = b->d_list_base + nb;
+  l.total = nullptr;
+  l.progs = b->d_enum;
+  l.prog_base = b->d_list_base + nb + 1;
+  l.np = (uint32_t)b->np;
+  hipError_t e = fbg::launch_tile_list(l, s);
+  if (e != hipSuccess) return hip_fail(e, "launch of the tile listing");
   fbg::BatchEnumArgs a;
   a.progs = b->d_enum;
   a.np = (uint32_t)b->np;
-  a.total_tiles = b->total_tiles;
-  a.tile_counts = b->d_tile_counts;
-  a.offsets = b->d_offsets;
-  a.list = b->d_tile_list;
-  a.nlist = b->d_tile_list + std::max<uint64_t>(b->total_tiles, 1);
+  a.list = l.list;
+  a.list_base = l.list_base;
+  a.nlist = l.nlist;
+  a.prog_base = l.prog_base;
   const int grid = cu_count(b->device) * 8;
-  e = fbg::launch_zero(nullptr, 0, a.nlist, 1, s);
-  if (e == hipSuccess) e = fbg::launch_list_tiles(a, grid, s);
-  if (e != hipSuccess) return hip_fail(e, "launch of the tile listing");
   for (const auto &pl : b->plans) {
     e = fbg::launch_batch_compact(pl.log2w, a, grid, 256, s);
     if (e != hipSuccess) return hip_fail(e, "launch of the compaction kernel");
@@ -1202,8 +1265,8 @@ void fbg_batch_free(fbg_batch *b) {
   if (b->d_progs_dnf) (void)hipFree(b->d_progs_dnf);
   if (b->d_tile_counts) (void)hipFree(b->d_tile_counts);
   if (b->d_chunk_counts) (void)hipFree(b->d_chunk_counts);
-  if (b->d_offsets) (void)hipFree(b->d_offsets);
-  if (b->d_scan_blk) (void)hipFree(b->d_scan_blk);
+  if (b->d_list_sums) (void)hipFree(b->d_list_sums);
+  if (b->d_list_base) (void)hipFree(b->d_list_base);
   if (b->d_enum) (void)hipFree(b->d_enum);
   if (b->d_tile_list) (void)hipFree(b->d_tile_list);
   for (auto &pl : b->plans) {

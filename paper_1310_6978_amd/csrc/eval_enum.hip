@@ -26,8 +26,10 @@ hipError_t launch_mode(int log2w, int var, const EvalArgs &a, int grid, int bloc
   switch (var) {
     case 0: return launch_w<MODE, 0>(log2w, a, grid, block, lds, s);
     case 1: return launch_w<MODE, 1>(log2w, a, grid, block, lds, s);
-    case 2: return launch_w<MODE, 2>(log2w, a, grid, block, lds, s);
-    case 3: return launch_w<MODE, 3>(log2w, a, grid, block, lds, s);
+  }
+  if constexpr (MODE != dev::MODE_ENUM) {  // the tiles of the compaction pass hold models: no cofactor variant
+    if (var == 2) return launch_w<MODE, 2>(log2w, a, grid, block, lds, s);
+    if (var == 3) return launch_w<MODE, 3>(log2w, a, grid, block, lds, s);
   }
   return hipErrorInvalidValue;
 }
@@ -55,9 +57,12 @@ int occ_mode(int log2w, int var, int block, size_t lds) {
   switch (var) {
     case 0: return occ_w<MODE, 0>(log2w, block, lds);
     case 1: return occ_w<MODE, 1>(log2w, block, lds);
-    case 2: return occ_w<MODE, 2>(log2w, block, lds);
-    default: return occ_w<MODE, 3>(log2w, block, lds);
   }
+  if constexpr (MODE != dev::MODE_ENUM) {
+    if (var == 2) return occ_w<MODE, 2>(log2w, block, lds);
+    if (var == 3) return occ_w<MODE, 3>(log2w, block, lds);
+  }
+  return 1;
 }
 
 }  // namespace

@@ -17,6 +17,11 @@ constexpr uint32_t kVgprRegs = 4;
 constexpr uint32_t kJ16VgprRegs = FBG_J16_VGPR_REGS;
 inline uint32_t vgpr_regs_of(int log2w) { return log2w == FBG_J16_LOG2W ? kJ16VgprRegs : kVgprRegs; }
 
+// Models a wave of an enumeration pass gathers in LDS before they leave: a
+// row of 64 words holds at most this many.
+constexpr uint32_t kStageModels = 2048;
+constexpr uint32_t kStageWords = kStageModels / 2;  // as 32-bit words: 4 KiB a wave
+
 struct EvalArgs {
   const uint32_t *code;   // encoded program: clause block, instructions, pattern table
   uint32_t nins;          // instructions after the clause block (16 words per lane: 2-word units)
@@ -29,7 +34,15 @@ struct EvalArgs {
   uint64_t out_slices;    // MODE_DNF: words written (>= nslices, >= 2)
   const uint32_t *xcd_code;  // MODE_DNF at 32 words per lane: the XCD-local encoding, or null
   uint32_t *tile_counts;  // MODE_TILECNT (out), MODE_ENUM (in)
-  const uint64_t *tile_offsets;  // MODE_ENUM
+  // MODE_ENUM: with tiles_per_block > 0 (a multiple of 4, at most 64) the blocks
+  // take that many tiles each and find their positions from tile_counts, the
+  // last one writing the total to out_count; else the list of the tiles that
+  // hold models (TileListArgs)
+  uint32_t tiles_per_block;
+  uint32_t lds_stride;    // words of LDS per wave: its registers, at least kStageWords
+  const uint64_t *list;
+  const uint64_t *list_base;
+  const uint64_t *nlist;
   uint64_t *out_idx;      // MODE_ENUM
   uint64_t capacity;      // MODE_ENUM
   // non-zero: the jump-table interpreter (16 words per lane) runs the copy of
@@ -85,11 +98,30 @@ struct EnumProg {
 struct BatchEnumArgs {
   const EnumProg *progs;
   uint32_t np;
-  uint64_t total_tiles;
-  const uint32_t *tile_counts;  // all programs, concatenated
-  const uint64_t *offsets;      // exclusive scan of tile_counts
-  uint32_t *list;               // tiles holding models (k_list_tiles)
-  uint32_t *nlist;              // their number (zeroed before k_list_tiles)
+  const uint64_t *list;       // the tiles holding models (TileListArgs)
+  const uint64_t *list_base;
+  const uint64_t *nlist;
+  const uint64_t *prog_base;  // models before each program's first tile
+};
+
+// From the model counts of n tiles (n >= 1) to the list of the tiles that
+// hold models and the positions of their models (k_tile_sums, k_tile_list).
+// Tiles go in blocks of kListBlock, nb = tile_list_blocks(n) of them.
+constexpr uint32_t kListBlock = 2048;
+struct TilePair {
+  uint64_t models, tiles;
+};
+struct TileListArgs {
+  const uint32_t *counts;  // n tile counts, 256-byte aligned
+  uint64_t n;
+  TilePair *sums;       // nb: per block (temporary)
+  uint64_t *list;       // up to n entries: tile | models before it in its block << 32
+  uint64_t *list_base;  // nb: models before each block
+  uint64_t *nlist;      // length of the list
+  uint64_t *total;      // number of models (or null)
+  const EnumProg *progs = nullptr;  // np > 0: prog_base[p] = models before progs[p].tile0
+  uint64_t *prog_base = nullptr;
+  uint32_t np = 0;
 };
 
 struct BatchItem {
@@ -137,11 +169,9 @@ hipError_t launch_batch_direct(int log2w, const BatchArgs &a, int grid, int bloc
 // Resident blocks per compute unit of an evaluator or batch launch.
 int eval_blocks_per_cu(int mode, int log2w, int var, int block, size_t lds);
 int batch_blocks_per_cu(int mode, int log2w, int var, int block, size_t lds);
-hipError_t launch_list_tiles(const BatchEnumArgs &a, int grid, hipStream_t s);
 hipError_t launch_batch_compact(int log2w, const BatchEnumArgs &a, int grid, int block, hipStream_t s);
-hipError_t launch_scan(const uint32_t *in, uint64_t n, uint64_t *out, uint64_t *block_sums, uint64_t *total,
-                       hipStream_t s);
-uint64_t scan_block_count(uint64_t n);
+hipError_t launch_tile_list(const TileListArgs &a, hipStream_t s);
+uint64_t tile_list_blocks(uint64_t n);
 // p[0..n) = 0 and head[0..nhead) = 0.
 hipError_t launch_zero(uint64_t *p, uint64_t n, uint32_t *head, uint32_t nhead, hipStream_t s);
 hipError_t launch_set_u64(uint64_t *p, uint64_t v, hipStream_t s);

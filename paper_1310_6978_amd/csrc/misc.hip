@@ -1,5 +1,5 @@
-// misc.hip -- launches of the small kernels (stored-DNF scans, the exclusive
-// scan of per-tile counts, fills) and the per-mode dispatch of the
+// misc.hip -- launches of the small kernels (stored-DNF scans, the lists
+// of the tiles that hold models, fills) and the per-mode dispatch of the
 // single-program evaluator (its kernels live in eval_*.hip).
 #define FBG_DEVICE_MISC_KERNELS
 #include "fbg_device.h"
@@ -43,20 +43,20 @@ hipError_t launch_dnf_scan(int mode, const EvalArgs &a, int grid, int block, hip
   return hipGetLastError();
 }
 
-hipError_t launch_scan(const uint32_t *in, uint64_t n, uint64_t *out, uint64_t *block_sums, uint64_t *total,
-                       hipStream_t s) {
-  const uint64_t nb = (n + dev::SCAN_BLOCK - 1) / dev::SCAN_BLOCK;
-  if (nb == 0) {
-    hipLaunchKernelGGL(dev::k_set_u64, dim3(1), dim3(64), 0, s, total, (uint64_t)0);
-    return hipGetLastError();
+uint64_t tile_list_blocks(uint64_t n) { return (n + kListBlock - 1) / kListBlock; }
+
+hipError_t launch_tile_list(const TileListArgs &a, hipStream_t s) {
+  const uint64_t nb = tile_list_blocks(a.n);
+  hipLaunchKernelGGL(dev::k_tile_sums, dim3((unsigned)nb), dim3(dev::LIST_THREADS), 0, s, a);
+  if (nb <= 1024) {
+    // every block adds up the (at most 16 KiB of) sums before it
+    hipLaunchKernelGGL((dev::k_tile_list<false>), dim3((unsigned)nb), dim3(dev::LIST_THREADS), 0, s, a);
+  } else {
+    hipLaunchKernelGGL(dev::k_tile_sums_scan, dim3(1), dim3(dev::LIST_THREADS), 0, s, a, nb);
+    hipLaunchKernelGGL((dev::k_tile_list<true>), dim3((unsigned)nb), dim3(dev::LIST_THREADS), 0, s, a);
   }
-  hipLaunchKernelGGL(dev::k_scan_reduce, dim3((unsigned)nb), dim3(dev::SCAN_THREADS), 0, s, in, n, block_sums);
-  hipLaunchKernelGGL(dev::k_scan_sums, dim3(1), dim3(dev::SCAN_THREADS), 0, s, block_sums, nb, total);
-  hipLaunchKernelGGL(dev::k_scan_apply, dim3((unsigned)nb), dim3(dev::SCAN_THREADS), 0, s, in, n, block_sums, out);
   return hipGetLastError();
 }
-
-uint64_t scan_block_count(uint64_t n) { return (n + dev::SCAN_BLOCK - 1) / dev::SCAN_BLOCK; }
 
 hipError_t launch_zero(uint64_t *p, uint64_t n, uint32_t *head, uint32_t nhead, hipStream_t s) {
   if (!head) nhead = 0;

@@ -1,0 +1,116 @@
+"""Enumeration at the edges of its paths: lists staged through LDS in one and
+in many flushes, blocks that find their own positions up to 16384 tiles and
+the list of the tiles with models beyond, programs of a batch that start
+inside a block of that list, truncated lists.  Against the oracle."""
+
+import random
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from formula_gen import many_registers, random_cnf
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def F():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a HIP device")
+    from paper_1310_6978_amd import fbg
+    return fbg
+
+
+def lists(call, want, caps):
+    """call(capacity, out, total) fills out; the first `capacity` models and
+    no word beyond them are written."""
+    import torch
+    for cap in caps:
+        out = torch.full((cap + 3,), -7, dtype=torch.int64, device="cuda")
+        tot = torch.full((1,), -1, dtype=torch.int64, device="cuda")
+        call(cap, out, tot)
+        torch.cuda.synchronize()
+        got = out.cpu().numpy()
+        k = min(cap, len(want))
+        assert int(tot.item()) == len(want)
+        assert np.array_equal(got[:k].view(np.uint64), want[:k])
+        assert (got[k:] == -7).all()
+
+
+def formulas():
+    rng = random.Random(11)
+    return {
+        "half": lambda n: "x%d\n" % (n - 1),                  # every word of half of the tiles full
+        "odd": lambda n: " ^ ".join("x%d" % k for k in range(n)) + "\n",   # 16 models in every word
+        "sparse": lambda n: random_cnf(rng, n, 3 * n, (2, 4)),
+        "one": lambda n: "\n".join("%sx%d" % ("~" if k % 3 == 0 else "", k) for k in range(n)) + "\n",
+        "general": lambda n: many_registers(rng, n, 9),
+    }
+
+
+@pytest.mark.parametrize("kind", ["half", "odd", "sparse", "one", "general"])
+@pytest.mark.parametrize("wpl", [1, 2, 8, 16, 32])
+@pytest.mark.parametrize("n", [3, 11, 13, 17])
+def test_lists(F, kind, wpl, n):
+    text = formulas()[kind](max(n, 4) if kind == "general" else n)
+    n = max(n, 4) if kind == "general" else n
+    p = F.Program(text, n)
+    p.set_tuning(wpl)
+    want, c = oracle.models(text, n)
+    dnf = F.eval_dnf(p)
+    caps = [c + 1, max(0, c // 2), 0]
+    print("lists", kind, wpl, n, c, flush=True)
+    lists(lambda cap, out, tot: F.enumerate_models(p, cap, out=out, total=tot), want, caps)
+    lists(lambda cap, out, tot: F.enumerate_dnf(dnf, n, cap, out=out, total=tot), want, caps)
+
+
+@pytest.mark.parametrize("n,wpl", [(24, 1), (25, 1), (26, 1), (27, 2)])
+@pytest.mark.parametrize("cofactor", [False, True])
+def test_tile_thresholds(F, n, wpl, cofactor):
+    """16384 tiles (n = 25 at one word per lane) are the last without a list."""
+    text = workloads.random_3cnf(n, 3 * n, n)[0]
+    p = F.Program(text, n)
+    p.set_tuning(wpl, cofactor=cofactor)
+    ref = F.Program(text, n)
+    want = F.eval_dnf(ref)
+    want = np.flatnonzero(np.unpackbits(want.cpu().numpy().view(np.uint8), bitorder="little")).astype(np.uint64)
+    assert len(want) == oracle.count(text, n)
+    print("thresholds", n, wpl, cofactor, len(want), flush=True)
+    lists(lambda cap, out, tot: F.enumerate_models(p, cap, out=out, total=tot), want, [len(want) + 1, 100])
+
+
+def test_more_blocks_than_are_summed(F):
+    """Over 1024 blocks of the list (n = 33 at one word per lane: 2048)."""
+    text = workloads.random_3cnf(33, 132, 5)[0]
+    p, q = F.Program(text, 33), F.Program(text, 33)
+    q.set_tuning(32)
+    p.set_tuning(1)
+    total = int(F.count(q).item())
+    a, ta = F.enumerate_models(p, total + 1)
+    b, tb = F.enumerate_models(q, total + 1)
+    assert total > 0 and int(ta.item()) == int(tb.item()) == total
+    assert np.array_equal(a.cpu().numpy()[:total], b.cpu().numpy()[:total])
+
+
+@pytest.mark.parametrize("wpl", [0, 1])
+def test_batch_programs_inside_list_blocks(F, wpl):
+    import torch
+    rng = random.Random(3)
+    ns = [5, 13, 20, 11, 22, 17, 12, 21]
+    texts = [random_cnf(rng, n, 2 * n, (2, 4)) if i % 3 else "x%d ^ x0\n" % (n - 1) for i, n in enumerate(ns)]
+    progs = [F.Program(t, n) for t, n in zip(texts, ns)]
+    wants = [oracle.models(t, n)[0] for t, n in zip(texts, ns)]
+    b = F.Batch(progs, words_per_lane=wpl)
+    b.set_dnf_outputs([torch.empty(F.dnf_words(n), dtype=torch.int64, device="cuda") for n in ns])
+    outs = [torch.full((len(w) + 2,), -7, dtype=torch.int64, device="cuda") for w in wants]
+    b.set_enum_outputs(outs)
+    for _ in range(2):
+        counts = b.eval_dnf()
+        b.enumerate()
+        torch.cuda.synchronize()
+        for o, w, c in zip(outs, wants, counts.cpu().tolist()):
+            got = o.cpu().numpy()
+            assert c == len(w) and np.array_equal(got[:c].view(np.uint64), w) and (got[c:] == -7).all()
