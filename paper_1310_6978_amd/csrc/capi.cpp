@@ -379,70 +379,60 @@ fbg::BatchProg batch_prog(const fbg_program *p, int l) {
   return b;
 }
 
-// Programs and vectors of at most this many tiles are enumerated in two
-// launches: the tile counts, then compaction blocks that add up the counts of
-// the tiles before them themselves (a block reads at most 64 KiB of them from
-// L2).  Beyond it the tiles that hold models are listed first
-// (launch_tile_list), which also spreads them evenly over the waves when few
-// tiles of many hold models.  8192 tiles of 1024 words each holding models
-// (triangle-free graphs, n = 28): 3 launches fewer, see k_tile_list for theirs.
-constexpr uint64_t kDirectEnumTiles = 16384;
+// Up to this many units (fbg_device.h) an enumeration is two launches: the
+// counts, then compaction blocks that add up the counts before them themselves.
+// Beyond it the units that hold models are listed first (launch_tile_list, two
+// small launches, about 5 us each), which also spreads them evenly over the
+// waves.  A stored vector's counting pass leaves the sums of its blocks too, so
+// that four times as many tiles can be added up.
+constexpr uint64_t kDirectUnits = 4096;
+constexpr uint64_t kDirectScanTiles = 16384;
 
-// The enumeration temporaries for nt tiles, each part 256-byte aligned:
-// per-tile uint32 counts and, beyond kDirectEnumTiles, the list of the tiles
-// that hold models (TileListArgs).
+// The enumeration temporaries for nu units, each part 256-byte aligned:
+// per-unit uint32 counts and, in a direct pass, sums of wpb of them each
+// (`sums`), else the list of the units that hold models (TileListArgs).
 struct EnumTemp {
   size_t list = 0, sums = 0, base = 0, nlist = 0, bytes = 0;  // offsets, and the size of all
 };
 
-EnumTemp enum_temp(uint64_t nt) {
+EnumTemp enum_temp(uint64_t nu, bool direct) {
   auto up = [](size_t b) { return (b + 255) / 256 * 256; };
   EnumTemp t;
-  t.list = up(nt * 4);
-  t.bytes = t.list;
-  if (nt <= kDirectEnumTiles) return t;
-  const uint64_t nb = fbg::tile_list_blocks(nt);
-  t.sums = t.list + up(nt * 8);
+  t.list = t.sums = up(nu * 4);
+  t.bytes = t.list + up(nu);
+  if (direct) return t;
+  const uint64_t nb = fbg::tile_list_blocks(nu);
+  t.sums = t.list + up(nu * 8);
   t.base = t.sums + up(nb * sizeof(fbg::TilePair));
   t.nlist = t.base + up(nb * 8);
   t.bytes = t.nlist + 256;
   return t;
 }
 
-// Blocks of a compaction pass.
-struct EnumShape {
-  int wpb, resident;  // waves per block; blocks that fill the device
-};
-
 // Two-pass enumeration given the pass launcher and the temporaries `tmp`
-// (enum_temp(a.ntiles).bytes of device memory): tile counts, the list of the
-// tiles that hold models unless there are few tiles, compaction.  Every
-// temporary word is written before it is read.  With zero_counts (the
-// uniform-cofactor passes, which write the counts of live tiles only) a fill
-// kernel clears the tile counts first, in one coalesced sweep instead of a
-// scattered write per dead tile.
+// (enum_temp(a.nunits, a.direct).bytes of device memory): counts per unit, the
+// list of the units that hold models unless direct, compaction.  Every
+// temporary word is written before it is read.  pass.zero_counts (the
+// uniform-cofactor passes, which write the counts of live tiles only): a fill
+// kernel clears the counts first, in one coalesced sweep instead of a scattered
+// write per dead tile.
 template <typename Pass>
-hipError_t enumerate_passes(fbg::EvalArgs a, const EnumShape &sh, char *tmp, uint64_t *d_idx, uint64_t capacity,
-                            uint64_t *d_total, hipStream_t s, bool zero_counts, Pass pass) {
-  const uint64_t nt = a.ntiles;
-  const EnumTemp t = enum_temp(nt);
-  uint32_t *cnt = (uint32_t *)tmp;
-  a.tile_counts = cnt;
-  hipError_t e = zero_counts ? fbg::launch_zero((uint64_t *)cnt, t.list / 8, nullptr, 0, s) : hipSuccess;
-  if (e == hipSuccess) e = pass(fbg::EVAL_TILECNT, a, 0);
+hipError_t enumerate_passes(fbg::EvalArgs a, char *tmp, uint64_t *d_idx, uint64_t capacity, uint64_t *d_total,
+                            hipStream_t s, const Pass &pass) {
+  const EnumTemp t = enum_temp(a.nunits, a.direct);
+  a.tile_counts = (uint32_t *)tmp;
+  if (pass.block_sums && a.direct) a.block_sums = (uint32_t *)(tmp + t.sums);
+  hipError_t e = hipSuccess;
+  if (pass.zero_counts()) e = fbg::launch_zero((uint64_t *)tmp, t.list / 8, nullptr, 0, s);
+  if (e == hipSuccess) e = pass(fbg::EVAL_TILECNT, a);
   if (e != hipSuccess) return e;
   a.out_idx = d_idx;
   a.capacity = capacity;
-  if (nt <= kDirectEnumTiles) {
-    // a multiple of 4 tiles per block, over about the blocks that fill the device
-    const uint64_t per = (nt + 4 * (uint64_t)sh.resident - 1) / (4 * (uint64_t)sh.resident);
-    a.tiles_per_block = (uint32_t)(4 * std::min<uint64_t>(per, 16));
-    a.out_count = d_total;
-    return pass(fbg::EVAL_ENUM, a, (int)((nt + a.tiles_per_block - 1) / a.tiles_per_block));
-  }
+  a.out_count = d_total;
+  if (a.direct) return pass(fbg::EVAL_ENUM, a);
   fbg::TileListArgs l;
-  l.counts = cnt;
-  l.n = nt;
+  l.counts = a.tile_counts;
+  l.n = a.nunits;
   l.list = (uint64_t *)(tmp + t.list);
   l.sums = (fbg::TilePair *)(tmp + t.sums);
   l.list_base = (uint64_t *)(tmp + t.base);
@@ -450,49 +440,72 @@ hipError_t enumerate_passes(fbg::EvalArgs a, const EnumShape &sh, char *tmp, uin
   l.total = d_total;
   e = fbg::launch_tile_list(l, s);
   if (e != hipSuccess || capacity == 0) return e;
-  a.tiles_per_block = 0;
   a.list = l.list;
   a.list_base = l.list_base;
   a.nlist = l.nlist;
-  return pass(fbg::EVAL_ENUM, a, sh.resident);
+  return pass(fbg::EVAL_ENUM, a);
 }
 
 // The same with the temporaries allocated on the stream and freed after.
 template <typename Pass>
-fbg_status enumerate_with(fbg::EvalArgs a, const EnumShape &sh, uint64_t *d_idx, uint64_t capacity,
-                          uint64_t *d_total, hipStream_t s, bool zero_counts, Pass pass) {
-  const size_t bytes = enum_temp(a.ntiles).bytes;
+fbg_status enumerate_with(const fbg::EvalArgs &a, uint64_t *d_idx, uint64_t capacity, uint64_t *d_total,
+                          hipStream_t s, const Pass &pass) {
+  const size_t bytes = enum_temp(a.nunits, a.direct).bytes;
   char *tmp = nullptr;
   hipError_t e = hipMallocAsync((void **)&tmp, bytes, s);
   if (e != hipSuccess) return fail(FBG_E_NOMEM, "hipMallocAsync of %zu bytes: %s", bytes, hipGetErrorString(e));
-  e = enumerate_passes(a, sh, tmp, d_idx, capacity, d_total, s, zero_counts, pass);
+  e = enumerate_passes(a, tmp, d_idx, capacity, d_total, s, pass);
   hipError_t e2 = hipFreeAsync(tmp, s);
   if (e != hipSuccess) return hip_fail(e, "launch of an enumeration kernel");
   if (e2 != hipSuccess) return hip_fail(e2, "hipFreeAsync");
   return FBG_OK;
 }
 
-// The passes of enumerating a program: the counts on geometry g, the
-// compaction (grid > 0 blocks, the same block size) with kStageWords of LDS per
-// wave at least.  (The compaction needs no cofactor variant: its tiles hold models.)
+// The passes of enumerating a program: the counts on geometry g; the
+// compaction in blocks of the same size, with LDS to gather models in.  (The
+// compaction needs no cofactor variant: its tiles hold models.)
 struct EvalPasses {
+  static constexpr bool block_sums = false;
   const fbg_program *p;
   Geometry g;
   int var;
   hipStream_t s;
-  EnumShape shape() const {
-    const int wpb = g.block / 64;
-    const int occ = fbg::eval_blocks_per_cu(fbg::EVAL_ENUM, g.log2w, var & 1, g.block, enum_lds());
-    return {wpb, cu_count(p->device) * occ};
+  bool zero_counts() const { return (var & 2) != 0; }
+  // Tiles are cut into units of at least four rows while there are fewer than
+  // 32768: the models of a theory crowd into few tiles, and the fullest unit
+  // is what the compaction waits for (tile_compact).
+  fbg::EvalArgs args() const {
+    fbg::EvalArgs a = base_args(p, g.log2w);
+    while (g.log2w - (int)a.unit_shift > 2 && (a.ntiles << a.unit_shift) < 32768) a.unit_shift++;
+    a.nunits = a.ntiles << a.unit_shift;
+    if (a.nunits <= kDirectUnits) a.direct = 1;
+    return a;
   }
-  size_t wave_lds() const {
-    return std::max(lds_per_wave((uint32_t)p->c.nregs, g.log2w), (size_t)fbg::kStageWords * 4);
-  }
-  size_t enum_lds() const { return wave_lds() * (size_t)(g.block / 64); }
-  hipError_t operator()(int mode, fbg::EvalArgs a, int grid) const {
+  hipError_t operator()(int mode, fbg::EvalArgs a) const {
     if (mode != fbg::EVAL_ENUM) return fbg::launch_eval(mode, g.log2w, var, a, g.grid, g.block, g.lds, s);
-    a.lds_stride = (uint32_t)(wave_lds() / 4);
-    return fbg::launch_eval(mode, g.log2w, var & 1, a, grid, g.block, enum_lds(), s);
+    const size_t wpb = (size_t)g.block / 64;
+    const size_t wave = std::max(lds_per_wave((uint32_t)p->c.nregs, g.log2w), (size_t)fbg::kStageModels * 2);
+    a.lds_stride = (uint32_t)(wave / 4);
+    const uint64_t blocks = (a.nunits + wpb - 1) / wpb;
+    uint64_t grid = blocks;
+    if (!a.direct)
+      grid = std::min<uint64_t>(blocks, (uint64_t)cu_count(p->device) *
+                                            (uint64_t)fbg::eval_blocks_per_cu(mode, g.log2w, var & 1, g.block, wave * wpb));
+    return fbg::launch_eval(mode, g.log2w, var & 1, a, (int)grid, g.block, wave * wpb, s);
+  }
+};
+
+// The passes of enumerating a stored vector: tiles of 8 KiB, of 1 KiB up to
+// n = 27 so that small vectors still fill the device.
+struct ScanPasses {
+  static constexpr bool block_sums = true;
+  int dev, log2w;
+  hipStream_t s;
+  bool zero_counts() const { return false; }
+  hipError_t operator()(int mode, const fbg::EvalArgs &a) const {
+    const uint64_t blocks = (a.ntiles + kWavesPerBlock - 1) / kWavesPerBlock;
+    const uint64_t grid = a.direct ? blocks : std::min<uint64_t>(blocks, (uint64_t)cu_count(dev) * 8);
+    return fbg::launch_dnf_scan(mode, log2w, a, (int)grid, 64 * kWavesPerBlock, s);
   }
 };
 
@@ -759,8 +772,7 @@ fbg_status fbg_enumerate(const fbg_program *p, uint64_t *d_idx, uint64_t capacit
   Geometry g;
   if ((st = geometry(p, nullptr, fbg::EVAL_TILECNT, g))) return st;
   const EvalPasses pass{p, g, p->variant(nullptr), (hipStream_t)stream};
-  return enumerate_with(base_args(p, g.log2w), pass.shape(), d_idx, capacity, d_total, pass.s, (pass.var & 2) != 0,
-                        pass);
+  return enumerate_with(pass.args(), d_idx, capacity, d_total, pass.s, pass);
 }
 
 fbg_status fbg_enumerate_noalloc(const fbg_program *p, uint64_t *d_idx, uint64_t capacity, uint64_t *d_total,
@@ -772,8 +784,9 @@ fbg_status fbg_enumerate_noalloc(const fbg_program *p, uint64_t *d_idx, uint64_t
     return fail(FBG_E_INVAL, "d_idx is NULL with capacity %llu", (unsigned long long)capacity);
   Geometry g;
   if ((st = geometry(p, nullptr, fbg::EVAL_TILECNT, g))) return st;
-  const fbg::EvalArgs a = base_args(p, g.log2w);
-  const size_t bytes = enum_temp(a.ntiles).bytes;
+  const EvalPasses pass{p, g, p->variant(nullptr), (hipStream_t)stream};
+  const fbg::EvalArgs a = pass.args();
+  const size_t bytes = enum_temp(a.nunits, a.direct).bytes;
   if (a.ntiles > fbg::kNoallocMaxTiles || bytes > fbg::kNoallocScratchBytes)
     return fail(FBG_E_RANGE,
                 "fbg_enumerate_noalloc: %llu tiles at %d words per lane need %zu bytes of scratch; the static "
@@ -783,8 +796,7 @@ fbg_status fbg_enumerate_noalloc(const fbg_program *p, uint64_t *d_idx, uint64_t
   void *scratch = nullptr;
   hipError_t e = fbg::noalloc_scratch(&scratch);
   if (e != hipSuccess) return hip_fail(e, "address of the static scratch");
-  const EvalPasses pass{p, g, p->variant(nullptr), (hipStream_t)stream};
-  e = enumerate_passes(a, pass.shape(), (char *)scratch, d_idx, capacity, d_total, pass.s, (pass.var & 2) != 0, pass);
+  e = enumerate_passes(a, (char *)scratch, d_idx, capacity, d_total, pass.s, pass);
   return e == hipSuccess ? FBG_OK : hip_fail(e, "launch of an enumeration kernel");
 }
 
@@ -801,15 +813,11 @@ fbg_status fbg_enumerate_dnf(const uint64_t *d_dnf, int32_t n_vars, uint64_t *d_
   memset(&a, 0, sizeof a);
   a.n = n_vars;
   a.nslices = 2 * dnf_words_of(n_vars);  // bits at or above 2^n are zero in a DNF vector
-  a.ntiles = tiles_of(a.nslices, 5);
+  const ScanPasses pass{dev, n_vars <= 27 ? 2 : 5, (hipStream_t)stream};
+  a.nunits = a.ntiles = tiles_of(a.nslices, pass.log2w);
+  a.direct = a.nunits <= kDirectScanTiles;
   a.out32 = (uint32_t *)d_dnf;
-  const uint64_t blocks = (a.ntiles + kWavesPerBlock - 1) / kWavesPerBlock;
-  const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>(blocks, (uint64_t)cu_count(dev) * 8));
-  hipStream_t s = (hipStream_t)stream;
-  return enumerate_with(a, {kWavesPerBlock, cu_count(dev) * 8}, d_idx, capacity, d_total, s, false,
-                        [&](int mode, const fbg::EvalArgs &aa, int g) {
-                          return fbg::launch_dnf_scan(mode, aa, g > 0 ? g : grid, 64 * kWavesPerBlock, s);
-                        });
+  return enumerate_with(a, d_idx, capacity, d_total, pass.s, pass);
 }
 
 // ------------------------------------------------------------------ batches

@@ -581,97 +581,68 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
   return v;
 }
 
-// Enumeration epilogues shared by the evaluator and the stored-DNF path.
+// Enumeration epilogues shared by the evaluator and the stored-DNF path.  A
+// unit of the two passes is 2^-shift of a tile: W >> shift rows, at least four
+// of them when shift > 0.
+
+// The model counts of a tile's units to dst[0 ..].
 template <int LOG2W>
-__device__ __forceinline__ void tile_count_out(const uint32_t (&acc)[1 << LOG2W], uint32_t lane, uint32_t *dst) {
+__device__ __forceinline__ void tile_count_out(const uint32_t (&acc)[1 << LOG2W], uint32_t lane, uint32_t shift,
+                                               uint32_t *dst) {
+  constexpr uint32_t W = 1u << LOG2W, STEP = W < 4 ? W : 4;
+  const uint32_t rows = W >> shift;
   uint32_t c = 0;
 #pragma unroll
-  for (int i = 0; i < (1 << LOG2W); i++) c += __popc(acc[i]);
-  c = wave_sum_u32(c);
-  if (lane == 0) *dst = c;
-}
-
-// Write n staged models (their offsets in the tile that starts at valuation
-// vbase) to out[base ..], one per lane and step.  The LDS entries may share
-// their words with the registers of the general part (another type to the
-// compiler): nothing moves across the two barriers.
-__device__ __forceinline__ void flush_stage(const uint16_t *stage, uint32_t n, uint32_t lane, uint64_t vbase,
-                                            uint64_t base, uint64_t *out, uint64_t capacity) {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_wave_barrier();
-  for (uint32_t k = lane; k < n; k += 64)
-    if (base + k < capacity) out[base + k] = vbase + stage[k];
-  __builtin_amdgcn_wave_barrier();
-  asm volatile("" ::: "memory");
-}
-
-// Compaction passes find the output position of a tile's models in one of two
-// ways (the host chooses, capi.cpp):
-//  - few tiles (a.tiles_per_block > 0): block b takes tiles
-//    [b T, (b + 1) T), T = a.tiles_per_block <= 64, and adds up the counts of all
-//    tiles before them itself; no scan kernel runs.  The last block writes the
-//    total.
-//  - many tiles: the waves share out the list of tiles that hold models, with
-//    the positions k_tile_list found.
-// body(t, position) for each of this wave's tiles that holds models (LDS part:
-// one word pair per wave).
-template <typename Body>
-__device__ __forceinline__ void for_model_tiles(const EvalArgs &a, uint32_t lane, uint32_t wib, uint32_t wpb,
-                                                uint64_t *part, Body &&body) {
-  if (a.tiles_per_block) {
-    const uint32_t T = a.tiles_per_block, nt = (uint32_t)a.ntiles;
-    const uint32_t first = blockIdx.x * T, end = min(first + T, nt);
-    const uint32_t c = first + lane < end ? a.tile_counts[first + lane] : 0u;  // T <= 64
-    const bool last = end == nt;
-    const uint64_t own = __ballot(c != 0u);
-    if (own == 0ull && !last) return;  // the same for every wave of the block
-    // sum of the counts before the block: `first` is a multiple of 4
-    uint64_t s = 0;
-    for (uint32_t k = threadIdx.x * 4; k < first; k += blockDim.x * 4) {
-      const uint4 v = *(const uint4 *)(a.tile_counts + k);
-      s += (uint64_t)v.x + v.y + v.z + v.w;
+  for (uint32_t i = 0; i < W; i++) {
+    c += __popc(acc[i]);
+    if ((i + 1) % STEP == 0 && ((i + 1) & (rows - 1)) == 0) {  // wave-uniform: the unit's last row
+      const uint32_t sum = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(c), 63);
+      if (lane == 0) dst[i >> (LOG2W - shift)] = sum;
+      c = 0;
     }
-    s = wave_sum_u64(s);
-    if (lane == 0) part[wib] = s;
-    __syncthreads();
-    uint64_t base = 0;
-    for (uint32_t w = 0; w < wpb; w++) base += part[w];
-    const uint32_t incl = wave_inclusive_scan(c);  // at most 64 x 2^16
-    if (last && threadIdx.x == 0)
-      *a.out_count = base + (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-    if (a.capacity == 0) return;
-    for (uint32_t k = wib; first + k < end; k += wpb) {
-      if (!((own >> k) & 1ull)) continue;
-      const uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)(incl - c), (int)k);
-      body((uint64_t)(first + k), base + before);
-    }
-    return;
-  }
-  const uint64_t wave = (uint64_t)blockIdx.x * wpb + wib, nwaves = (uint64_t)gridDim.x * wpb;
-  const uint64_t n = *a.nlist;
-  for (uint64_t k = wave; k < n; k += nwaves) {
-    const uint64_t e = a.list[k];
-    const uint32_t t = uni((uint32_t)e);
-    body((uint64_t)t, a.list_base[t / kListBlock] + (e >> 32));
   }
 }
 
-// The models of one tile, ascending, to out[base ..] (below capacity).  The
-// words of a tile ascend with (i, lane): word (U0 + i) * 64 + lane; each row i
-// is ranked across the lanes (by its ballot when no word holds two models, by
-// a prefix sum of the popcounts otherwise).
-// What bounds it is the stores: written straight from the words every lane
-// stores 8 bytes at its own place, one store instruction per model of the
-// fullest lane of every row.  The offsets in the tile (16 bits: a tile has at
-// most 2^16 valuations) are gathered in the wave's kStageModels LDS entries
-// instead and leave 64 consecutive indices (512 bytes) to a store.
+// LDS traffic of a wave with itself: the compiler moves nothing across (the
+// words may also hold registers of the general part), and the hardware keeps a
+// wave's LDS accesses in order.
+__device__ __forceinline__ void wave_lds_fence() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// The models of rows [r0, r0 + rows) of a tile, ascending, to out[base ..]
+// (below capacity).  stage: this wave's kStageModels LDS entries.
+//
+// What bounds it is instruction issue and the fullest unit, then the stores.
+// Words ascend with (i, lane); each row i is ranked across the lanes (by its
+// ballot when no word holds two models, by a prefix sum of the popcounts
+// otherwise).  Stored straight from the words, every model is a lane's 8-byte
+// store at its own place; the offsets in the tile (16 bits: a tile has at most
+// 2^16 valuations) are gathered in LDS instead and leave 64 consecutive indices
+// (512 bytes) to a store.  Triangle-free graphs, n = 28 (32768 units of four
+// rows, 3.5 M models): 17 us, with whole tiles of 16 rows 44 us (the models
+// crowd into few tiles, 12,626 in one), the scattered stores took 94 us.
+// Giving every lane one model a step instead (a search for the word that owns
+// it) measured slower: 21 us.
 template <int LOG2W>
-__device__ __forceinline__ void tile_compact(const uint32_t (&acc)[1 << LOG2W], uint64_t U0, uint32_t lane,
-                                             uint64_t base, uint64_t *out, uint64_t capacity, uint16_t *stage) {
+__device__ __forceinline__ void tile_compact(const uint32_t (&acc)[1 << LOG2W], uint32_t r0, uint32_t rows,
+                                             uint64_t U0, uint32_t lane, uint64_t base, uint64_t *out,
+                                             uint64_t capacity, uint16_t *stage) {
   const uint64_t vbase = U0 * 2048;
   uint32_t fill = 0;
+  auto flush = [&]() __attribute__((always_inline)) {
+    wave_lds_fence();
+    for (uint32_t k = lane; k < fill; k += 64)
+      if (base + k < capacity) out[base + k] = vbase + stage[k];
+    wave_lds_fence();
+    base += fill;
+    fill = 0;
+  };
 #pragma unroll
   for (int i = 0; i < (1 << LOG2W); i++) {
+    if ((uint32_t)i - r0 >= rows) continue;  // wave-uniform: not a row of this unit
     uint32_t x = acc[i];
     const uint64_t any = __ballot(x != 0u);
     if (any == 0ull) continue;  // wave-uniform: no model in this word of any lane
@@ -685,11 +656,7 @@ __device__ __forceinline__ void tile_compact(const uint32_t (&acc)[1 << LOG2W], 
       before = incl - c;
       row = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
     }
-    if (fill + row > kStageModels) {
-      flush_stage(stage, fill, lane, vbase, base, out, capacity);
-      base += fill;
-      fill = 0;
-    }
+    if (fill + row > kStageModels) flush();
     uint32_t pos = fill + before;
     while (x) {
       stage[pos++] = (uint16_t)((i * 64 + lane) * 32 + (uint32_t)__builtin_ctz(x));
@@ -697,7 +664,57 @@ __device__ __forceinline__ void tile_compact(const uint32_t (&acc)[1 << LOG2W], 
     }
     fill += row;
   }
-  flush_stage(stage, fill, lane, vbase, base, out, capacity);
+  flush();
+}
+
+// Compaction passes find the output position of a unit's models in one of two
+// ways (the host chooses, capi.cpp):
+//  - few units (a.direct): block b takes the units [b wpb, (b + 1) wpb), one per
+//    wave, and adds up the counts of all units before them itself (their sums
+//    per block where the counting pass left them, a.block_sums); no scan kernel
+//    runs.  The last block writes the total.
+//  - many units: the waves share out the list of units that hold models, with
+//    the positions k_tile_list found.
+// body(u, position) for each of this wave's units that holds models.
+template <typename Body>
+__device__ __forceinline__ void for_model_units(const EvalArgs &a, uint32_t lane, uint32_t wib, uint32_t wpb,
+                                                uint64_t *part, Body &&body) {
+  // the steps this wave takes: one unit of the block, or entries of the list
+  uint64_t k = (uint64_t)blockIdx.x * wpb + wib, step = (uint64_t)gridDim.x * wpb, n, at = 0;
+  if (a.direct) {
+    n = a.nunits;
+    const uint32_t first = blockIdx.x * wpb;
+    const uint32_t c = lane < wpb && first + lane < (uint32_t)n ? a.tile_counts[first + lane] : 0u;
+    const bool last = blockIdx.x == gridDim.x - 1;
+    if (__ballot(c != 0u) == 0ull && !last) return;  // the same for every wave of the block
+    const uint32_t *in = a.block_sums ? a.block_sums : a.tile_counts;  // padded to 256 bytes
+    const uint32_t m = a.block_sums ? blockIdx.x : first;
+    uint64_t s = 0;
+    for (uint32_t i = threadIdx.x * 4; i < m; i += blockDim.x * 4) {
+      const uint4 v = *(const uint4 *)(in + i);
+      // at most 16 x 2^16: 32 bits
+      s += v.x + (i + 1 < m ? v.y : 0u) + (i + 2 < m ? v.z : 0u) + (i + 3 < m ? v.w : 0u);
+    }
+    s = wave_sum_u64(s);
+    if (lane == 0) part[wib] = s;
+    __syncthreads();
+    for (uint32_t w = 0; w < wpb; w++) at += part[w];
+    const uint32_t incl = wave_inclusive_scan(c);
+    if (last && threadIdx.x == 0) *a.out_count = at + (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    at += (uint32_t)__builtin_amdgcn_readlane((int)(incl - c), (int)wib);
+    if (a.capacity == 0 || __builtin_amdgcn_readlane((int)c, (int)wib) == 0) return;
+  } else {
+    n = *a.nlist;
+  }
+  for (; k < n; k += step) {
+    uint32_t u = (uint32_t)k;
+    if (!a.direct) {
+      const uint64_t e = a.list[k];
+      u = uni((uint32_t)e);
+      at = a.list_base[u / kListBlock] + (e >> 32);
+    }
+    body(u, at);
+  }
 }
 
 // DNF write-out and count of one tile: the words past the valuation space
@@ -777,13 +794,14 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_eval(EvalArgs a)
   if (MODE == MODE_ENUM) {
     // (the cofactor variant is not needed here: these tiles hold models)
     __shared__ uint64_t part[4];
-    for_model_tiles(a, lane, wib, wpb, part, [&](uint64_t t, uint64_t base) {
-      const uint64_t U0 = t << LOG2W;
+    for_model_units(a, lane, wib, wpb, part, [&](uint32_t u, uint64_t at) __attribute__((always_inline)) {
+      const uint64_t U0 = (uint64_t)(u >> a.unit_shift) << LOG2W;
+      const uint32_t rows = W >> a.unit_shift, r0 = (u & ((1u << a.unit_shift) - 1u)) * rows;
       uint32_t acc[W];
       run_program<LOG2W, (VAR & 1) != 0>(a.code, a.nins, U0, lane, acc, st, regs, a.nregs * (W * 256u), nullptr,
                                          a.j16_any);
       mask_tail<LOG2W>(acc, U0, lane, a.nslices, a.n);
-      tile_compact<LOG2W>(acc, U0, lane, base, a.out_idx, a.capacity, (uint16_t *)regs);
+      tile_compact<LOG2W>(acc, r0, rows, U0, lane, at, a.out_idx, a.capacity, (uint16_t *)regs);
     });
     return;
   }
@@ -817,7 +835,7 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_eval(EvalArgs a)
     } else if (MODE == MODE_DNF) {
       store_tile<LOG2W>(acc, U0, lane, a.out32, a.out_slices);
     } else {
-      tile_count_out<LOG2W>(acc, lane, a.tile_counts + t);
+      tile_count_out<LOG2W>(acc, lane, a.unit_shift, a.tile_counts + (t << a.unit_shift));
     }
   });
   if (MODE == MODE_COUNT) {
@@ -826,15 +844,20 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_eval(EvalArgs a)
   }
 }
 
-// Enumeration over a stored DNF vector: chunks of 64 x 32 words laid out as
-// the evaluator's tiles with W = 32; a.out32 is the DNF (read only here).
-template <int MODE>
+// Enumeration over a stored DNF vector: tiles of 64 W words laid out as the
+// evaluator's (a unit is a tile here); a.out32 is the DNF (read only here).
+// The counting pass runs at the rate of HBM (2^30 bits: 20 us, 6.7 TB/s).  With
+// a.block_sums its blocks take a tile per wave and leave their sums as well, so
+// that a block of the compaction pass adds up a quarter as many numbers (16384
+// tiles: 9 us of a pass of 25 us went there).
+template <int LOG2W, int MODE>
 __global__ __launch_bounds__(256) void k_dnf_scan(EvalArgs a) {
-  constexpr int LOG2W = 5, W = 32;
+  constexpr int W = 1 << LOG2W;
+  __shared__ uint64_t part[4];
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wib = uni(threadIdx.x) >> 6;
   const uint32_t wpb = blockDim.x >> 6;
-  auto load = [&](uint64_t U0, uint32_t (&acc)[W]) {
+  auto load = [&](uint64_t U0, uint32_t (&acc)[W]) __attribute__((always_inline)) {
     const uint32_t *src = a.out32 + U0 * 64 + lane;
     if ((U0 + W) * 64 <= a.nslices) {  // wave-uniform: a whole tile, every load issued at once
 #pragma unroll
@@ -848,21 +871,35 @@ __global__ __launch_bounds__(256) void k_dnf_scan(EvalArgs a) {
     }
   };
   if (MODE == MODE_ENUM) {
-    __shared__ uint64_t part[4];
     __shared__ uint16_t stage[4][kStageModels];
-    for_model_tiles(a, lane, wib, wpb, part, [&](uint64_t t, uint64_t base) {
+    for_model_units(a, lane, wib, wpb, part, [&](uint32_t u, uint64_t at) __attribute__((always_inline)) {
       uint32_t acc[W];
-      load(t << LOG2W, acc);
-      tile_compact<LOG2W>(acc, t << LOG2W, lane, base, a.out_idx, a.capacity, stage[wib]);
+      const uint64_t U0 = (uint64_t)u << LOG2W;
+      load(U0, acc);
+      tile_compact<LOG2W>(acc, 0u, W, U0, lane, at, a.out_idx, a.capacity, stage[wib]);
     });
     return;
   }
   const uint64_t wave = (uint64_t)blockIdx.x * wpb + wib;
   const uint64_t nwaves = (uint64_t)gridDim.x * wpb;
+  uint32_t c = 0;
   for (uint64_t t = wave; t < a.ntiles; t += nwaves) {
     uint32_t acc[W];
     load(t << LOG2W, acc);
-    tile_count_out<LOG2W>(acc, lane, a.tile_counts + t);
+    c = 0;
+#pragma unroll
+    for (int i = 0; i < W; i++) c += __popc(acc[i]);
+    c = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(c), 63);
+    if (lane == 0) a.tile_counts[t] = c;
+  }
+  if (a.block_sums) {  // one tile per wave
+    if (lane == 0) part[wib] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      uint32_t sum = 0;
+      for (uint32_t w = 0; w < wpb; w++) sum += (uint32_t)part[w];
+      a.block_sums[blockIdx.x] = sum;
+    }
   }
 }
 
@@ -1090,7 +1127,7 @@ __global__ __launch_bounds__(256) void k_batch_compact(BatchEnumArgs a) {
       acc[i] = sidx < p->nslices ? src[i * 64] : 0u;
     }
     const uint64_t first = a.list_base[g / kListBlock] + (e >> 32) - a.prog_base[lo];
-    tile_compact<LOG2W>(acc, U0, lane, first, p->out, p->capacity, stage[wib]);
+    tile_compact<LOG2W>(acc, 0u, W, U0, lane, first, p->out, p->capacity, stage[wib]);
   }
 }
 

@@ -17,10 +17,9 @@ constexpr uint32_t kVgprRegs = 4;
 constexpr uint32_t kJ16VgprRegs = FBG_J16_VGPR_REGS;
 inline uint32_t vgpr_regs_of(int log2w) { return log2w == FBG_J16_LOG2W ? kJ16VgprRegs : kVgprRegs; }
 
-// Models a wave of an enumeration pass gathers in LDS before they leave: a
-// row of 64 words holds at most this many.
+// Models a wave of a compaction pass gathers in LDS before they leave (at
+// least the 2048 of a row of 64 words).
 constexpr uint32_t kStageModels = 2048;
-constexpr uint32_t kStageWords = kStageModels / 2;  // as 32-bit words: 4 KiB a wave
 
 struct EvalArgs {
   const uint32_t *code;   // encoded program: clause block, instructions, pattern table
@@ -33,13 +32,17 @@ struct EvalArgs {
   uint32_t *out32;        // MODE_DNF (written); stored-DNF scans (read)
   uint64_t out_slices;    // MODE_DNF: words written (>= nslices, >= 2)
   const uint32_t *xcd_code;  // MODE_DNF at 32 words per lane: the XCD-local encoding, or null
-  uint32_t *tile_counts;  // MODE_TILECNT (out), MODE_ENUM (in)
-  // MODE_ENUM: with tiles_per_block > 0 (a multiple of 4, at most 64) the blocks
-  // take that many tiles each and find their positions from tile_counts, the
-  // last one writing the total to out_count; else the list of the tiles that
-  // hold models (TileListArgs)
-  uint32_t tiles_per_block;
-  uint32_t lds_stride;    // words of LDS per wave: its registers, at least kStageWords
+  uint32_t *tile_counts;  // per unit: MODE_TILECNT (out), MODE_ENUM (in)
+  // Units of the enumeration passes: 2^unit_shift to a tile (fbg_device.h).
+  // MODE_ENUM: with `direct` a wave takes one unit, its block finding their
+  // positions from tile_counts (or block_sums) and the last block writing the
+  // total to out_count; else the list of the units that hold models
+  // (TileListArgs)
+  uint32_t unit_shift;
+  uint32_t direct;
+  uint64_t nunits;
+  uint32_t *block_sums;   // stored-DNF scans: sums of the counts of a block's units, or null
+  uint32_t lds_stride;    // words of LDS per wave: its registers, at least kStageModels / 2
   const uint64_t *list;
   const uint64_t *list_base;
   const uint64_t *nlist;
@@ -158,7 +161,7 @@ enum { EVAL_COUNT = 0, EVAL_DNF = 1, EVAL_TILECNT = 2, EVAL_ENUM = 3 };
 
 hipError_t launch_eval(int mode, int log2w, int var, const EvalArgs &a, int grid, int block, size_t lds,
                        hipStream_t s);
-hipError_t launch_dnf_scan(int mode, const EvalArgs &a, int grid, int block, hipStream_t s);
+hipError_t launch_dnf_scan(int mode, int log2w, const EvalArgs &a, int grid, int block, hipStream_t s);
 hipError_t launch_batch(int mode, int log2w, int var, const BatchArgs &a, int grid, int block, size_t lds,
                         hipStream_t s);
 // The DNF write-out of a plan of clause-only programs without the cofactor,

@@ -33,11 +33,15 @@ int eval_blocks_per_cu(int mode, int log2w, int var, int block, size_t lds) {
   }
 }
 
-hipError_t launch_dnf_scan(int mode, const EvalArgs &a, int grid, int block, hipStream_t s) {
-  if (mode == dev::MODE_TILECNT)
-    hipLaunchKernelGGL((dev::k_dnf_scan<dev::MODE_TILECNT>), dim3(grid), dim3(block), 0, s, a);
-  else if (mode == dev::MODE_ENUM)
-    hipLaunchKernelGGL((dev::k_dnf_scan<dev::MODE_ENUM>), dim3(grid), dim3(block), 0, s, a);
+hipError_t launch_dnf_scan(int mode, int log2w, const EvalArgs &a, int grid, int block, hipStream_t s) {
+  if (mode == dev::MODE_TILECNT && log2w == 2)
+    hipLaunchKernelGGL((dev::k_dnf_scan<2, dev::MODE_TILECNT>), dim3(grid), dim3(block), 0, s, a);
+  else if (mode == dev::MODE_TILECNT && log2w == 5)
+    hipLaunchKernelGGL((dev::k_dnf_scan<5, dev::MODE_TILECNT>), dim3(grid), dim3(block), 0, s, a);
+  else if (mode == dev::MODE_ENUM && log2w == 2)
+    hipLaunchKernelGGL((dev::k_dnf_scan<2, dev::MODE_ENUM>), dim3(grid), dim3(block), 0, s, a);
+  else if (mode == dev::MODE_ENUM && log2w == 5)
+    hipLaunchKernelGGL((dev::k_dnf_scan<5, dev::MODE_ENUM>), dim3(grid), dim3(block), 0, s, a);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

@@ -1,7 +1,8 @@
 """Enumeration at the edges of its paths: lists staged through LDS in one and
-in many flushes, blocks that find their own positions up to 16384 tiles and
-the list of the tiles with models beyond, programs of a batch that start
-inside a block of that list, truncated lists.  Against the oracle."""
+in many flushes, tiles cut into units, blocks that find their own positions
+up to 4096 units (16384 tiles of a stored vector) and the list of the units
+with models beyond, programs of a batch that start inside a block of that
+list, truncated lists.  Against the oracle."""
 
 import random
 
@@ -67,10 +68,11 @@ def test_lists(F, kind, wpl, n):
     lists(lambda cap, out, tot: F.enumerate_dnf(dnf, n, cap, out=out, total=tot), want, caps)
 
 
-@pytest.mark.parametrize("n,wpl", [(24, 1), (25, 1), (26, 1), (27, 2)])
+@pytest.mark.parametrize("n,wpl", [(22, 1), (23, 1), (24, 1), (23, 8), (25, 16), (28, 32)])
 @pytest.mark.parametrize("cofactor", [False, True])
 def test_tile_thresholds(F, n, wpl, cofactor):
-    """16384 tiles (n = 25 at one word per lane) are the last without a list."""
+    """4096 units (n = 23 at one word per lane) are the last without a list;
+    tiles are cut into units of four rows and more below 32768 units."""
     text = workloads.random_3cnf(n, 3 * n, n)[0]
     p = F.Program(text, n)
     p.set_tuning(wpl, cofactor=cofactor)
@@ -80,6 +82,20 @@ def test_tile_thresholds(F, n, wpl, cofactor):
     assert len(want) == oracle.count(text, n)
     print("thresholds", n, wpl, cofactor, len(want), flush=True)
     lists(lambda cap, out, tot: F.enumerate_models(p, cap, out=out, total=tot), want, [len(want) + 1, 100])
+
+
+@pytest.mark.parametrize("n", [27, 28, 30, 31])
+def test_stored_vector_thresholds(F, n):
+    """16384 tiles (n = 27 at 1 KiB, n = 30 at 8 KiB) are the last without a
+    list.  Models spread out, and crowded into the last tiles."""
+    for text in (workloads.random_3cnf(n, 3 * n, n)[0], "\n".join("x%d" % k for k in range(17, n)) + "\nx0 ^ x5\n"):
+        p = F.Program(text, n)
+        dnf = F.eval_dnf(p)
+        total = int(F.count(p).item())
+        want = F.enumerate_models(p, total + 1)[0].cpu().numpy()[:total].view(np.uint64)
+        assert total > 0 and (np.diff(want.astype(np.int64)) > 0).all()
+        print("stored", n, total, flush=True)
+        lists(lambda cap, out, tot: F.enumerate_dnf(dnf, n, cap, out=out, total=tot), want, [total + 1, 10])
 
 
 def test_more_blocks_than_are_summed(F):
