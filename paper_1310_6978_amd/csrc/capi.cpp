@@ -159,6 +159,7 @@ struct fbg_program {
   std::vector<uint32_t> words_xcd;
   uint64_t dev_off_xcd = 0;
   bool has_xcd = false;
+  double live[kMaxLog2W + 1] = {1, 1, 1, 1, 1, 1};  // share of tiles expected to pass the uniform-cofactor test
   double j16_cost = 0;  // per tile at 16 words per lane, from the jump-table form (0: none)
   uint32_t ncl = 0;  // leading clause instructions
   int auto_log2w = 0;
@@ -354,6 +355,31 @@ fbg::EvalArgs base_args(const fbg_program *p, int log2w) {
   return a;
 }
 
+// log2 of the waves that share a group of 64 tiles in a uniform-cofactor
+// launch: about eight (group, part) pairs for every wave, so that the live tiles
+// of a group (up to 12 of the 64 for equivalence relations on 9 elements, 56 for
+// triangle-free graphs on 8 vertices) are not one wave's chain; every part
+// repeats the test, which costs a few clauses.
+uint32_t cofactor_parts(uint64_t ntiles, const Geometry &g) {
+  const uint64_t groups = (ntiles + 63) / 64, want = 8 * (uint64_t)g.grid * (uint64_t)(g.block / 64);
+  uint32_t s = 0;
+  while (s < 6 && (groups << (s + 1)) <= want) s++;
+  return s;
+}
+
+// Share of a program's tiles expected to pass the uniform-cofactor test at
+// 2^l words per lane, its tile-only clauses taken as independent.
+double expected_live(const fbg_program *p, int l) {
+  double live = 1.0;
+  for (uint32_t k = 0; k < p->ncl; k++) {
+    const auto &lits = p->c.code[k].ls.lits;
+    bool tile_only = true;
+    for (const fbg::Lit &x : lits) tile_only = tile_only && x.k >= FBG_TILE_BASE_BIT + l;
+    if (tile_only) live *= 1.0 - std::ldexp(1.0, -(int)std::min<size_t>(lits.size(), 60));
+  }
+  return live;
+}
+
 // Estimated cost of one tile of a program in a batch or a server slice at 2^l
 // words per lane, in steps of the interpreter: at 16 words per lane the
 // general part's VALU instructions per word and half a step per dispatch of
@@ -364,6 +390,62 @@ fbg::EvalArgs base_args(const fbg_program *p, int log2w) {
 double tile_cost(const fbg_program *p, int l) {
   const double general = l == FBG_J16_LOG2W && p->j16_cost > 0 ? p->j16_cost : (double)(p->c.code.size() - p->ncl);
   return general + 4.0 + (p->ncl ? 8.0 + (double)p->ncl : 0.0);
+}
+
+// The same with the uniform cofactor: the test, and the tiles expected to pass
+// it (at 16 words per lane 0.6 % of the tiles of a 3-CNF system over 36 letters,
+// 40 % over 26, so pieces of equal tile counts would cost up to 30 times one
+// another).
+double cofactor_tile_cost(const fbg_program *p, int l) { return 0.5 + p->live[l] * tile_cost(p, l); }
+
+// Cut the tiles [b, e) of a program into about K work items (at most K, with
+// the cofactor 2 K), appended by add(item, tiles): interleaved runs of tiles, or with the uniform
+// cofactor of groups of 64 tiles, where the stride K is odd (live groups share
+// their low index bits, and an even K would give them to a few items); a range
+// of fewer groups than K has the live tiles of each group dealt over several
+// items.
+template <typename Add>
+void cut_tiles(uint32_t prog, uint32_t slot, uint64_t b, uint64_t e, uint64_t K, bool cofactor, double live,
+               Add &&add) {
+  fbg::BatchItem it;
+  it.prog = prog;
+  it.slot = slot;
+  it.t1 = e;
+  it.part = 0;
+  K = std::max<uint64_t>(1, std::min(K, e - b));
+  if (!cofactor) {
+    it.step = (uint32_t)K;
+    for (uint64_t k = 0; k < K; k++) {
+      it.t0 = b + k;
+      add(it, (double)((e - b - k + K - 1) / K));
+    }
+    return;
+  }
+  const uint64_t g0 = b / 64, groups = (e - 1) / 64 - g0 + 1;
+  if (K < groups) {
+    if (!(K & 1)) K++;
+    it.step = (uint32_t)K;
+    for (uint64_t k = 0; k < K; k++) {
+      it.t0 = k == 0 ? b : (g0 + k) * 64;
+      add(it, (double)((groups - k + K - 1) / K) * 64.0);
+    }
+    return;
+  }
+  // as many shares as K asks for, and once more where the live tiles of a
+  // group, should they crowd four times as close as expected, would be more
+  // than eight evaluations for a wave of the block
+  uint32_t s = 0;
+  while (s < 6 && (groups << (s + 1)) <= K) s++;
+  const double crowd = 64.0 * std::min(1.0, 4.0 * live) / (double)(kWavesPerBlock << s);
+  if (crowd > 8.0 && s < 6) s++;
+  it.step = 1;
+  for (uint64_t g = 0; g < groups; g++)
+    for (uint32_t part = 0; part < (1u << s); part++) {
+      it.t0 = g == 0 ? b : (g0 + g) * 64;
+      it.t1 = std::min(e, (g0 + g + 1) * 64);
+      it.part = part << 8 | s;
+      add(it, (double)(it.t1 - it.t0) / (double)(1u << s));
+    }
 }
 
 fbg::BatchProg batch_prog(const fbg_program *p, int l) {
@@ -478,6 +560,7 @@ struct EvalPasses {
     fbg::EvalArgs a = base_args(p, g.log2w);
     while (g.log2w - (int)a.unit_shift > 2 && (a.ntiles << a.unit_shift) < 32768) a.unit_shift++;
     a.nunits = a.ntiles << a.unit_shift;
+    a.part_shift = cofactor_parts(a.ntiles, g);
     if (a.nunits <= kDirectUnits) a.direct = 1;
     return a;
   }
@@ -554,6 +637,7 @@ fbg_status compile_common(const char *src, int32_t n_vars, const int32_t *subst,
   }
   p->nslices = slices_of(p->c.n);
   p->ncl = fbg::leading_clauses(p->c);
+  for (int l = 0; l <= kMaxLog2W; l++) p->live[l] = expected_live(p, l);
   size_t total = 0;
   std::string enc_err;
   for (int l = 0; l <= kMaxLog2W; l++) {
@@ -726,6 +810,7 @@ fbg_status fbg_count_tuned(const fbg_program *p, uint64_t *d_count, const fbg_tu
   if ((st = geometry(p, tune, fbg::EVAL_COUNT, g))) return st;
   fbg::EvalArgs a = base_args(p, g.log2w);
   a.out_count = d_count;
+  a.part_shift = cofactor_parts(a.ntiles, g);
   e = fbg::launch_set_u64(d_count, 0, s);
   if (e != hipSuccess) return hip_fail(e, "launch");
   e = fbg::launch_eval(fbg::EVAL_COUNT, g.log2w, p->variant(tune), a, g.grid, g.block, g.lds, s);
@@ -750,6 +835,7 @@ fbg_status fbg_eval_dnf_tuned(const fbg_program *p, uint64_t *d_out, uint64_t ou
   fbg::EvalArgs a = base_args(p, g.log2w);
   a.out32 = (uint32_t *)d_out;
   a.out_slices = 2 * need;
+  a.part_shift = cofactor_parts(a.ntiles, g);
   // the XCD-local layout (fbg_kernels.h) on the grid of one tile per wave
   if (g.log2w == 5 && p->has_xcd && p->variant(tune) == 0 && ((uintptr_t)d_out & 15) == 0)
     a.xcd_code = p->d_code + p->dev_off_xcd;
@@ -919,41 +1005,34 @@ fbg_status fbg_batch_create(const fbg_program *const *ps, int32_t np, const fbg_
       fbg_batch_free(b);
       return st;
     }
+    const bool cofactor = (var & 2) != 0;
+    auto per_tile = [&](int32_t i) { return cofactor ? cofactor_tile_cost(ps[i], l) : tile_cost(ps[i], l); };
     double total_cost = 0;
     for (int32_t i : members) {
       fbg::BatchProg &q = b->host_progs[(size_t)i];
       q = batch_prog(ps[i], l);
-      total_cost += (double)q.ntiles * tile_cost(ps[i], l);
+      total_cost += (double)q.ntiles * per_tile(i);
       b->plan_of[(size_t)i] = (int)b->plans.size();
     }
     // about eight items per wave (on C3, 2.1 % faster than four and 0.9 %
     // than sixteen: finer items even out the end of the queues, more of them
     // cost pops); never split below one tile.  A program's K items
-    // interleave: item k takes tiles k, k + K, k + 2K, ..., so the waves
-    // working on neighbouring items at the same time write neighbouring tiles
-    // (DNF vectors), which keeps the HBM writes close together.
-    const double target = std::max(1.0, total_cost / (double)(waves * 8));
+    // interleave, so the waves working on neighbouring items at the same time
+    // write neighbouring tiles (DNF vectors), which keeps the HBM writes close
+    // together.
+    // With the cofactor an item is a block's: about eight per block.
+    const double target = std::max(1.0, total_cost / (double)(waves * (cofactor ? 2 : 8)));
     std::vector<fbg::BatchItem> items;
     std::vector<double> cost;
     for (int32_t i : members) {
       const fbg::BatchProg &q = b->host_progs[(size_t)i];
-      const double per_tile = tile_cost(ps[i], l);
-      const uint64_t chunk = (uint64_t)std::max(1.0, target / per_tile);
-      uint64_t K = (q.ntiles + chunk - 1) / chunk;
-      // with the uniform cofactor an odd K: the tiles that survive its test
-      // often share their low index bits, and an even (above all a
-      // power-of-two) K would give them to a few items
-      if ((var & 2) && K > 1 && K < q.ntiles && !(K & 1)) K++;
-      for (uint64_t k = 0; k < K; k++) {
-        fbg::BatchItem it;
-        it.prog = (uint32_t)i;
-        it.slot = (uint32_t)i;
-        it.t0 = k;
-        it.t1 = q.ntiles;
-        it.step = K;
-        items.push_back(it);
-        cost.push_back((double)((q.ntiles - k + K - 1) / K) * per_tile);
-      }
+      const double w = per_tile(i);
+      const uint64_t chunk = (uint64_t)std::max(1.0, target / w);
+      cut_tiles((uint32_t)i, (uint32_t)i, 0, q.ntiles, (q.ntiles + chunk - 1) / chunk, cofactor,
+                ps[i]->live[l], [&](const fbg::BatchItem &it, double tiles) {
+                  items.push_back(it);
+                  cost.push_back(tiles * w);
+                });
     }
     if (items.size() > 0xFFFFFFF0ull) {
       fbg_batch_free(b);
@@ -976,7 +1055,7 @@ fbg_status fbg_batch_create(const fbg_program *const *ps, int32_t np, const fbg_
     if (tune && tune->direct_run > 0) pl.direct_run = (uint32_t)tune->direct_run;
     pl.max_regs = lds_keep;
     pl.gstride = gstride;
-    const uint64_t want = (pl.nitems + wpb - 1) / wpb;
+    const uint64_t want = cofactor ? pl.nitems : (pl.nitems + wpb - 1) / wpb;
     for (int mode : {fbg::EVAL_COUNT, fbg::EVAL_DNF}) {
       uint64_t maxb = (uint64_t)cus * (uint64_t)fbg::batch_blocks_per_cu(mode, l, var, pl.block, lds);
       if (tune && tune->grid_blocks > 0) maxb = (uint64_t)tune->grid_blocks;
@@ -1000,6 +1079,7 @@ fbg_status fbg_batch_create(const fbg_program *const *ps, int32_t np, const fbg_
         it.t0 = pl.ntiles;
         it.t1 = pl.ntiles + q.ntiles;
         it.step = 1;
+        it.part = 0;
         direct.push_back(it);
         pl.ntiles += q.ntiles;
         pl.max_prog_tiles = std::max<uint64_t>(pl.max_prog_tiles, q.ntiles);
@@ -1377,53 +1457,48 @@ fbg_status fbg_server_launch(fbg_server *sv, const fbg_program *const *ps, int32
   fbg::BatchProg *hp = (fbg::BatchProg *)(sl.h + kServerHeadBytes);
   fbg::BatchItem *hi = (fbg::BatchItem *)(sl.h + items_at);
   for (int32_t i = 0; i < np; i++) hp[i] = batch_prog(ps[i], l);  // tilings checked above
-  // Cut the items into pieces of about equal estimated cost (tile_cost per
-  // tile) so that every resident wave gets about four, within the staging
-  // capacity: an item of c tiles at cost w each gives ceil(c / ceil(T / w)) <=
-  // c w / T + 1 pieces for a target T (one more with the uniform cofactor,
-  // below), so want + 2 nitems <= max_items in all (checked below all the
-  // same).  (Sorting the pieces by cost as the batch plans do cost more host
-  // time per slice than it saved.)
+  // Cut the items into pieces of about equal estimated cost so that every
+  // resident wave (with the uniform cofactor every block) gets about four,
+  // within the staging capacity: an item of c tiles at cost w each gives
+  // ceil(c / ceil(T / w)) <= c w / T + 1 pieces for a target T (with the
+  // cofactor up to twice as many), so want + nitems, or twice that, is within
+  // max_items (checked below all the same).  (Sorting the pieces by cost as
+  // the batch plans do cost more host time per slice than it saved.)
+  auto per_tile = [&](int32_t i) {
+    const fbg_program *q = ps[i];
+    return sv->cofactor ? cofactor_tile_cost(q, l) : tile_cost(q, l);
+  };
   double total = 0;
   for (int32_t k = 0; k < nitems; k++)
-    total += (double)(items[k].tile_end - items[k].tile_begin) * tile_cost(ps[items[k].prog], l);
-  const int64_t spare = (int64_t)sv->max_items - (sv->cofactor ? 2 : 1) * (int64_t)nitems;
+    total += (double)(items[k].tile_end - items[k].tile_begin) * per_tile(items[k].prog);
+  const int64_t spare = (sv->cofactor ? sv->max_items / 2 : sv->max_items) - (int64_t)nitems;
   const uint64_t room = (uint64_t)std::max<int64_t>(0, spare);
-  const uint64_t want = std::min<uint64_t>(room, (uint64_t)cus * occ * wpb * 4);
+  const uint64_t want = std::min<uint64_t>(room, (uint64_t)cus * occ * (sv->cofactor ? 1 : wpb) * 4);
   const double target = want > 0 ? total / (double)want * (1.0 + 1e-9) : 0.0;
-  // With the uniform cofactor an item's P pieces interleave (piece j takes
-  // tiles j, j + P, ... of it) with P odd: the tiles that survive the test
-  // often share index bits, and contiguous pieces, or an even stride, would
-  // give them to a few pieces.
   int32_t npieces = 0;
+  bool full = false;
   for (int32_t k = 0; k < nitems; k++) {
-    const double w = tile_cost(ps[items[k].prog], l);
-    const uint64_t chunk = want > 0 ? std::max<uint64_t>(1, (uint64_t)std::ceil(target / w)) : ~0ull;
     const uint64_t b = items[k].tile_begin, e = items[k].tile_end;
-    if (sv->cofactor && e - b > chunk) {
-      uint64_t P = (e - b + chunk - 1) / chunk;
-      if (!(P & 1) && P < e - b) P++;
-      for (uint64_t j = 0; j < P; j++) {
+    if (b == e) continue;
+    const uint64_t chunk = want > 0 ? std::max<uint64_t>(1, (uint64_t)std::ceil(target / per_tile(items[k].prog))) : ~0ull;
+    if (!sv->cofactor) {
+      for (uint64_t t = b; t < e; t += std::min(chunk, e - t)) {
         if (npieces >= sv->max_items) return fail(FBG_E_INVAL, "internal: more pieces than staging room");
-        fbg::BatchItem &q = hi[npieces++];
-        q.prog = (uint32_t)items[k].prog;
-        q.slot = (uint32_t)items[k].slot;
-        q.t0 = b + j;
-        q.t1 = e;
-        q.step = P;
+        hi[npieces++] = {(uint32_t)items[k].prog, (uint32_t)items[k].slot, t, t + std::min(chunk, e - t), 1u, 0u};
       }
       continue;
     }
-    for (uint64_t t = b; t < e; t += std::min(chunk, e - t)) {
-      if (npieces >= sv->max_items) return fail(FBG_E_INVAL, "internal: more pieces than staging room");
-      fbg::BatchItem &q = hi[npieces++];
-      q.prog = (uint32_t)items[k].prog;
-      q.slot = (uint32_t)items[k].slot;
-      q.t0 = t;
-      q.t1 = t + std::min(chunk, e - t);
-      q.step = 1;
-    }
+    const uint64_t K = chunk == ~0ull ? 1 : (e - b + chunk - 1) / chunk;
+    cut_tiles((uint32_t)items[k].prog, (uint32_t)items[k].slot, b, e, K, true,
+              chunk == ~0ull ? 0.0 : ps[items[k].prog]->live[l], [&](const fbg::BatchItem &it, double) {
+                if (npieces < sv->max_items)
+                  hi[npieces++] = it;
+                else
+                  full = true;
+              });
   }
+  if (full) return fail(FBG_E_INVAL, "internal: more pieces than staging room");
+  if (npieces == 0) return FBG_OK;  // empty ranges only
   hipStream_t s = (hipStream_t)stream;
   e = hipMemcpyAsync(sl.d, sl.h, items_at + (size_t)npieces * sizeof(fbg::BatchItem), hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return hip_fail(e, "server upload");
@@ -1435,7 +1510,8 @@ fbg_status fbg_server_launch(fbg_server *sv, const fbg_program *const *ps, int32
   a.head = (uint32_t *)sl.d;
   a.counts = d_counts;
   a.j16_any = j16_any();
-  const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((npieces + wpb - 1) / wpb, (int64_t)cus * occ));
+  const int64_t blocks = (var & 2) ? npieces : (npieces + wpb - 1) / wpb;
+  const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(blocks, (int64_t)cus * occ));
   e = fbg::launch_batch(fbg::EVAL_COUNT, l, var, a, grid, 64 * wpb, lds, s);
   if (e == hipSuccess) e = hipEventRecord(sl.done, s);
   sl.used = true;

@@ -1399,18 +1399,27 @@ uint32_t encode_program(const Compiled &c, int log2w, std::vector<uint32_t> &wor
     emit_chunk(stat, lo, std::min(stat.size(), lo + FBG_CB_CHUNK), 0, log2w, pats, block);
   for (size_t lo = 0; lo < multi.size(); lo += FBG_CB_CHUNK, nmulti++)
     emit_chunk(multi, lo, std::min(multi.size(), lo + FBG_CB_CHUNK), lo == 0 ? 1 : 2, log2w, pats, block);
-  // the uniform-cofactor table: the tile selectors of every clause made only
-  // of tile literals, at the end of the block; its length in the first
-  // static chunk's h[4] (such clauses are static, so that chunk exists)
+  // the uniform-cofactor table (fbg_isa.h): every clause made only of tile
+  // literals, those without a literal on the low six tile bits first; its
+  // length in the first static chunk's h[4] (such clauses are static, so that
+  // chunk exists)
   uint32_t ncof = 0;
-  for (const BlockClause &b : stat) {
-    if (!b.tile_only) continue;
-    block.push_back((uint32_t)b.s.sel);
-    block.push_back((uint32_t)(b.s.sel >> 32));
-    block.push_back((uint32_t)b.s.neg);
-    block.push_back((uint32_t)(b.s.neg >> 32));
-    ncof++;
-  }
+  const uint64_t low = 63ull << log2w;  // the tile bits inside a group of 64
+  for (int within = 0; within < 2; within++)
+    for (const BlockClause &b : stat) {
+      if (!b.tile_only || (within != 0) != ((b.s.sel & low) != 0)) continue;
+      uint64_t tiles = 0;  // tiles of a group that satisfy it through their low bits
+      for (uint64_t t = 0; t < 64; t++)
+        if (((t << log2w) & b.s.sel) != (b.s.neg & low)) tiles |= 1ull << t;
+      for (const uint64_t v : {b.s.sel >> (log2w + 6), b.s.neg >> (log2w + 6), tiles, (uint64_t)0}) {
+        block.push_back((uint32_t)v);
+        block.push_back((uint32_t)(v >> 32));
+      }
+      ncof++;
+    }
+  // up to a multiple of four entries with clauses that hold everywhere
+  for (uint32_t k = ncof; k % 4; k++)
+    for (const uint32_t v : {0u, 0u, 0u, 0u, ~0u, ~0u, 0u, 0u}) block.push_back(v);
   if (nstat > 0) block[FBG_CB_HDR + 4] = ncof;
   block[0] = (uint32_t)block.size();
   block[1] = nstat;
@@ -1754,11 +1763,13 @@ uint32_t clause_block_value(const uint32_t *cb, const uint32_t *table, int log2w
   const uint32_t *ch = cb + FBG_CB_HDR;
   if (cof && cb[1] > 0) {  // the uniform-cofactor table at the end of the block
     const uint32_t ncof = ch[4];
-    const uint32_t *td = cb + cb[0] - 4 * ncof;
-    for (uint32_t c = 0; c < ncof; c++) {
-      const uint64_t sel = (uint64_t)td[4 * c] | ((uint64_t)td[4 * c + 1] << 32);
-      const uint64_t neg = (uint64_t)td[4 * c + 2] | ((uint64_t)td[4 * c + 3] << 32);
-      if ((U0 & sel) == neg) return 0u;
+    const uint32_t *td = cb + cb[0] - FBG_CB_COF_WORDS * ((ncof + 3) / 4 * 4);
+    const uint64_t t = U0 >> log2w;
+    for (uint32_t c = 0; c < ncof; c++, td += FBG_CB_COF_WORDS) {
+      const uint64_t sel = (uint64_t)td[0] | ((uint64_t)td[1] << 32);
+      const uint64_t neg = (uint64_t)td[2] | ((uint64_t)td[3] << 32);
+      const uint64_t tiles = (uint64_t)td[4] | ((uint64_t)td[5] << 32);
+      if (((t >> 6) & sel) == neg && !((tiles >> (t & 63)) & 1u)) return 0u;
     }
   }
   uint32_t extra = ~0u;  // the multi keys' factors of word i

@@ -375,29 +375,30 @@ __device__ __forceinline__ void run_clauses(const uint32_t *__restrict__ cb_g, c
   }
 }
 
-// The uniform-cofactor test of one tile (lane-parallel: each lane may ask
-// about another tile): 0 when a clause made only of tile literals is false on
-// the whole tile, which makes the program false there (acc only loses bits
-// after the clause block), else 1.  The encoder lists the tile selectors of
-// every such clause in a table at the end of the clause block, its length in
-// the first static chunk's h[4]; they are read as scalars.  Every lane runs
-// it (no divergent branch around it), and the result is a 0/1 word, not a
-// lane-mask boolean.
-template <int LOG2W>
-__device__ __forceinline__ uint32_t tile_alive(const uint32_t *__restrict__ cb_g, uint64_t t) {
+// The uniform-cofactor test of the tiles 64 g .. 64 g + 63: a bit per tile, clear
+// where a clause made only of tile literals is false, which makes the program
+// false on the whole tile (acc only loses bits after the clause block).  The
+// table at the end of the clause block (fbg_isa.h) is read as scalars and the
+// test runs on the scalar unit alone, four instructions per clause for 64
+// tiles; the clauses that do not depend on the tile within the group come first
+// and most groups end after a few of them (equivalence relations on 9 elements:
+// 9 of the 90 clauses on average).
+__device__ __forceinline__ uint64_t group_alive(const uint32_t *__restrict__ cb_g, uint64_t g) {
   const code_ptr cb = (code_ptr)cb_g;
-  if (cb[1] == 0) return 1u;
-  const uint32_t k = cb[FBG_CB_HDR + 4];
-  const code_ptr td = cb + cb[0] - 4 * k;
-  const uint64_t U0 = t << LOG2W;
-  uint32_t dead = 0u;
-  for (uint32_t c = 0; c < k; ++c) {
-    const u32x4 e = *(const __attribute__((address_space(4))) u32x4 *)(td + 4 * c);
-    const uint64_t sel = (uint64_t)e[0] | ((uint64_t)e[1] << 32);
-    const uint64_t neg = (uint64_t)e[2] | ((uint64_t)e[3] << 32);
-    dead |= (uint32_t)((U0 & sel) == neg);
+  uint64_t alive = ~0ull;
+  if (cb[1] == 0) return alive;
+  const uint32_t k = (cb[FBG_CB_HDR + 4] + 3) / 4 * 4;
+  const code_ptr td = cb + cb[0] - FBG_CB_COF_WORDS * k;
+  for (uint32_t c = 0; c < k && alive != 0ull; c += 4) {
+    const u32x16 e0 = *(const __attribute__((address_space(4))) u32x16 *)(td + FBG_CB_COF_WORDS * c);
+    const u32x16 e1 = *(const __attribute__((address_space(4))) u32x16 *)(td + FBG_CB_COF_WORDS * (c + 2));
+#define FBG_U64(v, i) ((uint64_t)v[i] | ((uint64_t)v[(i) + 1] << 32))
+#define FBG_TEST(v, i) alive &= (g & FBG_U64(v, i)) != FBG_U64(v, (i) + 2) ? ~0ull : FBG_U64(v, (i) + 4);
+    FBG_TEST(e0, 0) FBG_TEST(e0, 8) FBG_TEST(e1, 0) FBG_TEST(e1, 8)
+#undef FBG_TEST
+#undef FBG_U64
   }
-  return dead ^ 1u;
+  return alive;
 }
 
 // A bijection of [0, n): cycle-walking over a bijection of the bits-bit
@@ -415,43 +416,27 @@ __device__ __forceinline__ uint64_t tile_hash(uint64_t x, uint64_t n, uint32_t b
   return x;
 }
 
-// Visit the tiles first, first + stride, ... below end.  body(t, alive):
-// alive = false means the tile is known to be all zeros (uniform cofactor)
-// and need not be evaluated.  With COF the wave tests the next 64 tiles at
-// once, one per lane, and visits only the live ones, or (ALL) every tile,
-// the dead ones with alive = false.  Lanes past the end test some tile
-// beyond it; the valid mask removes them.  With HASH (COF only: a launch in
-// which wave w of nw visits w, w + nw, ... of the tiles [0, end)) the k-th
-// tile a wave visits is tile_hash of that index instead: the tiles that
-// survive the test often share their low index bits, and a power-of-two
-// stride would give them all to a few waves.
-template <int LOG2W, bool COF, bool ALL, bool HASH = false, typename Body>
-__device__ __forceinline__ void for_tiles(const uint32_t *__restrict__ code, uint64_t first, uint64_t stride,
-                                          uint64_t end, uint32_t lane, Body &&body) {
-  if (!COF) {
-    for (uint64_t t = first; t < end; t += stride) body(t, true);
-    return;
+// Visit the tiles of group g (64 g .. 64 g + 63) within [t0, t1) that this part
+// takes: of the tiles that pass the uniform-cofactor test, or (ALL) of all
+// tiles, the dead ones with alive = false (all zeros, not to be evaluated),
+// those whose running number r is `part` modulo mask + 1 (a power of two).
+// That many waves share the group: its surviving tiles often come many
+// together.  Returns the next running number.
+template <bool ALL, typename Body>
+__device__ __forceinline__ uint32_t visit_group(const uint32_t *__restrict__ code, uint64_t g, uint64_t t0,
+                                                uint64_t t1, uint32_t r, uint32_t part, uint32_t mask,
+                                                Body &&body) {
+  const uint64_t first = g * 64;
+  uint64_t valid = ~0ull;
+  if (first < t0) valid &= ~0ull << (t0 - first);            // t0 < first + 64
+  if (first + 64 > t1) valid &= ~0ull >> (first + 64 - t1);  // first < t1
+  const uint64_t alive = group_alive(code, g) & valid;
+  for (uint64_t todo = ALL ? valid : alive; todo; r++, todo &= todo - 1) {
+    if ((r & mask) != part) continue;
+    const uint32_t l = (uint32_t)__builtin_ctzll(todo);
+    body(first + l, ((alive >> l) & 1ull) != 0);
   }
-  uint32_t bits = 0;
-  if (HASH)
-    while ((1ull << bits) < end) bits++;
-  const uint64_t mask = bits >= 64 ? ~0ull : (1ull << bits) - 1;
-  for (uint64_t q0 = 0; first + q0 * stride < end; q0 += 64) {
-    const uint64_t il = first + (q0 + lane) * stride;
-    const uint64_t valid = __ballot(il < end);
-    const uint64_t tl = HASH && il < end ? tile_hash(il, end, bits, mask) : il;
-    const uint64_t alive = __ballot(tile_alive<LOG2W>(code, tl) != 0u) & valid;
-    uint64_t todo = ALL ? valid : alive;
-    while (todo) {
-      const uint32_t l = (uint32_t)__builtin_ctzll(todo);
-      todo &= todo - 1;
-      // lane l's tile, read as a scalar (l is wave-uniform)
-      const uint64_t t = HASH ? (uint64_t)__builtin_amdgcn_readlane((uint32_t)tl, l) |
-                                    (uint64_t)__builtin_amdgcn_readlane((uint32_t)(tl >> 32), l) << 32
-                              : first + (q0 + l) * stride;
-      body(t, ((alive >> l) & 1ull) != 0);
-    }
-  }
+  return r;
 }
 
 // Interpret one program over the W words of this lane in tile group U0: the
@@ -809,7 +794,7 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_eval(EvalArgs a)
   // counting skips them, and so does the tile-count pass, whose counts the
   // host clears beforehand
   constexpr bool ALL = MODE == MODE_DNF;
-  for_tiles<LOG2W, (VAR & 2) != 0, ALL, true>(a.code, wave, nwaves, a.ntiles, lane, [&](uint64_t t, bool alive) {
+  auto tile = [&](uint64_t t, bool alive) __attribute__((always_inline)) {
     const uint64_t U0 = t << LOG2W;
     uint32_t acc[W];
     if (LOG2W == 5 && VAR == 0 && MODE == MODE_DNF && a.xcd_code) {
@@ -837,7 +822,24 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_eval(EvalArgs a)
     } else {
       tile_count_out<LOG2W>(acc, lane, a.unit_shift, a.tile_counts + (t << a.unit_shift));
     }
-  });
+  };
+  if constexpr ((VAR & 2) != 0) {
+    // uniform cofactor: 2^part_shift waves to a group of 64 tiles.  The k-th
+    // (group, part) of the launch is taken at a hash of k: live groups share
+    // their low index bits, and a power-of-two stride would give them all to a
+    // few waves.
+    const uint64_t n = ((a.ntiles + 63) / 64) << a.part_shift;
+    uint32_t bits = 0;
+    while ((1ull << bits) < n) bits++;
+    const uint64_t hmask = (1ull << bits) - 1;
+    const uint32_t pmask = (1u << a.part_shift) - 1u;
+    for (uint64_t k = wave; k < n; k += nwaves) {
+      const uint64_t x = tile_hash(k, n, bits, hmask);
+      visit_group<ALL>(a.code, x >> a.part_shift, 0, a.ntiles, 0u, (uint32_t)x & pmask, pmask, tile);
+    }
+  } else {
+    for (uint64_t t = wave; t < a.ntiles; t += nwaves) tile(t, true);
+  }
   if (MODE == MODE_COUNT) {
     const uint64_t s = wave_sum_u64(total);
     if (lane == 0 && s) atomicAdd((unsigned long long *)a.out_count, (unsigned long long)s);
@@ -915,9 +917,10 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_batch(BatchArgs 
   extern __shared__ uint32_t lds[];
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wib = uni(threadIdx.x) >> 6;
+  const uint32_t wpb = blockDim.x >> 6;
   uint32_t *regs = lds + (size_t)wib * a.max_regs * (W * 64);
   // registers beyond the LDS block: this wave's block of global scratch
-  uint32_t *gregs = a.gscratch ? a.gscratch + ((size_t)blockIdx.x * (blockDim.x >> 6) + wib) * a.gstride : nullptr;
+  uint32_t *gregs = a.gscratch ? a.gscratch + ((size_t)blockIdx.x * wpb + wib) * a.gstride : nullptr;
   typedef const __attribute__((address_space(4))) BatchItem *item_ptr;
   typedef const __attribute__((address_space(4))) BatchProg *prog_ptr;
   // A wave adds its count to a program's slot once per run of items of
@@ -928,7 +931,8 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_batch(BatchArgs 
   if (VAR & 1) st.clear();
   auto process = [&](uint32_t item) {
     const item_ptr it = (item_ptr)a.items + item;
-    const uint64_t t0 = it->t0, t1 = it->t1, step = it->step;
+    const uint64_t t0 = it->t0, t1 = it->t1;
+    const uint32_t step = it->step, part = it->part;
     const uint32_t slot = it->slot;
     const prog_ptr p = (prog_ptr)a.progs + it->prog;
     if (slot != cur_slot) {  // wave-uniform
@@ -937,7 +941,7 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_batch(BatchArgs 
       total = 0;
       cur_slot = slot;
     }
-    for_tiles<LOG2W, (VAR & 2) != 0, MODE == MODE_DNF>(p->code, t0, step, t1, lane, [&](uint64_t t, bool alive) {
+    auto tile = [&](uint64_t t, bool alive) __attribute__((always_inline)) {
       const uint64_t U0 = t << LOG2W;
       uint32_t acc[W];
       if (alive) {
@@ -960,7 +964,16 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_batch(BatchArgs 
         const uint32_t tc = wave_sum_u32(c);
         if (lane == 0) p->tile_counts[t] = tc;
       }
-    });
+    };
+    if constexpr ((VAR & 2) != 0) {
+      // the waves of the block share the item
+      const uint32_t n = wpb << (part & 0xFFu), mine = (part >> 8) * wpb + wib;
+      uint32_t r = 0;
+      for (uint64_t g = t0 >> 6; g * 64 < t1; g += step)
+        r = visit_group<MODE == MODE_DNF>(p->code, g, t0, t1, r, mine, n - 1u, tile);
+    } else {
+      for (uint64_t t = t0; t < t1; t += step) tile(t, true);
+    }
   };
   // Items come sorted by cost, largest first, dealt over kQueues queues:
   // queue q holds items q, q + kQueues, ...  A wave pops from the queue of
@@ -968,16 +981,57 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_batch(BatchArgs 
   // until all are drained; a drained queue is seen by a plain read before
   // any atomic is spent on it.
   const uint32_t q0 = blockIdx.x % kQueues;
-  for (uint32_t k = 0; k < kQueues; ++k) {
-    const uint32_t q = (q0 + k) % kQueues;
-    uint32_t *head = a.head + q * kQueueStride;
-    if (k > 0 && q + kQueues * __builtin_amdgcn_readfirstlane(*(volatile uint32_t *)head) >= a.nitems) continue;
+  if constexpr ((VAR & 2) != 0) {
+    // Uniform cofactor: a block pops an item for all its waves, and the next
+    // one while it works on it.  The live tiles of an item come many together
+    // or not at all, and a wave alone took up to 44 evaluations one after the
+    // other (6 us each) where it expected five; four times as many pops, 13 ns
+    // each at one address, were a quarter of the launch.  A server slice of 48
+    // requests, 45,500 live tiles of 494,000: 119 us, with an item per wave 250 us.
+    __shared__ uint32_t popped;
+    uint32_t k = 0, q = q0;
+    bool first = true;
     for (;;) {
-      uint32_t r = 0;
-      if (lane == 0) r = atomicAdd(head, 1u);
-      const uint32_t item = q + kQueues * __builtin_amdgcn_readfirstlane(r);  // lane 0 took the item
-      if (item >= a.nitems) break;  // this queue is drained
+      // lane 0 of the block pops from queue q (~0: nothing left in any)
+      auto pop = [&]() __attribute__((always_inline)) { return q + kQueues * atomicAdd(a.head + q * kQueueStride, 1u); };
+      if (first) {
+        if (threadIdx.x == 0) popped = pop();
+        first = false;
+        __syncthreads();
+      }
+      uint32_t item = uni(popped);
+      __syncthreads();
+      if (item >= a.nitems) {  // the queue is drained: on to one that is not
+        if (threadIdx.x == 0) {
+          while (item >= a.nitems && ++k < kQueues) {
+            q = (q0 + k) % kQueues;
+            if (q + kQueues * *(volatile uint32_t *)(a.head + q * kQueueStride) < a.nitems) item = pop();
+          }
+          popped = item;
+        }
+        __syncthreads();
+        item = uni(popped);
+        __syncthreads();
+        if (item >= a.nitems) break;  // the same for the whole block
+      }
+      uint32_t next = 0;
+      if (threadIdx.x == 0) next = pop();
       process(item);
+      if (threadIdx.x == 0) popped = next;
+      __syncthreads();
+    }
+  } else {
+    for (uint32_t k = 0; k < kQueues; ++k) {
+      const uint32_t q = (q0 + k) % kQueues;
+      uint32_t *head = a.head + q * kQueueStride;
+      if (k > 0 && q + kQueues * __builtin_amdgcn_readfirstlane(*(volatile uint32_t *)head) >= a.nitems) continue;
+      for (;;) {
+        uint32_t r = 0;
+        if (lane == 0) r = atomicAdd(head, 1u);
+        const uint32_t item = q + kQueues * __builtin_amdgcn_readfirstlane(r);  // lane 0 took the item
+        if (item >= a.nitems) break;  // this queue is drained
+        process(item);
+      }
     }
   }
   const uint64_t s = wave_sum_u64(total);

@@ -33,6 +33,7 @@ struct EvalArgs {
   uint64_t out_slices;    // MODE_DNF: words written (>= nslices, >= 2)
   const uint32_t *xcd_code;  // MODE_DNF at 32 words per lane: the XCD-local encoding, or null
   uint32_t *tile_counts;  // per unit: MODE_TILECNT (out), MODE_ENUM (in)
+  uint32_t part_shift;    // uniform cofactor: 2^part_shift waves share a group of 64 tiles
   // Units of the enumeration passes: 2^unit_shift to a tile (fbg_device.h).
   // MODE_ENUM: with `direct` a wave takes one unit, its block finding their
   // positions from tile_counts (or block_sums) and the last block writing the
@@ -130,8 +131,13 @@ struct TileListArgs {
 struct BatchItem {
   uint32_t prog;    // index into the program table
   uint32_t slot;    // index into the counts array
-  uint64_t t0, t1;  // tiles t0, t0 + step, t0 + 2 step, ... below t1
-  uint64_t step;
+  // tiles t0, t0 + step, t0 + 2 step, ... below t1; with the uniform cofactor
+  // the tiles of [t0, t1) in the groups of 64 tiles t0 / 64, t0 / 64 + step, ...,
+  // share part >> 8 of 2^(part & 255) of the live ones (a block's item: its
+  // waves share it further)
+  uint64_t t0, t1;
+  uint32_t step;
+  uint32_t part;
 };
 
 // A plan's work items are split over kQueues queues (item i in queue
