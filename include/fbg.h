@@ -237,8 +237,10 @@ fbg_status fbg_count(const fbg_program *p, uint64_t *d_count, void *stream);
  *             when capacity is 0.
  *   d_total   device pointer to one uint64; receives the total number of
  *             models (also when it exceeds capacity).
- * Allocates temporary device memory on `stream` (stream-ordered) for the
- * per-tile counts and the list of the tiles that hold models.
+ * The per-tile counts and the list of the tiles that hold models take a block
+ * of the device's scratch pool (at most 8 blocks of 16 MiB, kept while the
+ * device has programs) if one is free and large enough, else temporary memory
+ * allocated on `stream` (stream-ordered; always so under stream capture).
  */
 fbg_status fbg_enumerate(const fbg_program *p, uint64_t *d_idx, uint64_t capacity, uint64_t *d_total,
                          void *stream);
@@ -346,7 +348,7 @@ fbg_status fbg_enumerate_noalloc(const fbg_program *p, uint64_t *d_idx, uint64_t
  * conventions as fbg_enumerate, for a vector d_dnf of max(1, 2^(n-6)) words
  * that a previous fbg_eval_dnf wrote (bits at or above 2^n must be zero).
  * Reads 2^n/8 bytes instead of evaluating the program again.  n <=
- * FBG_MAX_DNF_VARS.  Allocates temporary device memory on `stream`.
+ * FBG_MAX_DNF_VARS.  Temporary device memory as fbg_enumerate.
  */
 fbg_status fbg_enumerate_dnf(const uint64_t *d_dnf, int32_t n_vars, uint64_t *d_idx, uint64_t capacity,
                              uint64_t *d_total, void *stream);

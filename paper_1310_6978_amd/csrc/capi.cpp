@@ -134,6 +134,109 @@ class CodeArena {
   std::vector<void *> free_[64];
 };
 
+// Device scratch for the temporaries of an enumeration.  hipMallocAsync and
+// hipFreeAsync cost the host 11 us a call (whatever the pool's release
+// threshold); a block kept here costs an event record and a query.  A block is
+// handed out again only once the event recorded behind its last use has
+// completed, so calls on any streams and threads may overlap, each with its own
+// block; with every block in flight, under stream capture (a graph may replay
+// at any time) or beyond kBlock bytes the caller allocates on its stream as
+// before.  At most kBlocks blocks of a device, freed with its last program.
+class ScratchPool {
+ public:
+  static constexpr size_t kBlock = (size_t)16 << 20;
+  static constexpr int kBlocks = 8;
+
+  static ScratchPool &of(int dev) {
+    static std::mutex m;
+    static std::vector<ScratchPool *> pools;
+    std::lock_guard<std::mutex> g(m);
+    if ((size_t)dev >= pools.size()) pools.resize((size_t)dev + 1, nullptr);
+    if (!pools[(size_t)dev]) pools[(size_t)dev] = new ScratchPool();
+    return *pools[(size_t)dev];
+  }
+
+  // A block for `bytes` of work on s, or -1.
+  int acquire(size_t bytes, hipStream_t s, char **out) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (bytes > kBlock || hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return -1;
+    std::lock_guard<std::mutex> g(mu_);
+    const RelaxedCapture relaxed;
+    for (size_t i = 0; i < b_.size(); i++) {
+      const size_t k = (next_ + i) % b_.size();
+      if (b_[k].taken) continue;
+      if (b_[k].used) {
+        const hipError_t e = hipEventQuery(b_[k].done);
+        if (e == hipErrorNotReady) (void)hipGetLastError();  // not an error of the launches that follow
+        if (e != hipSuccess) continue;
+      }
+      return take(k, out);
+    }
+    if (b_.size() >= (size_t)kBlocks) return -1;
+    Block n;
+    if (hipMalloc((void **)&n.p, kBlock) != hipSuccess) return -1;
+    if (hipEventCreateWithFlags(&n.done, hipEventDisableTiming) != hipSuccess) {
+      (void)hipFree(n.p);
+      return -1;
+    }
+    b_.push_back(n);
+    return take(b_.size() - 1, out);
+  }
+
+  // The work using block k has been put on s.
+  hipError_t release(int k, hipStream_t s) {
+    std::lock_guard<std::mutex> g(mu_);
+    Block &b = b_[(size_t)k];
+    const hipError_t e = hipEventRecord(b.done, s);
+    b.used = true;
+    if (e == hipSuccess) b.taken = false;  // else it is never handed out again
+    return e;
+  }
+
+  void program_added() {
+    std::lock_guard<std::mutex> g(mu_);
+    programs_++;
+  }
+  void program_removed() {
+    std::lock_guard<std::mutex> g(mu_);
+    if (--programs_ > 0) return;
+    const RelaxedCapture relaxed;
+    for (size_t i = b_.size(); i-- > 0;) {
+      if (b_[i].taken) return;  // in use by another thread; later blocks keep their index
+      if (b_[i].used && hipEventQuery(b_[i].done) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+      }
+      (void)hipEventDestroy(b_[i].done);
+      (void)hipFree(b_[i].p);
+      b_.pop_back();
+    }
+  }
+
+ private:
+  // A query or an allocation does not disturb another stream's capture.
+  struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  };
+  struct Block {
+    char *p = nullptr;
+    hipEvent_t done = nullptr;
+    bool taken = false, used = false;
+  };
+  int take(size_t k, char **out) {
+    b_[k].taken = true;
+    next_ = k + 1;
+    *out = b_[k].p;
+    return (int)k;
+  }
+  std::mutex mu_;
+  std::vector<Block> b_;
+  size_t next_ = 0;
+  int64_t programs_ = 0;
+};
+
 fbg_status parse_wpl(int w, int &log2w) {
   if (w < 1 || w > FBG_MAX_WORDS_PER_LANE || (w & (w - 1)))
     return fail(FBG_E_INVAL, "words_per_lane must be 1, 2, 4, 8, 16 or 32 (got %d)", w);
@@ -528,18 +631,22 @@ hipError_t enumerate_passes(fbg::EvalArgs a, char *tmp, uint64_t *d_idx, uint64_
   return pass(fbg::EVAL_ENUM, a);
 }
 
-// The same with the temporaries allocated on the stream and freed after.
+// The same with a block of the device's scratch pool, or with the temporaries
+// allocated on the stream and freed after.
 template <typename Pass>
-fbg_status enumerate_with(const fbg::EvalArgs &a, uint64_t *d_idx, uint64_t capacity, uint64_t *d_total,
+fbg_status enumerate_with(int dev, const fbg::EvalArgs &a, uint64_t *d_idx, uint64_t capacity, uint64_t *d_total,
                           hipStream_t s, const Pass &pass) {
   const size_t bytes = enum_temp(a.nunits, a.direct).bytes;
   char *tmp = nullptr;
-  hipError_t e = hipMallocAsync((void **)&tmp, bytes, s);
+  ScratchPool &pool = ScratchPool::of(dev);
+  const int block = pool.acquire(bytes, s, &tmp);
+  hipError_t e = hipSuccess;
+  if (block < 0) e = hipMallocAsync((void **)&tmp, bytes, s);
   if (e != hipSuccess) return fail(FBG_E_NOMEM, "hipMallocAsync of %zu bytes: %s", bytes, hipGetErrorString(e));
   e = enumerate_passes(a, tmp, d_idx, capacity, d_total, s, pass);
-  hipError_t e2 = hipFreeAsync(tmp, s);
+  const hipError_t e2 = block < 0 ? hipFreeAsync(tmp, s) : pool.release(block, s);
   if (e != hipSuccess) return hip_fail(e, "launch of an enumeration kernel");
-  if (e2 != hipSuccess) return hip_fail(e2, "hipFreeAsync");
+  if (e2 != hipSuccess) return hip_fail(e2, "release of the temporaries");
   return FBG_OK;
 }
 
@@ -689,6 +796,7 @@ fbg_status compile_common(const char *src, int32_t n_vars, const int32_t *subst,
     p->auto_log2w = pick_log2w(p->nslices, (uint32_t)p->c.nregs, p->general(), -1);
   }
   p->auto_log2w = nearest_tiling(p->tilings, p->auto_log2w);
+  if (p->d_code) ScratchPool::of(p->device).program_added();
   if (p->general() && p->has_tiling(FBG_J16_LOG2W))
     p->j16_cost = fbg::j16_general_cost(p->words[FBG_J16_LOG2W], p->nins[FBG_J16_LOG2W]);
   *out = p;
@@ -750,7 +858,10 @@ fbg_status fbg_compile_subst(const char *src, int32_t n_vars, const int32_t *sub
 
 void fbg_program_free(fbg_program *p) {
   if (!p) return;
-  if (p->d_code) CodeArena::of(p->device).release(p->d_code, p->code_class);
+  if (p->d_code) {
+    CodeArena::of(p->device).release(p->d_code, p->code_class);
+    ScratchPool::of(p->device).program_removed();
+  }
   delete p;
 }
 
@@ -858,7 +969,7 @@ fbg_status fbg_enumerate(const fbg_program *p, uint64_t *d_idx, uint64_t capacit
   Geometry g;
   if ((st = geometry(p, nullptr, fbg::EVAL_TILECNT, g))) return st;
   const EvalPasses pass{p, g, p->variant(nullptr), (hipStream_t)stream};
-  return enumerate_with(pass.args(), d_idx, capacity, d_total, pass.s, pass);
+  return enumerate_with(p->device, pass.args(), d_idx, capacity, d_total, pass.s, pass);
 }
 
 fbg_status fbg_enumerate_noalloc(const fbg_program *p, uint64_t *d_idx, uint64_t capacity, uint64_t *d_total,
@@ -903,7 +1014,7 @@ fbg_status fbg_enumerate_dnf(const uint64_t *d_dnf, int32_t n_vars, uint64_t *d_
   a.nunits = a.ntiles = tiles_of(a.nslices, pass.log2w);
   a.direct = a.nunits <= kDirectScanTiles;
   a.out32 = (uint32_t *)d_dnf;
-  return enumerate_with(a, d_idx, capacity, d_total, pass.s, pass);
+  return enumerate_with(dev, a, d_idx, capacity, d_total, pass.s, pass);
 }
 
 // ------------------------------------------------------------------ batches

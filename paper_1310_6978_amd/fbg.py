@@ -155,19 +155,18 @@ def _tune(words_per_lane=0, grid_blocks=0, cofactor=False, direct_run=0):
                              int(direct_run)))
 
 
-def _torch_stream(stream):
-    """The torch stream object of `stream` (None: the current stream; an
-    integer: a caller-owned hipStream_t)."""
-    import torch
-    if stream is None:
-        return torch.cuda.current_stream()
-    if hasattr(stream, "cuda_stream"):
-        return stream
-    return torch.cuda.ExternalStream(int(stream))
-
-
 def _stream(stream):
-    return ctypes.c_void_p(_torch_stream(stream).cuda_stream)
+    """The hipStream_t of `stream` as an integer (None: the current stream of
+    the current device; a torch stream; an integer: a caller-owned
+    hipStream_t).  The raw handle of the current stream: building torch's
+    stream object costs 3 us, as much as a launch."""
+    if stream is None:
+        import torch
+        torch.cuda.init()
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if hasattr(stream, "cuda_stream"):
+        return stream.cuda_stream
+    return int(stream)
 
 
 # Deferred release.  A launch reads a program's code (and a batch its work
@@ -196,7 +195,8 @@ def _sweep():
 def _release_after(streams, release, keepalive=()):
     import torch
     events = []
-    for s in streams.values():
+    for handle, device in streams:
+        s = torch.cuda.ExternalStream(handle, device=device) if handle else torch.cuda.default_stream(device)
         e = torch.cuda.Event()
         e.record(s)
         events.append(e)
@@ -205,15 +205,17 @@ def _release_after(streams, release, keepalive=()):
     _sweep()
 
 
-def _used_on(objs, stream):
-    """Note that a launch on `stream` uses every object of `objs`."""
-    s = _torch_stream(stream)
+def _used_on(objs, handle):
+    """Note that a launch on the stream `handle` of the current device uses
+    every object of `objs`."""
+    import torch
+    key = (handle, torch._C._cuda_getDevice())
     for o in objs:
-        o._streams[s.cuda_stream] = s
+        o._streams.add(key)
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _device_u64(nelem, like=None):
@@ -252,7 +254,7 @@ class Program:
             _check(lib.fbg_compile_assume(src, int(n), a.ctypes.data_as(ctypes.POINTER(ctypes.c_int8)),
                                           int(flags), ctypes.byref(h)))
         self._h = h
-        self._streams = {}
+        self._streams = set()   # (stream handle, device) of the launches that use it
         self._batches = weakref.WeakSet()   # batches holding this program (their launches read it too)
         _sweep()
         info = ProgramInfo()
@@ -273,7 +275,7 @@ class Program:
         if h is None:
             return
         self._h = None
-        streams, self._streams = self._streams, {}
+        streams, self._streams = self._streams, set()
         for b in list(self._batches):
             streams.update(b._streams)
         if streams:
@@ -335,12 +337,13 @@ def eval_dnf(prog, out=None, stream=None, words_per_lane=0, grid_blocks=0, cofac
     words = dnf_words(prog.n)
     if out is None:
         out = _device_u64(words)
+    st = _stream(stream)
     tune = _tune(words_per_lane, grid_blocks, cofactor)
     if tune is None:
-        _check(lib.fbg_eval_dnf(prog.handle, _ptr(out), out.numel(), _stream(stream)))
+        _check(lib.fbg_eval_dnf(prog.handle, _ptr(out), out.numel(), st))
     else:
-        _check(lib.fbg_eval_dnf_tuned(prog.handle, _ptr(out), out.numel(), tune, _stream(stream)))
-    _used_on([prog], stream)
+        _check(lib.fbg_eval_dnf_tuned(prog.handle, _ptr(out), out.numel(), tune, st))
+    _used_on((prog,), st)
     return out
 
 
@@ -348,12 +351,13 @@ def count(prog, out=None, stream=None, words_per_lane=0, grid_blocks=0, cofactor
     """fbg_count: one-element int64 device tensor holding the model count."""
     if out is None:
         out = _device_u64(1)
+    st = _stream(stream)
     tune = _tune(words_per_lane, grid_blocks, cofactor)
     if tune is None:
-        _check(lib.fbg_count(prog.handle, _ptr(out), _stream(stream)))
+        _check(lib.fbg_count(prog.handle, _ptr(out), st))
     else:
-        _check(lib.fbg_count_tuned(prog.handle, _ptr(out), tune, _stream(stream)))
-    _used_on([prog], stream)
+        _check(lib.fbg_count_tuned(prog.handle, _ptr(out), tune, st))
+    _used_on((prog,), st)
     return out
 
 
@@ -364,9 +368,10 @@ def enumerate_models(prog, capacity, out=None, total=None, stream=None):
         out = _device_u64(capacity)
     if total is None:
         total = _device_u64(1)
-    ptr = _ptr(out) if capacity > 0 else ctypes.c_void_p(0)
-    _check(lib.fbg_enumerate(prog.handle, ptr, int(capacity), _ptr(total), _stream(stream)))
-    _used_on([prog], stream)
+    st = _stream(stream)
+    ptr = _ptr(out) if capacity > 0 else None
+    _check(lib.fbg_enumerate(prog.handle, ptr, int(capacity), _ptr(total), st))
+    _used_on((prog,), st)
     return out, total
 
 
@@ -374,9 +379,10 @@ def enumerate_models_noalloc(prog, out, total, stream=None):
     """fbg_enumerate_noalloc: as enumerate_models into caller-given device
     tensors (out: capacity int64 words, may be empty; total: one word), with
     the temporaries in the library's static device scratch."""
-    ptr = _ptr(out) if out.numel() > 0 else ctypes.c_void_p(0)
-    _check(lib.fbg_enumerate_noalloc(prog.handle, ptr, int(out.numel()), _ptr(total), _stream(stream)))
-    _used_on([prog], stream)
+    st = _stream(stream)
+    ptr = _ptr(out) if out.numel() > 0 else None
+    _check(lib.fbg_enumerate_noalloc(prog.handle, ptr, int(out.numel()), _ptr(total), st))
+    _used_on((prog,), st)
     return out, total
 
 
@@ -387,7 +393,7 @@ def enumerate_dnf(dnf, n, capacity, out=None, total=None, stream=None):
         out = _device_u64(capacity)
     if total is None:
         total = _device_u64(1)
-    ptr = _ptr(out) if capacity > 0 else ctypes.c_void_p(0)
+    ptr = _ptr(out) if capacity > 0 else None
     _check(lib.fbg_enumerate_dnf(_ptr(dnf), int(n), ptr, int(capacity), _ptr(total), _stream(stream)))
     return out, total
 
@@ -414,12 +420,13 @@ class Server:
         """progs: list of Program; items: (prog index, slot, tile_begin,
         tile_end) tuples, or a numpy array of ITEM_DTYPE; counts: int64 device
         tensor of slots (added to)."""
+        st = _stream(stream)
         arr = (ctypes.c_void_p * len(progs))(*[p.handle.value for p in progs])
         its = np.ascontiguousarray(np.asarray(items, dtype=ITEM_DTYPE) if not isinstance(items, np.ndarray)
                                    else items.astype(ITEM_DTYPE, copy=False))
         _check(lib.fbg_server_launch(self._h, arr, len(progs), its.ctypes.data_as(ctypes.POINTER(Item)), len(its),
-                                     _ptr(counts), counts.numel(), _stream(stream)))
-        _used_on(progs, stream)
+                                     _ptr(counts), counts.numel(), st))
+        _used_on(progs, st)
 
     def free(self):
         if getattr(self, "_h", None) is not None:
@@ -443,7 +450,7 @@ class Batch:
         _check(lib.fbg_batch_create(arr, len(self._progs),
                                     _tune(words_per_lane, grid_blocks, cofactor, direct_run), ctypes.byref(h)))
         self._h = h
-        self._streams = {}
+        self._streams = set()
         for p in self._progs:
             p._batches.add(self)
 
@@ -455,9 +462,10 @@ class Batch:
         (fbg_batch_count_graph)."""
         if out is None:
             out = _device_u64(len(self._progs))
+        st = _stream(stream)
         f = lib.fbg_batch_count_graph if graph else lib.fbg_batch_count
-        _check(f(self._h, _ptr(out), _stream(stream)))
-        _used_on([self], stream)
+        _check(f(self._h, _ptr(out), st))
+        _used_on((self,), st)
         return out
 
     def set_dnf_outputs(self, outs):
@@ -482,8 +490,9 @@ class Batch:
     def enumerate(self, stream=None):
         """Models of every program into its enumeration output, ascending
         (after eval_dnf on the same stream)."""
-        _check(lib.fbg_batch_enumerate(self._h, _stream(stream)))
-        _used_on([self], stream)
+        st = _stream(stream)
+        _check(lib.fbg_batch_enumerate(self._h, st))
+        _used_on((self,), st)
 
     def eval_dnf(self, counts=None, stream=None):
         """Every program's DNF vector into its output tensor and its count
@@ -492,8 +501,9 @@ class Batch:
         tiles per wave)."""
         if counts is None:
             counts = _device_u64(len(self._progs))
-        _check(lib.fbg_batch_eval_dnf(self._h, _ptr(counts), _stream(stream)))
-        _used_on([self], stream)
+        st = _stream(stream)
+        _check(lib.fbg_batch_eval_dnf(self._h, _ptr(counts), st))
+        _used_on((self,), st)
         return counts
 
     def free(self):
@@ -503,7 +513,7 @@ class Batch:
         if h is None:
             return
         self._h = None
-        streams = dict(self._streams)   # kept: the programs' own free() still waits for these launches
+        streams = set(self._streams)   # kept: the programs' own free() still waits for these launches
         if streams:
             _release_after(streams, lambda: lib.fbg_batch_free(h), keepalive=self._progs)
         else:
