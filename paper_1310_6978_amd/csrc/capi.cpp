@@ -266,6 +266,7 @@ struct fbg_program {
   double j16_cost = 0;  // per tile at 16 words per lane, from the jump-table form (0: none)
   uint32_t ncl = 0;  // leading clause instructions
   int auto_log2w = 0;
+  bool tuned = false;  // auto_log2w was set by fbg_program_set_tuning
   uint64_t nslices = 1;
   bool cofactor = false;  // default evaluation variant (fbg_program_set_tuning)
   bool general() const { return c.code.size() > ncl; }
@@ -287,6 +288,7 @@ struct fbg_batch {
     int block = 256;
     size_t lds = 0;
     uint32_t nitems = 0;
+    uint32_t pop_ahead = 0;  // short items
     uint32_t max_regs = 0;  // LDS registers per wave
     fbg::BatchItem *d_items = nullptr;
     // clause-only programs without the cofactor: the DNF write-out runs one
@@ -897,6 +899,7 @@ fbg_status fbg_program_set_tuning(fbg_program *p, const fbg_tune *tune) {
   size_t lds;
   if ((st = block_shape((uint32_t)p->c.nregs, l, wpb, lds))) return st;
   p->auto_log2w = l;
+  p->tuned = p->tuned || tune->words_per_lane != 0;
   p->cofactor = (tune->flags & FBG_TUNE_COFACTOR) != 0;
   return FBG_OK;
 }
@@ -1035,7 +1038,6 @@ fbg_status fbg_batch_create(const fbg_program *const *ps, int32_t np, const fbg_
   if (tune && (tune->direct_run < 0 || tune->direct_run > 64))
     return fail(FBG_E_INVAL, "direct_run must be 0..64 (got %d)", tune->direct_run);
   const int cus = cu_count(dev);
-  const uint64_t waves = (uint64_t)cus * 32;
 
   fbg_batch *b = new (std::nothrow) fbg_batch();
   if (!b) return fail(FBG_E_NOMEM, "out of host memory");
@@ -1071,17 +1073,32 @@ fbg_status fbg_batch_create(const fbg_program *const *ps, int32_t np, const fbg_
     for (int32_t i = 0; i < np; i++)
       if (group_of(ps[i]) == group) members.push_back(i);
     if (members.empty()) continue;
-    // words per lane: the tuning, else the choice for the largest program
+    // words per lane: the tuning, else the choice for the largest program,
+    // or more while the tiles of all programs together still give half the
+    // waves of a full device one each (a tile costs little more at twice the
+    // words: 16 systems of 2^24 valuations took 352 us to count at the one word
+    // per lane that suits one of them, 36 at 32 words)
     int l = fixed_l;
     if (l < 0) {
       uint64_t best = 0;
+      bool tuned = false;
       l = 0;
       for (int32_t i : members) {
         const uint64_t cost = ps[i]->nslices * (uint64_t)std::max<size_t>(1, ps[i]->c.code.size());
         if (cost >= best) {
           best = cost;
           l = ps[i]->auto_log2w;
+          tuned = ps[i]->tuned;
         }
+      }
+      for (int up = kMaxLog2W; up > l && !tuned; up--) {
+        uint64_t tiles = 0;
+        bool all = true;
+        for (int32_t i : members) {
+          tiles += tiles_of(ps[i]->nslices, up);
+          all = all && ps[i]->has_tiling(up);
+        }
+        if (all && tiles >= (uint64_t)cus * 16) l = up;
       }
     }
     uint32_t max_regs = 0;
@@ -1125,14 +1142,25 @@ fbg_status fbg_batch_create(const fbg_program *const *ps, int32_t np, const fbg_
       total_cost += (double)q.ntiles * per_tile(i);
       b->plan_of[(size_t)i] = (int)b->plans.size();
     }
-    // about eight items per wave (on C3, 2.1 % faster than four and 0.9 %
-    // than sixteen: finer items even out the end of the queues, more of them
-    // cost pops); never split below one tile.  A program's K items
-    // interleave, so the waves working on neighbouring items at the same time
-    // write neighbouring tiles (DNF vectors), which keeps the HBM writes close
-    // together.
-    // With the cofactor an item is a block's: about eight per block.
-    const double target = std::max(1.0, total_cost / (double)(waves * (cofactor ? 2 : 8)));
+    // Items of about equal cost T, never below one tile.  Pops are atomics at
+    // eight addresses, about 3 ns each over all (65,536 items: 197 us whatever
+    // the work), and the queues end unevenly by about T steps of 40 to 60 ns: for
+    // the S steps of a batch the sum is least at T = sqrt(S / 16), S / T items.
+    // Large batches do better with finer items (up to 65,536, a sixteenth of a
+    // wave's share; a step of the general part is 16 VALU instructions, of the
+    // clause block 2.7).  In items of S / 65,536 throughout: 92 DAGs with n <= 28
+    // 338 us, now 65; 16 systems of 2^24 valuations 351, now 36 (with more words
+    // per lane, above); 256 DAGs 400, now 328; 1024 DAGs 945, now 926.  Items of
+    // falling size, half the work first, bring more programs at a time into the
+    // scalar cache (the 1024: 1014).  With the uniform cofactor an item is a
+    // block's: about eight per block.
+    // A program's items interleave, so the waves working on neighbouring items
+    // at the same time write neighbouring tiles (DNF vectors), which keeps the
+    // HBM writes close together.
+    const double target =
+        cofactor ? std::max(1.0, total_cost / (double)(cus * 64))
+                 : std::max(total_cost / (double)(cus * 256),
+                            std::min(std::sqrt(total_cost / 16.0), (var & 1) ? 550.0 : 3300.0));
     std::vector<fbg::BatchItem> items;
     std::vector<double> cost;
     for (int32_t i : members) {
@@ -1163,6 +1191,7 @@ fbg_status fbg_batch_create(const fbg_program *const *ps, int32_t np, const fbg_
     pl.block = 64 * wpb;
     pl.lds = lds;
     pl.nitems = (uint32_t)sorted.size();
+    pl.pop_ahead = target < ((var & 1) ? 1200.0 : 7200.0);  // about 100 us
     if (tune && tune->direct_run > 0) pl.direct_run = (uint32_t)tune->direct_run;
     pl.max_regs = lds_keep;
     pl.gstride = gstride;
@@ -1249,6 +1278,7 @@ fbg_status batch_launch(fbg_batch *b, int mode, const fbg::BatchProg *d_progs, u
     a.items = pl.d_items;
     a.nitems = pl.nitems;
     a.max_regs = pl.max_regs;
+    a.pop_ahead = pl.pop_ahead;
     a.head = b->d_head + k * fbg::kHeadWords;
     a.counts = d_counts;
     a.gscratch = pl.d_gscratch;
@@ -1618,6 +1648,7 @@ fbg_status fbg_server_launch(fbg_server *sv, const fbg_program *const *ps, int32
   a.items = (const fbg::BatchItem *)(sl.d + items_at);
   a.nitems = (uint32_t)npieces;
   a.max_regs = lds_regs(max_regs, l);
+  a.pop_ahead = 1;
   a.head = (uint32_t *)sl.d;
   a.counts = d_counts;
   a.j16_any = j16_any();

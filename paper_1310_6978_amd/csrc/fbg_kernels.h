@@ -155,6 +155,7 @@ struct BatchArgs {
   uint32_t max_regs;      // LDS registers per wave (beyond vgpr_regs_of(log2w))
   uint32_t *head;     // kHeadWords words of queue heads, zeroed before the launch
   uint64_t *counts;   // per slot; the kernel adds to it
+  uint32_t pop_ahead = 0;  // queue pops overlap the work of the item before (short items)
   uint32_t run = 1;   // k_batch_direct: consecutive tiles per wave
   // registers beyond the max_regs LDS registers (jump-table form only):
   // gstride words of global scratch per wave of the grid, or none
