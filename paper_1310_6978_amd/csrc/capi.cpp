@@ -398,11 +398,25 @@ fbg_status check_tiling(const fbg_program *p, int l) {
   return FBG_OK;
 }
 
+// The words per lane at which a small program is one tile for each wave of one
+// block, or the program's own tiling: such a count or enumeration is a single
+// launch.  Only where a tile's work does not grow with its words: clauses (to
+// n = 18), general parts to 8 words (n = 16).
+int one_block_log2w(const fbg_program *p) {
+  int l = p->auto_log2w;
+  if (p->tuned) return l;
+  for (int k = 0; k <= (p->general() ? 3 : kMaxLog2W); k++)
+    if (p->has_tiling(k) && tiles_of(p->nslices, k) <= (uint64_t)kWavesPerBlock &&
+        lds_per_wave((uint32_t)p->c.nregs, k) * kWavesPerBlock <= kMaxLdsPerBlock)
+      return k;
+  return l;
+}
+
 // Launch shape of an evaluator kernel: a persistent grid of exactly the
 // blocks that can be resident at once (more would only queue behind them and
 // finish in a tail), each wave striding over the tiles.
 fbg_status geometry(const fbg_program *p, const fbg_tune *tune, int mode, Geometry &g) {
-  int l = p->auto_log2w;
+  int l = mode == fbg::EVAL_DNF ? p->auto_log2w : one_block_log2w(p);
   fbg_status st;
   if (tune && tune->words_per_lane && (st = parse_wpl(tune->words_per_lane, l))) return st;
   if ((st = check_tiling(p, l))) return st;
@@ -610,6 +624,12 @@ hipError_t enumerate_passes(fbg::EvalArgs a, char *tmp, uint64_t *d_idx, uint64_
   a.tile_counts = (uint32_t *)tmp;
   if (pass.block_sums && a.direct) a.block_sums = (uint32_t *)(tmp + t.sums);
   hipError_t e = hipSuccess;
+  if (a.direct == fbg::ENUM_ONE_BLOCK) {
+    a.out_idx = d_idx;
+    a.capacity = capacity;
+    a.out_count = d_total;
+    return pass(fbg::EVAL_ENUM, a);
+  }
   if (pass.zero_counts()) e = fbg::launch_zero((uint64_t *)tmp, t.list / 8, nullptr, 0, s);
   if (e == hipSuccess) e = pass(fbg::EVAL_TILECNT, a);
   if (e != hipSuccess) return e;
@@ -638,11 +658,15 @@ hipError_t enumerate_passes(fbg::EvalArgs a, char *tmp, uint64_t *d_idx, uint64_
 template <typename Pass>
 fbg_status enumerate_with(int dev, const fbg::EvalArgs &a, uint64_t *d_idx, uint64_t capacity, uint64_t *d_total,
                           hipStream_t s, const Pass &pass) {
+  hipError_t e = hipSuccess;
+  if (a.direct == fbg::ENUM_ONE_BLOCK) {  // no temporaries
+    e = enumerate_passes(a, nullptr, d_idx, capacity, d_total, s, pass);
+    return e == hipSuccess ? FBG_OK : hip_fail(e, "launch of an enumeration kernel");
+  }
   const size_t bytes = enum_temp(a.nunits, a.direct).bytes;
   char *tmp = nullptr;
   ScratchPool &pool = ScratchPool::of(dev);
   const int block = pool.acquire(bytes, s, &tmp);
-  hipError_t e = hipSuccess;
   if (block < 0) e = hipMallocAsync((void **)&tmp, bytes, s);
   if (e != hipSuccess) return fail(FBG_E_NOMEM, "hipMallocAsync of %zu bytes: %s", bytes, hipGetErrorString(e));
   e = enumerate_passes(a, tmp, d_idx, capacity, d_total, s, pass);
@@ -670,7 +694,12 @@ struct EvalPasses {
     while (g.log2w - (int)a.unit_shift > 2 && (a.ntiles << a.unit_shift) < 32768) a.unit_shift++;
     a.nunits = a.ntiles << a.unit_shift;
     a.part_shift = cofactor_parts(a.ntiles, g);
-    if (a.nunits <= kDirectUnits) a.direct = 1;
+    if (a.nunits <= kDirectUnits) a.direct = fbg::ENUM_DIRECT;
+    if (a.ntiles <= (uint64_t)(g.block / 64)) {
+      a.direct = fbg::ENUM_ONE_BLOCK;
+      a.unit_shift = 0;
+      a.nunits = a.ntiles;
+    }
     return a;
   }
   hipError_t operator()(int mode, fbg::EvalArgs a) const {
@@ -925,7 +954,8 @@ fbg_status fbg_count_tuned(const fbg_program *p, uint64_t *d_count, const fbg_tu
   fbg::EvalArgs a = base_args(p, g.log2w);
   a.out_count = d_count;
   a.part_shift = cofactor_parts(a.ntiles, g);
-  e = fbg::launch_set_u64(d_count, 0, s);
+  // (one block stores the count; more add to it)
+  e = g.grid > 1 ? fbg::launch_set_u64(d_count, 0, s) : hipSuccess;
   if (e != hipSuccess) return hip_fail(e, "launch");
   e = fbg::launch_eval(fbg::EVAL_COUNT, g.log2w, p->variant(tune), a, g.grid, g.block, g.lds, s);
   return e == hipSuccess ? FBG_OK : hip_fail(e, "launch of the count kernel");
@@ -1013,9 +1043,12 @@ fbg_status fbg_enumerate_dnf(const uint64_t *d_dnf, int32_t n_vars, uint64_t *d_
   memset(&a, 0, sizeof a);
   a.n = n_vars;
   a.nslices = 2 * dnf_words_of(n_vars);  // bits at or above 2^n are zero in a DNF vector
-  const ScanPasses pass{dev, n_vars <= 27 ? 2 : 5, (hipStream_t)stream};
+  // (n <= 18: four tiles of 8 KiB, one block)
+  const ScanPasses pass{dev, n_vars > 18 && n_vars <= 27 ? 2 : 5, (hipStream_t)stream};
   a.nunits = a.ntiles = tiles_of(a.nslices, pass.log2w);
-  a.direct = a.nunits <= kDirectScanTiles;
+  a.direct = a.nunits <= kWavesPerBlock     ? fbg::ENUM_ONE_BLOCK
+             : a.nunits <= kDirectScanTiles ? fbg::ENUM_DIRECT
+                                            : fbg::ENUM_LISTED;
   a.out32 = (uint32_t *)d_dnf;
   return enumerate_with(dev, a, d_idx, capacity, d_total, pass.s, pass);
 }

@@ -551,6 +551,18 @@ __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
   return a + b;
 }
 
+// The sum over a block's waves of a per-lane value, for every thread (part: a
+// word pair per wave).
+__device__ __forceinline__ uint64_t block_sum_u64(uint64_t v, uint64_t *part, uint32_t lane, uint32_t wib,
+                                                  uint32_t wpb) {
+  v = wave_sum_u64(v);
+  if (lane == 0) part[wib] = v;
+  __syncthreads();
+  uint64_t s = 0;
+  for (uint32_t w = 0; w < wpb; w++) s += part[w];
+  return s;
+}
+
 // Inclusive prefix sum over the 64 lanes: four row shifts and two row
 // broadcasts on the VALU (DPP), against six dependent LDS permutes of a
 // __shfl_up scan.  Every lane must be active.
@@ -654,7 +666,11 @@ __device__ __forceinline__ void tile_compact(const uint32_t (&acc)[1 << LOG2W], 
 
 // Compaction passes find the output position of a unit's models in one of two
 // ways (the host chooses, capi.cpp):
-//  - few units (a.direct): block b takes the units [b wpb, (b + 1) wpb), one per
+//  - at most a block's waves' worth of units (ENUM_ONE_BLOCK): one launch of one
+//    block, a unit per wave, no counting pass and no temporaries; the waves
+//    rank themselves (one_block_position).  Models of a theory over 15 letters:
+//    14 us a call with the two passes, 6.6 so.
+//  - few units (ENUM_DIRECT): block b takes the units [b wpb, (b + 1) wpb), one per
 //    wave, and adds up the counts of all units before them itself (their sums
 //    per block where the counting pass left them, a.block_sums); no scan kernel
 //    runs.  The last block writes the total.
@@ -666,7 +682,9 @@ __device__ __forceinline__ void for_model_units(const EvalArgs &a, uint32_t lane
                                                 uint64_t *part, Body &&body) {
   // the steps this wave takes: one unit of the block, or entries of the list
   uint64_t k = (uint64_t)blockIdx.x * wpb + wib, step = (uint64_t)gridDim.x * wpb, n, at = 0;
-  if (a.direct) {
+  if (a.direct == ENUM_ONE_BLOCK) {
+    n = wpb;  // also waves without a tile, for the barrier
+  } else if (a.direct) {
     n = a.nunits;
     const uint32_t first = blockIdx.x * wpb;
     const uint32_t c = lane < wpb && first + lane < (uint32_t)n ? a.tile_counts[first + lane] : 0u;
@@ -700,6 +718,26 @@ __device__ __forceinline__ void for_model_units(const EvalArgs &a, uint32_t lane
     }
     body(u, at);
   }
+}
+
+// ENUM_ONE_BLOCK: the position of this wave's models among those of the block's
+// waves; the first thread writes the total.
+template <int LOG2W>
+__device__ __forceinline__ uint64_t one_block_position(const uint32_t (&acc)[1 << LOG2W], const EvalArgs &a,
+                                                       uint64_t *part, uint32_t lane, uint32_t wib, uint32_t wpb) {
+  uint32_t c = 0;
+#pragma unroll
+  for (int i = 0; i < (1 << LOG2W); i++) c += __popc(acc[i]);
+  c = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(c), 63);
+  if (lane == 0) part[wib] = c;
+  __syncthreads();
+  uint64_t at = 0, total = 0;
+  for (uint32_t w = 0; w < wpb; w++) {
+    if (w < wib) at += part[w];
+    total += part[w];
+  }
+  if (threadIdx.x == 0) *a.out_count = total;
+  return at;
 }
 
 // DNF write-out and count of one tile: the words past the valuation space
@@ -776,9 +814,9 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_eval(EvalArgs a)
   uint64_t total = 0;
   GenState<W> st;
   if (VAR & 1) st.clear();
+  __shared__ uint64_t part[4];
   if (MODE == MODE_ENUM) {
     // (the cofactor variant is not needed here: these tiles hold models)
-    __shared__ uint64_t part[4];
     for_model_units(a, lane, wib, wpb, part, [&](uint32_t u, uint64_t at) __attribute__((always_inline)) {
       const uint64_t U0 = (uint64_t)(u >> a.unit_shift) << LOG2W;
       const uint32_t rows = W >> a.unit_shift, r0 = (u & ((1u << a.unit_shift) - 1u)) * rows;
@@ -786,6 +824,7 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_eval(EvalArgs a)
       run_program<LOG2W, (VAR & 1) != 0>(a.code, a.nins, U0, lane, acc, st, regs, a.nregs * (W * 256u), nullptr,
                                          a.j16_any);
       mask_tail<LOG2W>(acc, U0, lane, a.nslices, a.n);
+      if (a.direct == ENUM_ONE_BLOCK) at = one_block_position<LOG2W>(acc, a, part, lane, wib, wpb);
       tile_compact<LOG2W>(acc, r0, rows, U0, lane, at, a.out_idx, a.capacity, (uint16_t *)regs);
     });
     return;
@@ -841,8 +880,16 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_eval(EvalArgs a)
     for (uint64_t t = wave; t < a.ntiles; t += nwaves) tile(t, true);
   }
   if (MODE == MODE_COUNT) {
-    const uint64_t s = wave_sum_u64(total);
-    if (lane == 0 && s) atomicAdd((unsigned long long *)a.out_count, (unsigned long long)s);
+    // one atomic per block: they meet at one address, 12 ns each (triangle-free
+    // graphs, n = 28, 2384 of 8192 waves with models: 29 of 36 us with one per
+    // wave).  A launch of one block stores its sum: nothing clears the count.
+    const uint64_t s = block_sum_u64(total, part, lane, wib, wpb);
+    if (threadIdx.x == 0) {
+      if (gridDim.x == 1)
+        *a.out_count = s;
+      else if (s)
+        atomicAdd((unsigned long long *)a.out_count, (unsigned long long)s);
+    }
   }
 }
 
@@ -878,6 +925,7 @@ __global__ __launch_bounds__(256) void k_dnf_scan(EvalArgs a) {
       uint32_t acc[W];
       const uint64_t U0 = (uint64_t)u << LOG2W;
       load(U0, acc);
+      if (a.direct == ENUM_ONE_BLOCK) at = one_block_position<LOG2W>(acc, a, part, lane, wib, wpb);
       tile_compact<LOG2W>(acc, 0u, W, U0, lane, at, a.out_idx, a.capacity, stage[wib]);
     });
     return;
@@ -1039,8 +1087,23 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_batch(BatchArgs 
       }
     }
   }
+  // the waves of a block mostly end in the same program: one atomic for them
+  __shared__ uint64_t part[4];
+  __shared__ uint32_t part_slot[4];
   const uint64_t s = wave_sum_u64(total);
-  if (lane == 0 && s) atomicAdd((unsigned long long *)(a.counts + cur_slot), (unsigned long long)s);
+  if (lane == 0) part[wib] = s, part_slot[wib] = cur_slot;
+  __syncthreads();
+  if (threadIdx.x < wpb) {
+    const uint32_t me = threadIdx.x;
+    uint64_t sum = 0;
+    bool first = true;  // of the waves with this slot
+    for (uint32_t w = 0; w < wpb; w++) {
+      if (part_slot[w] != part_slot[me]) continue;
+      sum += part[w];
+      first = first && w >= me;
+    }
+    if (first && sum) atomicAdd((unsigned long long *)(a.counts + part_slot[me]), (unsigned long long)sum);
+  }
 }
 
 // Batched DNF write-out of a plan of clause-only programs without the uniform

@@ -21,6 +21,9 @@ inline uint32_t vgpr_regs_of(int log2w) { return log2w == FBG_J16_LOG2W ? kJ16Vg
 // least the 2048 of a row of 64 words).
 constexpr uint32_t kStageModels = 2048;
 
+// EvalArgs.direct
+enum { ENUM_LISTED = 0, ENUM_DIRECT = 1, ENUM_ONE_BLOCK = 2 };
+
 struct EvalArgs {
   const uint32_t *code;   // encoded program: clause block, instructions, pattern table
   uint32_t nins;          // instructions after the clause block (16 words per lane: 2-word units)
@@ -35,10 +38,10 @@ struct EvalArgs {
   uint32_t *tile_counts;  // per unit: MODE_TILECNT (out), MODE_ENUM (in)
   uint32_t part_shift;    // uniform cofactor: 2^part_shift waves share a group of 64 tiles
   // Units of the enumeration passes: 2^unit_shift to a tile (fbg_device.h).
-  // MODE_ENUM: with `direct` a wave takes one unit, its block finding their
-  // positions from tile_counts (or block_sums) and the last block writing the
-  // total to out_count; else the list of the units that hold models
-  // (TileListArgs)
+  // MODE_ENUM: with `direct` a wave takes one unit; its block finds their
+  // positions from tile_counts (or block_sums), the last block writing the
+  // total to out_count, or there is only one block and no tile counts.  Else the
+  // list of the units that hold models (TileListArgs)
   uint32_t unit_shift;
   uint32_t direct;
   uint64_t nunits;
