@@ -130,3 +130,34 @@ def test_batch_programs_inside_list_blocks(F, wpl):
         for o, w, c in zip(outs, wants, counts.cpu().tolist()):
             got = o.cpu().numpy()
             assert c == len(w) and np.array_equal(got[:c].view(np.uint64), w) and (got[c:] == -7).all()
+
+
+@pytest.mark.parametrize("general", [False, True])
+@pytest.mark.parametrize("wpl", [1, 4, 16, 32])
+def test_tiles_that_end_early(F, wpl, general):
+    """Clauses that empty some tiles through tile literals, some through lane
+    and in-word literals only, and some only through word literals, before a
+    general part: counts (alone, in a batch, through a server) and models."""
+    import torch
+    n = 20
+    rng = random.Random(7)
+    text = "x19 | x18\n~x19 | x17 | ~x16\nx0 | x5\n~x0 | x6\nx3 | ~x7 | x19\n"        # tile, lane and in-word
+    text += "x11 | x12 | x19\n~x12 | x11 | x18\n" + random_cnf(rng, n, 12, (2, 3))    # word bits at some tilings
+    text += "x18 | ~x0 | ~x5\nx18 | x0 | ~x5\nx18 | x5 | ~x6\nx18 | x6\n~x6 | x18\n"  # nothing left where x18 is false
+    if general:
+        text += "(x1 ^ x2 ^ x19) | (x4 & ~x13)\n"
+    p = F.Program(text, n)
+    want, c = oracle.models(text, n)
+    assert c > 0
+    print("early", wpl, general, c, flush=True)
+    assert int(F.count(p, words_per_lane=wpl).item()) == c
+    assert F.count_batch([p, p], words_per_lane=wpl).cpu().tolist() == [c, c]
+    sv = F.Server(2, 64, wpl)
+    counts = torch.zeros(2, dtype=torch.int64, device="cuda")
+    t = F.program_tiles(p, wpl)
+    sv.launch([p], [(0, 0, 0, t // 3), (0, 1, t // 3, t)], counts)
+    torch.cuda.synchronize()
+    assert sum(counts.cpu().tolist()) == c
+    sv.free()
+    p.set_tuning(wpl)
+    lists(lambda cap, out, tot: F.enumerate_models(p, cap, out=out, total=tot), want, [c + 1])
