@@ -1179,21 +1179,23 @@ fbg_status fbg_batch_create(const fbg_program *const *ps, int32_t np, const fbg_
     // eight addresses, about 3 ns each over all (65,536 items: 197 us whatever
     // the work), and the queues end unevenly by about T steps of 40 to 60 ns: for
     // the S steps of a batch the sum is least at T = sqrt(S / 16), S / T items.
-    // Large batches do better with finer items (up to 65,536, a sixteenth of a
-    // wave's share; a step of the general part is 16 VALU instructions, of the
-    // clause block 2.7).  In items of S / 65,536 throughout: 92 DAGs with n <= 28
-    // 338 us, now 65; 16 systems of 2^24 valuations 351, now 36 (with more words
-    // per lane, above); 256 DAGs 400, now 328; 1024 DAGs 945, now 926.  Items of
-    // falling size, half the work first, bring more programs at a time into the
-    // scalar cache (the 1024: 1014).  With the uniform cofactor an item is a
-    // block's: about eight per block.
+    // Large batches of general programs do better with finer items (up to 65,536,
+    // a sixteenth of a wave's share); a step of clauses is shorter (2.7 VALU
+    // instructions, 16 in the general part, and most tiles stop early), which
+    // puts T at sqrt(S / 6).  In items of S / 65,536 throughout: 92 DAGs with
+    // n <= 28 338 us, now 65; 256 DAGs 400, now 328; 1024 DAGs 945, now 926;
+    // 16 systems of 2^24 valuations 351, now 32 (with more words per lane,
+    // above), of 2^32 204, now 180.  Items of falling size, half the work first,
+    // bring more programs at a time into the scalar cache (the 1024: 1014).  With
+    // the uniform cofactor an item is a block's: about eight per block.
     // A program's items interleave, so the waves working on neighbouring items
     // at the same time write neighbouring tiles (DNF vectors), which keeps the
     // HBM writes close together.
-    const double target =
-        cofactor ? std::max(1.0, total_cost / (double)(cus * 64))
-                 : std::max(total_cost / (double)(cus * 256),
-                            std::min(std::sqrt(total_cost / 16.0), (var & 1) ? 550.0 : 3300.0));
+    double target = std::sqrt(total_cost / 6.0);
+    if (cofactor)
+      target = std::max(1.0, total_cost / (double)(cus * 64));
+    else if (var & 1)
+      target = std::max(total_cost / (double)(cus * 256), std::min(std::sqrt(total_cost / 16.0), 550.0));
     std::vector<fbg::BatchItem> items;
     std::vector<double> cost;
     for (int32_t i : members) {

@@ -294,7 +294,8 @@ typedef const __attribute__((address_space(4))) char *code_byte_ptr;
 // its first chunks.  Counting uses it; the DNF write-out of clause programs does
 // not (it waits for the stores, which the evaluation spreads out).  One count of
 // a 3-CNF system of 136 clauses over 35 letters: 398 us to the end of every
-// tile, 85 so, 63 with the tiles scattered over the waves (k_eval).
+// tile, 85 so, 58 with the tiles scattered over the waves (k_eval), 47 where a
+// chunk of group 0 alone does not look for keys of the other groups.
 template <int LOG2W, bool STOP>
 __device__ __forceinline__ bool run_clauses(const uint32_t *__restrict__ cb_g, const code_ptr table, uint64_t U0,
                                             uint32_t lane, uint32_t (&acc)[1 << LOG2W]) {
@@ -316,16 +317,34 @@ __device__ __forceinline__ bool run_clauses(const uint32_t *__restrict__ cb_g, c
     // keys by group; hd[5 + g] is where group g's keys end (bytes)
     const code_byte_ptr hb = (code_byte_ptr)h;
     uint32_t off = (FBG_CB_CHUNK_HDR + 64 + 4 * nc) * 4;
+    auto keys = [&](int g) __attribute__((always_inline)) {
+      if (!STOP) {
+        // the whole block runs: two keys to a scalar load (the write-out of 16
+        // vectors of 2^32 bits: 1331 -> 1307 us; a count that mostly stops in
+        // its first chunk loses more to the second compare than it gains)
+        for (; off + 16 <= hd[5 + g]; off += 16) {
+          const u32x4 km = *(const __attribute__((address_space(4))) u32x4 *)(hb + off);
 #pragma unroll
-    for (int g = 0; g < NG; g++) {
+          for (int j = 0; j < 4; j += 2) {
+            const uint32_t x = (uint32_t)__builtin_amdgcn_sbfe((int)A, km[j], 1u);
+            G[g] = __builtin_amdgcn_bitop3_b32(G[g], km[j + 1], x, kTT_KEY);
+          }
+        }
+      }
       for (; off < hd[5 + g]; off += 8) {
         const u32x2 km = *(const __attribute__((address_space(4))) u32x2 *)(hb + off);
         const uint32_t x = (uint32_t)__builtin_amdgcn_sbfe((int)A, km[0], 1u);
         G[g] = __builtin_amdgcn_bitop3_b32(G[g], km[1], x, kTT_KEY);
       }
-    }
-    if (STOP && __ballot(G[0] != 0u) == 0ull) return false;
+    };
+    keys(0);
     ch += hd[1];
+    if (STOP) {
+      if (__ballot(G[0] != 0u) == 0ull) return false;
+      if (off >= hd[5 + NG - 1]) continue;  // a chunk of group 0 alone, as the first ones are
+    }
+#pragma unroll
+    for (int g = 1; g < NG; g++) keys(g);
   }
   // the first multi chunk: its false runs now, its keys inside the tree
   u32x16 mh = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
