@@ -610,13 +610,18 @@ EnumTemp enum_temp(uint64_t nu, bool direct) {
   return t;
 }
 
+// From this many tiles on, the uniform-cofactor test of an enumeration has a
+// launch of its own (launch_cofactor_masks): below it there are few enough groups
+// for several waves to repeat a group's test.
+constexpr uint64_t kMaskTiles = 1ull << 18;
+
 // Two-pass enumeration given the pass launcher and the temporaries `tmp`
 // (enum_temp(a.nunits, a.direct).bytes of device memory): counts per unit, the
 // list of the units that hold models unless direct, compaction.  Every
 // temporary word is written before it is read.  pass.zero_counts (the
 // uniform-cofactor passes, which write the counts of live tiles only): a fill
-// kernel clears the counts first, in one coalesced sweep instead of a scattered
-// write per dead tile.
+// kernel, or the one that makes the masks, clears the counts first, in one
+// coalesced sweep instead of a scattered write per dead tile.
 template <typename Pass>
 hipError_t enumerate_passes(fbg::EvalArgs a, char *tmp, uint64_t *d_idx, uint64_t capacity, uint64_t *d_total,
                             hipStream_t s, const Pass &pass) {
@@ -630,7 +635,18 @@ hipError_t enumerate_passes(fbg::EvalArgs a, char *tmp, uint64_t *d_idx, uint64_
     a.out_count = d_total;
     return pass(fbg::EVAL_ENUM, a);
   }
-  if (pass.zero_counts()) e = fbg::launch_zero((uint64_t *)tmp, t.list / 8, nullptr, 0, s);
+  if (pass.zero_counts() && a.ntiles >= kMaskTiles && !a.direct) {
+    // the masks lie where the list comes later; a group set per 64 groups, its
+    // live tiles over the waves of the device
+    uint64_t *masks = (uint64_t *)(tmp + t.list);
+    e = fbg::launch_cofactor_masks(a.code, a.ntiles / 64, masks, a.tile_counts, a.unit_shift, pass.fill_grid(), s);
+    a.masks = masks;
+    a.part_shift = 0;
+    while (a.part_shift < 6 && (a.ntiles >> 12 << a.part_shift) < (uint64_t)pass.fill_grid() * kWavesPerBlock)
+      a.part_shift++;
+  } else if (pass.zero_counts()) {
+    e = fbg::launch_zero((uint64_t *)tmp, t.list / 8, nullptr, 0, s);
+  }
   if (e == hipSuccess) e = pass(fbg::EVAL_TILECNT, a);
   if (e != hipSuccess) return e;
   a.out_idx = d_idx;
@@ -686,6 +702,7 @@ struct EvalPasses {
   int var;
   hipStream_t s;
   bool zero_counts() const { return (var & 2) != 0; }
+  int fill_grid() const { return cu_count(p->device) * 8; }
   // Tiles are cut into units of at least four rows while there are fewer than
   // 32768: the models of a theory crowd into few tiles, and the fullest unit
   // is what the compaction waits for (tile_compact).
@@ -723,6 +740,7 @@ struct ScanPasses {
   int dev, log2w;
   hipStream_t s;
   bool zero_counts() const { return false; }
+  int fill_grid() const { return 1; }
   hipError_t operator()(int mode, const fbg::EvalArgs &a) const {
     const uint64_t blocks = (a.ntiles + kWavesPerBlock - 1) / kWavesPerBlock;
     const uint64_t grid = a.direct ? blocks : std::min<uint64_t>(blocks, (uint64_t)cu_count(dev) * 8);

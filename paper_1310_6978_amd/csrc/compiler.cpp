@@ -1417,8 +1417,8 @@ uint32_t encode_program(const Compiled &c, int log2w, std::vector<uint32_t> &wor
       }
       ncof++;
     }
-  // up to a multiple of four entries with clauses that hold everywhere
-  for (uint32_t k = ncof; k % 4; k++)
+  // up to a multiple of eight entries with clauses that hold everywhere
+  for (uint32_t k = ncof; k % 8; k++)
     for (const uint32_t v : {0u, 0u, 0u, 0u, ~0u, ~0u, 0u, 0u}) block.push_back(v);
   if (nstat > 0) block[FBG_CB_HDR + 4] = ncof;
   block[0] = (uint32_t)block.size();
@@ -1763,7 +1763,7 @@ uint32_t clause_block_value(const uint32_t *cb, const uint32_t *table, int log2w
   const uint32_t *ch = cb + FBG_CB_HDR;
   if (cof && cb[1] > 0) {  // the uniform-cofactor table at the end of the block
     const uint32_t ncof = ch[4];
-    const uint32_t *td = cb + cb[0] - FBG_CB_COF_WORDS * ((ncof + 3) / 4 * 4);
+    const uint32_t *td = cb + cb[0] - FBG_CB_COF_WORDS * ((ncof + 7) / 8 * 8);
     const uint64_t t = U0 >> log2w;
     for (uint32_t c = 0; c < ncof; c++, td += FBG_CB_COF_WORDS) {
       const uint64_t sel = (uint64_t)td[0] | ((uint64_t)td[1] << 32);

@@ -413,18 +413,25 @@ __device__ __forceinline__ bool run_clauses(const uint32_t *__restrict__ cb_g, c
 // tiles; the clauses that do not depend on the tile within the group come first
 // and most groups end after a few of them (equivalence relations on 9 elements:
 // 9 of the 90 clauses on average).
+// STEP entries are fetched and tested between two looks at the result.
+template <uint32_t STEP>
 __device__ __forceinline__ uint64_t group_alive(const uint32_t *__restrict__ cb_g, uint64_t g) {
   const code_ptr cb = (code_ptr)cb_g;
   uint64_t alive = ~0ull;
   if (cb[1] == 0) return alive;
-  const uint32_t k = (cb[FBG_CB_HDR + 4] + 3) / 4 * 4;
+  const uint32_t k = (cb[FBG_CB_HDR + 4] + 7) / 8 * 8;
   const code_ptr td = cb + cb[0] - FBG_CB_COF_WORDS * k;
-  for (uint32_t c = 0; c < k && alive != 0ull; c += 4) {
-    const u32x16 e0 = *(const __attribute__((address_space(4))) u32x16 *)(td + FBG_CB_COF_WORDS * c);
-    const u32x16 e1 = *(const __attribute__((address_space(4))) u32x16 *)(td + FBG_CB_COF_WORDS * (c + 2));
+  for (uint32_t c = 0; c < k && alive != 0ull; c += STEP) {
+    u32x16 e[STEP / 2];
+#pragma unroll
+    for (uint32_t j = 0; j < STEP / 2; j++)
+      e[j] = *(const __attribute__((address_space(4))) u32x16 *)(td + FBG_CB_COF_WORDS * (c + 2 * j));
 #define FBG_U64(v, i) ((uint64_t)v[i] | ((uint64_t)v[(i) + 1] << 32))
 #define FBG_TEST(v, i) alive &= (g & FBG_U64(v, i)) != FBG_U64(v, (i) + 2) ? ~0ull : FBG_U64(v, (i) + 4);
-    FBG_TEST(e0, 0) FBG_TEST(e0, 8) FBG_TEST(e1, 0) FBG_TEST(e1, 8)
+#pragma unroll
+    for (uint32_t j = 0; j < STEP / 2; j++) {
+      FBG_TEST(e[j], 0) FBG_TEST(e[j], 8)
+    }
 #undef FBG_TEST
 #undef FBG_U64
   }
@@ -470,7 +477,7 @@ __device__ __forceinline__ uint32_t visit_group(const uint32_t *__restrict__ cod
   uint64_t valid = ~0ull;
   if (first < t0) valid &= ~0ull << (t0 - first);            // t0 < first + 64
   if (first + 64 > t1) valid &= ~0ull >> (first + 64 - t1);  // first < t1
-  const uint64_t alive = group_alive(code, g) & valid;
+  const uint64_t alive = group_alive<4>(code, g) & valid;
   for (uint64_t todo = ALL ? valid : alive; todo; r++, todo &= todo - 1) {
     if ((r & mask) != part) continue;
     const uint32_t l = (uint32_t)__builtin_ctzll(todo);
@@ -923,6 +930,32 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_eval(EvalArgs a)
     // (group, part) of the launch is taken at a hash of k: live groups share
     // their low index bits, and a power-of-two stride would give them all to a
     // few waves.
+    if (MODE == MODE_TILECNT && a.masks) {
+      // The tests are done (k_cofactor_masks).  A wave looks at 64 groups, a mask
+      // per lane, and takes every 2^part_shift-th of their live
+      // tiles: mostly one tile or none.  Equivalence relations on 9 elements (825
+      // live tiles of 2^20, up to 12 in a group): 12 us and 11, 40 with the test in
+      // the wave, whose three evaluations in a row took 9 us each.
+      // (2^18 <= ntiles <= 2^38, a power of two)
+      const uint32_t nsets = (uint32_t)(a.ntiles >> 12), sets = 31u - (uint32_t)__builtin_clz(nsets);
+      const uint32_t pm = (1u << a.part_shift) - 1u;
+      for (uint64_t x = wave; x < (uint64_t)nsets << a.part_shift; x += nwaves) {
+        const uint32_t set = (uint32_t)x & (nsets - 1u), part_no = (uint32_t)(x >> sets);
+        // live groups share index bits, high or low: scattered
+        const uint32_t g = (uint32_t)scatter_tile((uint64_t)lane * nsets + set, sets + 6u);
+        const uint64_t m = a.masks[g];
+        uint32_t r = 0;
+        for (uint64_t b = __ballot(m != 0ull); b; b &= b - 1) {
+          const uint32_t l = (uint32_t)__builtin_ctzll(b);
+          uint64_t todo = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)m, l) |
+                          (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(m >> 32), l) << 32;
+          for (; todo; r++, todo &= todo - 1)
+            if ((r & pm) == part_no)
+              tile((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)g, l) * 64 + (uint32_t)__builtin_ctzll(todo), true);
+        }
+      }
+      return;
+    }
     const uint64_t n = ((a.ntiles + 63) / 64) << a.part_shift;
     uint32_t bits = 0;
     while ((1ull << bits) < n) bits++;
@@ -1322,6 +1355,21 @@ constexpr int LIST_PER_THREAD = kListBlock / LIST_THREADS;
 static_assert(LIST_PER_THREAD == 8, "two 16-byte loads a thread");
 
 #ifdef FBG_DEVICE_MISC_KERNELS  // defined once, in misc.hip
+
+// The uniform-cofactor test of every group of 64 tiles (ntiles a multiple of
+// 64): the live tiles' mask, and zeros for the model counts of the group's
+// units.  A wave per group and step.
+__global__ __launch_bounds__(256) void k_cofactor_masks(const uint32_t *code, uint64_t ngroups, uint64_t *masks,
+                                                        uint32_t *counts, uint32_t unit_shift) {
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint64_t wave = (uint64_t)blockIdx.x * (blockDim.x >> 6) + (uni(threadIdx.x) >> 6);
+  const uint64_t nwaves = (uint64_t)gridDim.x * (blockDim.x >> 6);
+  for (uint64_t g = wave; g < ngroups; g += nwaves) {
+    const uint64_t alive = group_alive<8>(code, g);
+    if (lane == 0) masks[g] = alive;
+    for (uint32_t j = 0; j < (1u << unit_shift); j++) counts[((g << unit_shift) + j) * 64 + lane] = 0u;
+  }
+}
 
 // The counts of a thread's eight tiles (the counts array is 256-byte aligned).
 __device__ __forceinline__ void load_counts(const uint32_t *in, uint64_t n, uint64_t at, uint32_t (&c)[8]) {

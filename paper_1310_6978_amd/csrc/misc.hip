@@ -47,6 +47,12 @@ hipError_t launch_dnf_scan(int mode, int log2w, const EvalArgs &a, int grid, int
   return hipGetLastError();
 }
 
+hipError_t launch_cofactor_masks(const uint32_t *code, uint64_t ngroups, uint64_t *masks, uint32_t *counts,
+                                 uint32_t unit_shift, int grid, hipStream_t s) {
+  hipLaunchKernelGGL(dev::k_cofactor_masks, dim3(grid), dim3(256), 0, s, code, ngroups, masks, counts, unit_shift);
+  return hipGetLastError();
+}
+
 uint64_t tile_list_blocks(uint64_t n) { return (n + kListBlock - 1) / kListBlock; }
 
 hipError_t launch_tile_list(const TileListArgs &a, hipStream_t s) {

@@ -68,11 +68,12 @@ def test_lists(F, kind, wpl, n):
     lists(lambda cap, out, tot: F.enumerate_dnf(dnf, n, cap, out=out, total=tot), want, caps)
 
 
-@pytest.mark.parametrize("n,wpl", [(22, 1), (23, 1), (24, 1), (23, 8), (25, 16), (28, 32)])
+@pytest.mark.parametrize("n,wpl", [(22, 1), (23, 1), (24, 1), (23, 8), (25, 16), (28, 32), (29, 1)])
 @pytest.mark.parametrize("cofactor", [False, True])
 def test_tile_thresholds(F, n, wpl, cofactor):
     """4096 units (n = 23 at one word per lane) are the last without a list;
-    tiles are cut into units of four rows and more below 32768 units."""
+    tiles are cut into units of four rows and more below 32768 units; from
+    2^18 tiles (n = 29) the cofactor test has a launch of its own."""
     text = workloads.random_3cnf(n, 3 * n, n)[0]
     p = F.Program(text, n)
     p.set_tuning(wpl, cofactor=cofactor)
