@@ -141,7 +141,8 @@ class CodeArena {
 // completed, so calls on any streams and threads may overlap, each with its own
 // block; with every block in flight, under stream capture (a graph may replay
 // at any time) or beyond kBlock bytes the caller allocates on its stream as
-// before.  At most kBlocks blocks of a device, freed with its last program.
+// before.  At most kBlocks blocks of a device; with its last program all but one
+// go back (stream-ordered: no call waits for the device).
 class ScratchPool {
  public:
   static constexpr size_t kBlock = (size_t)16 << 20;
@@ -152,11 +153,13 @@ class ScratchPool {
     static std::vector<ScratchPool *> pools;
     std::lock_guard<std::mutex> g(m);
     if ((size_t)dev >= pools.size()) pools.resize((size_t)dev + 1, nullptr);
-    if (!pools[(size_t)dev]) pools[(size_t)dev] = new ScratchPool();
+    if (!pools[(size_t)dev]) pools[(size_t)dev] = new ScratchPool(dev);
     return *pools[(size_t)dev];
   }
 
-  // A block for `bytes` of work on s, or -1.
+  explicit ScratchPool(int dev) : dev_(dev) { b_.reserve(kBlocks); }
+
+  // A block for `bytes` of work on s, a stream of the current device, or -1.
   int acquire(size_t bytes, hipStream_t s, char **out) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (bytes > kBlock || hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return -1;
@@ -174,9 +177,10 @@ class ScratchPool {
     }
     if (b_.size() >= (size_t)kBlocks) return -1;
     Block n;
-    if (hipMalloc((void **)&n.p, kBlock) != hipSuccess) return -1;
+    // on s, where its first use follows; later uses follow that one's event
+    if (hipMallocAsync((void **)&n.p, kBlock, s) != hipSuccess) return -1;
     if (hipEventCreateWithFlags(&n.done, hipEventDisableTiming) != hipSuccess) {
-      (void)hipFree(n.p);
+      (void)hipFreeAsync(n.p, s);
       return -1;
     }
     b_.push_back(n);
@@ -199,16 +203,19 @@ class ScratchPool {
   }
   void program_removed() {
     std::lock_guard<std::mutex> g(mu_);
-    if (--programs_ > 0) return;
+    if (--programs_ > 0 || b_.size() < 2) return;
+    int cur = -1;
+    if (hipGetDevice(&cur) != hipSuccess || cur != dev_) return;  // (with a later program of the device)
     const RelaxedCapture relaxed;
-    for (size_t i = b_.size(); i-- > 0;) {
-      if (b_[i].taken) return;  // in use by another thread; later blocks keep their index
-      if (b_[i].used && hipEventQuery(b_[i].done) != hipSuccess) {
+    while (b_.size() > 1) {
+      const Block &n = b_.back();
+      if (n.taken) return;  // in use by another thread; the blocks before it keep their index
+      if (n.used && hipEventQuery(n.done) != hipSuccess) {
         (void)hipGetLastError();
         return;
       }
-      (void)hipEventDestroy(b_[i].done);
-      (void)hipFree(b_[i].p);
+      (void)hipEventDestroy(n.done);
+      (void)hipFreeAsync(n.p, nullptr);
       b_.pop_back();
     }
   }
@@ -231,6 +238,7 @@ class ScratchPool {
     *out = b_[k].p;
     return (int)k;
   }
+  const int dev_;
   std::mutex mu_;
   std::vector<Block> b_;
   size_t next_ = 0;

@@ -162,3 +162,39 @@ def test_tiles_that_end_early(F, wpl, general):
     sv.free()
     p.set_tuning(wpl)
     lists(lambda cap, out, tot: F.enumerate_models(p, cap, out=out, total=tot), want, [c + 1])
+
+
+def test_overlapping_enumerations(F):
+    """More calls in flight than the scratch pool has blocks, on several
+    streams and threads, and again after the last program has gone."""
+    import threading
+
+    import torch
+    text, n = workloads.equivalence_relations(8)      # 28 letters, 4140 models
+    for _ in range(2):
+        p = F.Program(text, n)
+        want = None
+        got, errors = {}, []
+
+        def work(t):
+            try:
+                s = torch.cuda.Stream()
+                with torch.cuda.stream(s):
+                    got[t] = [F.enumerate_models(p, 4200) for _ in range(8)]
+                s.synchronize()
+            except Exception as e:  # noqa: BLE001 - reported below
+                errors.append(e)
+        threads = [threading.Thread(target=work, args=(t,)) for t in range(4)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        assert not errors, errors
+        for lists_ in got.values():
+            for m, tot in lists_:
+                assert int(tot.item()) == 4140
+                m = m.cpu().numpy()[:4140]
+                want = m if want is None else want
+                assert np.array_equal(m, want)
+        assert (np.diff(want) > 0).all()
+        p.free()
