@@ -12,7 +12,7 @@ programs resident on the device:
                   generator synthesis, evaluation, the 2^32-bit DNF vector of
                   every instance (512 MiB each), its model count and the
                   model count of every tile
-  * enumerate     one batched enumeration: a scan over the tile counts of all
+  * enumerate     one batched enumeration: a list of the tiles with models of all
                   instances and one compaction launch that reads the DNF
                   vectors only in tiles holding models
 
@@ -74,7 +74,7 @@ PAPER_CONTEXT = {"valuations_per_s": 2.0 ** 30, "node_bit_ops_per_s": 2.0 ** 47,
 # (their code, comments left out) the counters were taken on.  The bench line
 # reports the bytes only while the sources still have that digest, and null
 # otherwise.
-C1_TRAFFIC = {"bytes": 8606066816, "kernel_sources_sha1": "f9c1039855fcdb7cf1166deeffbccc7ce8e7d404"}
+C1_TRAFFIC = {"bytes": 8603526912, "kernel_sources_sha1": "a95a5b34e45e8b31bca9da30af88b4815b94b93e"}
 KERNEL_SOURCES = ("fbg_device.h", "fbg_asm16.h", "fbg_isa.h", "fbg_kernels.h", "batch.hip")
 
 
@@ -578,7 +578,7 @@ def bench_theories(args, torch, fbg):
                     best = ms
         vals += 2.0 ** n
         best_total += best
-        # every model listed (two passes: tile counts and scan, then the
+        # every model listed (two passes: tile counts and their list, then the
         # compaction of the tiles that hold models), at the library's tiling
         # (then again with the uniform cofactor at the same tiling: the same
         # list, element by element)

@@ -112,7 +112,9 @@ typedef struct {
 /* Uniform-cofactor evaluation: the index bits above the lane and word bits
    are constant on a tile, so clauses with a true tile literal are skipped and
    a clause made only of false tile literals ends the tile.  Same results;
-   data-dependent (usually much smaller) work. */
+   data-dependent (usually much smaller) work.  (Counts and enumerations also
+   end a tile early without it, once its clauses leave no model on the tile;
+   the test finds such tiles 64 at a time.) */
 #define FBG_TUNE_COFACTOR 1
 
 /* Compile flags: the tilings to encode.  A program is encoded once per
@@ -314,9 +316,9 @@ fbg_status fbg_batch_eval_dnf(fbg_batch *b, uint64_t *d_counts, void *stream);
  * pending.
  * fbg_batch_enumerate -- after fbg_batch_eval_dnf on the same stream: the
  *   first min(count_i, capacity_i) models of every program i, ascending,
- *   into d_idx[i] (count_i is d_counts[i] of that call).  One scan over the
- *   tile counts of all programs, then one compaction launch per plan that
- *   reads only the tiles holding models.  Allocates nothing.
+ *   into d_idx[i] (count_i is d_counts[i] of that call).  The list of
+ *   the tiles holding models of all programs, then one compaction launch per
+ *   plan that reads only these tiles.  Allocates nothing.
  */
 fbg_status fbg_batch_set_enum_outputs(fbg_batch *b, uint64_t *const *d_idx, const uint64_t *capacity);
 fbg_status fbg_batch_enumerate(fbg_batch *b, void *stream);

@@ -319,7 +319,7 @@ struct fbg_batch {
   std::vector<fbg::BatchProg> host_progs;
   std::vector<fbg::BatchProg> host_dnf;   // host copy of d_progs_dnf
   // batched enumeration (fbg_batch_set_enum_outputs): per-tile counts written
-  // by fbg_batch_eval_dnf, their scan, and the per-program output table
+  // by fbg_batch_eval_dnf, their list, and the per-program output table
   std::vector<int> plan_of;               // plan index of every program
   uint64_t total_tiles = 0;
   uint32_t *d_tile_counts = nullptr;

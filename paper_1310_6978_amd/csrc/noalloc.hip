@@ -1,6 +1,6 @@
 // noalloc.hip -- the static device scratch of the entry point that allocates
 // nothing (fbg_enumerate_noalloc): the enumeration's temporaries (per-tile
-// model counts, their exclusive scan, block sums) live in one file-scope
+// model counts, the list of tiles with models, sums of its blocks) live in one file-scope
 // device array of fixed size instead of a stream-ordered allocation.  Every
 // device the library runs on holds its own copy until the process ends.
 #include <hip/hip_runtime.h>
