@@ -295,7 +295,8 @@ typedef const __attribute__((address_space(4))) char *code_byte_ptr;
 // not (it waits for the stores, which the evaluation spreads out).  One count of
 // a 3-CNF system of 136 clauses over 35 letters: 398 us to the end of every
 // tile, 85 so, 58 with the tiles scattered over the waves (k_eval), 47 where a
-// chunk of group 0 alone does not look for keys of the other groups.
+// chunk of group 0 alone does not look for keys of the other groups, 27 where the
+// waves of k_eval hold the first key (FirstKey).
 template <int LOG2W, bool STOP>
 __device__ __forceinline__ bool run_clauses(const uint32_t *__restrict__ cb_g, const code_ptr table, uint64_t U0,
                                             uint32_t lane, uint32_t (&acc)[1 << LOG2W]) {
@@ -403,6 +404,48 @@ __device__ __forceinline__ bool run_clauses(const uint32_t *__restrict__ cb_g, c
     }
   }
   return true;
+}
+
+// The first key of the clause block where it is a run of clauses without in-word
+// and word literals (tile literals alone come first): false on every lane of a
+// tile, they leave no model there.  A wave that visits several tiles of a
+// program holds it in registers, so that such a tile costs no load (run_clauses
+// waits for the chunk's header, its lane words and the key, one after the other).
+// Lane l holds one half of the tile selector of clause l mod 32, the low one
+// below lane 32, the high one above.
+// One count of 3-CNF systems: 35 letters, 136 clauses 46.8 us, with the key held
+// 26.6; 32 letters, 60 clauses (8 tiles a wave) 37.7, 36.6; the models over 33
+// letters, 150 clauses 39.4, 34.7.  Below kFirstKeyTiles tiles a wave its own loads
+// cost what they save.  Not with a general part (posets with a special element, 8
+// tiles a wave: 26.0, with it 27.0), nor in batches, where the item's program
+// changes (16 systems of 2^32 valuations 169, 198; 256 DAGs 322, 334).
+constexpr uint32_t kFirstKeyTiles = 4;
+struct FirstKey {
+  uint32_t lb, sel, neg;     // per lane
+  uint32_t T, F, top;        // per wave
+  bool any;
+};
+
+__device__ __forceinline__ FirstKey first_key(const uint32_t *__restrict__ cb_g, uint32_t lane) {
+  FirstKey f = {0, 0, 0, 0, 0, 0, false};
+  if (((code_ptr)cb_g)[1] == 0) return f;
+  const uint32_t *ch = cb_g + FBG_CB_HDR;
+  const u32x16 hd = *(const __attribute__((address_space(4))) u32x16 *)(code_ptr)ch;
+  const uint32_t nc = hd[0], k0 = FBG_CB_CHUNK_HDR + 64 + 4 * nc;
+  const u32x2 km = *(const __attribute__((address_space(4))) u32x2 *)((code_ptr)ch + k0);
+  f.any = hd[5] > 4 * k0 && km[1] == 0u;
+  f.T = hd[2], f.F = hd[3], f.top = km[0];
+  const uint32_t *td = ch + FBG_CB_CHUNK_HDR + 64 + 4 * min(lane & (FBG_CB_CHUNK - 1u), nc - 1u) + (lane >> 5);
+  f.lb = ch[FBG_CB_CHUNK_HDR + lane];
+  f.sel = td[0], f.neg = td[2];
+  return f;
+}
+
+__device__ __forceinline__ bool first_key_false(const FirstKey &f, uint64_t U0, uint32_t lane) {
+  const uint32_t half = lane < 32u ? (uint32_t)U0 : (uint32_t)(U0 >> 32);
+  const uint64_t b = __ballot((half & f.sel) != f.neg);
+  const uint32_t A = runs_false(~(f.lb | (uint32_t)b | (uint32_t)(b >> 32)), f.T, f.F);
+  return __ballot((A >> (f.top & 31u) & 1u) == 0u) == 0ull;
 }
 
 // The uniform-cofactor test of the tiles 64 g .. 64 g + 63: a bit per tile, clear
@@ -892,6 +935,9 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_eval(EvalArgs a)
   // counting skips them, and so does the tile-count pass, whose counts the
   // host clears beforehand
   constexpr bool ALL = MODE == MODE_DNF;
+  FirstKey fk = {0, 0, 0, 0, 0, 0, false};
+  if constexpr (MODE != MODE_DNF && VAR == 0)
+    if (a.ntiles >= kFirstKeyTiles * nwaves) fk = first_key(a.code, lane);
   auto tile = [&](uint64_t t, bool alive) __attribute__((always_inline)) {
     const uint64_t U0 = t << LOG2W;
     uint32_t acc[W];
@@ -903,8 +949,10 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_eval(EvalArgs a)
       return;
     }
     if (alive) {
-      const bool live = run_program<LOG2W, (VAR & 1) != 0, MODE != MODE_DNF>(
-          a.code, a.nins, U0, lane, acc, st, regs, a.nregs * (W * 256u), nullptr, a.j16_any);
+      bool live = MODE == MODE_DNF || VAR != 0 || !fk.any || !first_key_false(fk, U0, lane);
+      if (live)
+        live = run_program<LOG2W, (VAR & 1) != 0, MODE != MODE_DNF>(
+            a.code, a.nins, U0, lane, acc, st, regs, a.nregs * (W * 256u), nullptr, a.j16_any);
       if (MODE != MODE_DNF && !live) {
         if (MODE == MODE_TILECNT && lane < (1u << a.unit_shift)) a.tile_counts[(t << a.unit_shift) + lane] = 0u;
         return;

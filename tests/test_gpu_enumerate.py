@@ -164,6 +164,34 @@ def test_tiles_that_end_early(F, wpl, general):
     lists(lambda cap, out, tot: F.enumerate_models(p, cap, out=out, total=tot), want, [c + 1])
 
 
+@pytest.mark.parametrize("first", ["tile", "low", "inword", "word", "wide"])
+@pytest.mark.parametrize("wpl", [1, 8, 32])
+def test_first_key_held_by_the_waves(F, wpl, first):
+    """Few waves, many tiles each (one block, just under and from four tiles a
+    wave on; enumerations at 2^15 tiles): clause blocks that start with a run
+    of tile literals, of lane literals, of clauses with an in-word or a word
+    literal in each, and with more clauses than a chunk holds."""
+    rng = random.Random(wpl)
+    n = 20
+    tile, lane = "x19 | x18\n~x19 | x17\n~x18 | x16 | ~x17\n", "x5 | ~x7\n~x6 | x8 | x19\n"
+    text = {"tile": tile + lane, "low": lane, "inword": "x0 | ~x19\nx1 | x7\n", "word": "x11 | x19\n~x11 | x7\n",
+            "wide": "".join("%sx%d | %sx%d | %sx%d\n" % (rng.choice(["", "~"]), a, rng.choice(["", "~"]), b,
+                                                          rng.choice(["", "~"]), c)
+                            for a, b, c in (rng.sample(range(5, n), 3) for _ in range(50)))}[first]
+    p = F.Program(text, n)
+    want = oracle.count(text, n)
+    for grid in (1, 2, F.program_tiles(p, wpl) // 16, F.program_tiles(p, wpl) // 16 + 1):
+        print("first key", wpl, first, grid, want, flush=True)
+        assert int(F.count(p, words_per_lane=wpl, grid_blocks=max(1, grid)).item()) == want
+    if wpl == 1 and first != "low":
+        n = 26  # 2^15 tiles
+        text += "x25 | x24\n~x25 | x23\nx22\n~x21\nx20 | x3\n~x4\n" + "x9 & x10 & x12 & x13 & x14\n"
+        q = F.Program(text, n)
+        q.set_tuning(1)
+        want, c = oracle.models(text, n)
+        lists(lambda cap, out, tot: F.enumerate_models(q, cap, out=out, total=tot), want, [c // 2, c + 1])
+
+
 def test_overlapping_enumerations(F):
     """More calls in flight than the scratch pool has blocks, on several
     streams and threads, and again after the last program has gone."""
