@@ -74,7 +74,7 @@ PAPER_CONTEXT = {"valuations_per_s": 2.0 ** 30, "node_bit_ops_per_s": 2.0 ** 47,
 # (their code, comments left out) the counters were taken on.  The bench line
 # reports the bytes only while the sources still have that digest, and null
 # otherwise.
-C1_TRAFFIC = {"bytes": 8603587072, "kernel_sources_sha1": "7c7b7524e7b1782f1a0c66403d7d5780d1e478cf"}
+C1_TRAFFIC = {"bytes": 8603416064, "kernel_sources_sha1": "1c63f03d7510dca5e6629331d8d2ada37d5597fd"}
 KERNEL_SOURCES = ("fbg_device.h", "fbg_asm16.h", "fbg_isa.h", "fbg_kernels.h", "batch.hip")
 
 

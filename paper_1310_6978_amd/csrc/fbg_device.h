@@ -297,7 +297,7 @@ typedef const __attribute__((address_space(4))) char *code_byte_ptr;
 // tile, 85 so, 58 with the tiles scattered over the waves (k_eval), 47 where a
 // chunk of group 0 alone does not look for keys of the other groups, 27 where the
 // waves of k_eval hold the first key (FirstKey).
-template <int LOG2W, bool STOP>
+template <int LOG2W, bool STOP, bool BATCH = false>
 __device__ __forceinline__ bool run_clauses(const uint32_t *__restrict__ cb_g, const code_ptr table, uint64_t U0,
                                             uint32_t lane, uint32_t (&acc)[1 << LOG2W]) {
   constexpr int W = 1 << LOG2W;
@@ -319,10 +319,28 @@ __device__ __forceinline__ bool run_clauses(const uint32_t *__restrict__ cb_g, c
     const code_byte_ptr hb = (code_byte_ptr)h;
     uint32_t off = (FBG_CB_CHUNK_HDR + 64 + 4 * nc) * 4;
     auto keys = [&](int g) __attribute__((always_inline)) {
-      if (!STOP) {
-        // the whole block runs: two keys to a scalar load (the write-out of 16
-        // vectors of 2^32 bits: 1331 -> 1307 us; a count that mostly stops in
-        // its first chunk loses more to the second compare than it gains)
+      if (!STOP && !BATCH) {
+        // the whole block runs: two keys to a scalar load, the second one without
+        // effect where the group ends between them (128 MiB of a 3-CNF system's
+        // vector 26.8 -> 25.7 us, 32 MiB 11.0 -> 10.9; a script with a general part
+        // 50.5 -> 48.7; a count that mostly stops in its first chunk loses more to
+        // the second compare than it gains)
+        for (; off < hd[5 + g]; off += 16) {
+          u32x4 km = *(const __attribute__((address_space(4))) u32x4 *)(hb + off);
+          km[3] = off + 8 < hd[5 + g] ? km[3] : ~0u;
+#pragma unroll
+          for (int j = 0; j < 4; j += 2) {
+            const uint32_t x = (uint32_t)__builtin_amdgcn_sbfe((int)A, km[j], 1u);
+            G[g] = __builtin_amdgcn_bitop3_b32(G[g], km[j + 1], x, kTT_KEY);
+          }
+        }
+        off = hd[5 + g];
+        return;
+      }
+      if (BATCH) {
+        // the batched write-out: pairs, then the odd key by itself.  More code,
+        // which costs a lone vector up to 2^29 bits a microsecond (2^28: 11.0, so
+        // 11.9), but 16 vectors of 2^32 bits take 1309 us and not 1330
         for (; off + 16 <= hd[5 + g]; off += 16) {
           const u32x4 km = *(const __attribute__((address_space(4))) u32x4 *)(hb + off);
 #pragma unroll
@@ -539,7 +557,7 @@ __device__ __forceinline__ uint32_t visit_group(const uint32_t *__restrict__ cod
 // before the general part whenever the clauses leave no model, since acc only
 // loses bits after them.  (Posets with a special element, 138 clauses and 41
 // instructions over 30 letters, models in 1577 of 32768 tiles: 67 us, 29 so.)
-template <int LOG2W, bool GEN, bool STOP>
+template <int LOG2W, bool GEN, bool STOP, bool BATCH = false>
 __device__ __forceinline__ bool run_program(const uint32_t *__restrict__ code_g, uint32_t nins, uint64_t U0,
                                             uint32_t lane, uint32_t (&acc)[1 << LOG2W],
                                             GenState<1 << LOG2W> &st, uint32_t *__restrict__ regs,
@@ -549,7 +567,7 @@ __device__ __forceinline__ bool run_program(const uint32_t *__restrict__ code_g,
   const code_ptr cb = (code_ptr)code_g;
   const code_ptr ins = cb + cb[0];
   const code_ptr table = ins + FBG_TABLE_OFFSET(nins, LOG2W);
-  if constexpr (!GEN) return run_clauses<LOG2W, STOP>(code_g, table, U0, lane, acc);
+  if constexpr (!GEN) return run_clauses<LOG2W, STOP, BATCH>(code_g, table, U0, lane, acc);
   // programs without clauses (most general programs) skip the block and its
   // product tree: acc starts all-ones (wave-uniform test)
   if (cb[1] + cb[2] == 0) {
@@ -1292,7 +1310,7 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, 0)) void k_batch_direct(Batch
       // the pieces x + 8 h + 16 (t & 3) + 64 (t >> 5) of the vector, h = 0, 1
       // (words 0..15 and 16..31 of each lane), x = bits 2..4 of t; full tiles
       // only (n >= 21), output 16-byte aligned
-      run_program<LOG2W, false, false>(p->xcd_code, p->nins, U0, lane, acc, st, nullptr);
+      run_program<LOG2W, false, false, true>(p->xcd_code, p->nins, U0, lane, acc, st, nullptr);
       const uint64_t piece = ((t >> 2) & 7) + 16 * (t & 3) + 64 * (t >> 5);
       store_xcd_tile(acc, p->out32 + piece * 1024 + lane * 4);
       uint32_t c0 = 0, c1 = 0;
@@ -1309,7 +1327,7 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, 0)) void k_batch_direct(Batch
       // block fill 32 contiguous bytes
       if (lane == 0) *(uint2 *)(p->chunk_counts + 2 * t) = make_uint2(c0, c1);
     } else {
-      run_program<LOG2W, false, false>(p->code, p->nins, U0, lane, acc, st, nullptr);
+      run_program<LOG2W, false, false, true>(p->code, p->nins, U0, lane, acc, st, nullptr);
       const uint32_t c = store_count_tile<LOG2W>(acc, U0, lane, p->nslices, p->n, p->out32, p->out_slices);
       const uint32_t tc = wave_sum_u32(c);
       if (lane == 0) p->tile_counts[t] = tc;
