@@ -74,7 +74,7 @@ PAPER_CONTEXT = {"valuations_per_s": 2.0 ** 30, "node_bit_ops_per_s": 2.0 ** 47,
 # (their code, comments left out) the counters were taken on.  The bench line
 # reports the bytes only while the sources still have that digest, and null
 # otherwise.
-C1_TRAFFIC = {"bytes": 8603416064, "kernel_sources_sha1": "1c63f03d7510dca5e6629331d8d2ada37d5597fd"}
+C1_TRAFFIC = {"bytes": 8603514368, "kernel_sources_sha1": "625b7ed8fd042235a4a4e45082cb9d7ade00dfd9"}
 KERNEL_SOURCES = ("fbg_device.h", "fbg_asm16.h", "fbg_isa.h", "fbg_kernels.h", "batch.hip")
 
 

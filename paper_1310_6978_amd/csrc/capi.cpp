@@ -386,6 +386,7 @@ int pick_log2w(uint64_t nslices, uint32_t nregs, bool general, int dev) {
 struct Geometry {
   int log2w, grid, block;
   size_t lds;
+  int var;  // the kernel variant (kernel_variant)
 };
 
 fbg_status block_shape(uint32_t nregs, int l, int &wpb, size_t &lds) {
@@ -420,6 +421,31 @@ int one_block_log2w(const fbg_program *p) {
   return l;
 }
 
+double expected_live(const fbg_program *p, int l);
+
+// The kernel variant of a launch over one program's tiles.  The uniform-cofactor
+// test takes 64 tiles at a time but reads its whole table for every group, and the
+// live tiles of a group come many together; the plain kernel sees an empty tile
+// by its first key.  The results are the same, so a program that asks for the
+// test is run without it where that is faster:
+//   counts below 2^20 tiles, enumerations below 2^18 (3-CNF systems of 30 letters
+//   at 4 words per lane 9.9 us and with the test 32.8, of 32 at 32 words 14.6 and
+//   51.5, of 33 and 60 clauses 50.5 and 103; equivalence relations on 9
+//   elements, 2^20 tiles of which 825 are live: 80 and 41);
+//   enumerations with more than one tile in 32 expected to live (33 letters, 60
+//   clauses, 16 words: 203 us with the test, without it below 90);
+//   vectors of programs of up to 256 clauses, whose evaluation hides behind the
+//   stores or ends early (2^30 bits at 32 words per lane 27 and 35; a script of
+//   138 clauses and a general part at 16 words 38 and 71, at 32 words 135 and 119).
+int kernel_variant(const fbg_program *p, const fbg_tune *tune, int mode, int l, uint64_t ntiles) {
+  const int var = p->variant(tune);
+  if (!(var & 2)) return var;
+  const bool plain = mode == fbg::EVAL_DNF    ? p->ncl <= 256 && !(var == 3 && l == 5)
+                     : mode == fbg::EVAL_COUNT ? ntiles < 1ull << 20
+                                               : ntiles < 1ull << 18 || expected_live(p, l) > 1.0 / 32;
+  return plain ? var & 1 : var;
+}
+
 // Launch shape of an evaluator kernel: a persistent grid of exactly the
 // blocks that can be resident at once (more would only queue behind them and
 // finish in a tail), each wave striding over the tiles.
@@ -432,14 +458,15 @@ fbg_status geometry(const fbg_program *p, const fbg_tune *tune, int mode, Geomet
   if ((st = block_shape((uint32_t)p->c.nregs, l, wpb, g.lds))) return st;
   const uint64_t ntiles = tiles_of(p->nslices, l);
   const uint64_t blocks = (ntiles + wpb - 1) / wpb;
-  const int occ = fbg::eval_blocks_per_cu(mode, l, p->variant(tune), 64 * wpb, g.lds);
+  g.var = kernel_variant(p, tune, mode, l, ntiles);
+  const int occ = fbg::eval_blocks_per_cu(mode, l, g.var, 64 * wpb, g.lds);
   uint64_t maxb = (uint64_t)cu_count(p->device) * (uint64_t)occ;
   // A DNF write-out without the cofactor runs one tile per wave on a grid of
   // fresh blocks: the blocks start in order, so the writes advance through
   // the vector together (a 2^32-bit vector at W = 32: 0.101 ms against 0.109
   // on a resident grid).  Counting keeps the resident grid, whose waves add
   // their counts once each; the cofactor filters 64 tiles per wave at once.
-  if (mode == fbg::EVAL_DNF && !(p->variant(tune) & 2)) maxb = blocks;
+  if (mode == fbg::EVAL_DNF && !(g.var & 2)) maxb = blocks;
   if (tune && tune->grid_blocks > 0) maxb = (uint64_t)tune->grid_blocks;
   g.log2w = l;
   g.block = 64 * wpb;
@@ -983,7 +1010,7 @@ fbg_status fbg_count_tuned(const fbg_program *p, uint64_t *d_count, const fbg_tu
   // (one block stores the count; more add to it)
   e = g.grid > 1 ? fbg::launch_set_u64(d_count, 0, s) : hipSuccess;
   if (e != hipSuccess) return hip_fail(e, "launch");
-  e = fbg::launch_eval(fbg::EVAL_COUNT, g.log2w, p->variant(tune), a, g.grid, g.block, g.lds, s);
+  e = fbg::launch_eval(fbg::EVAL_COUNT, g.log2w, g.var, a, g.grid, g.block, g.lds, s);
   return e == hipSuccess ? FBG_OK : hip_fail(e, "launch of the count kernel");
 }
 
@@ -1007,10 +1034,9 @@ fbg_status fbg_eval_dnf_tuned(const fbg_program *p, uint64_t *d_out, uint64_t ou
   a.out_slices = 2 * need;
   a.part_shift = cofactor_parts(a.ntiles, g);
   // the XCD-local layout (fbg_kernels.h) on the grid of one tile per wave
-  if (g.log2w == 5 && p->has_xcd && p->variant(tune) == 0 && ((uintptr_t)d_out & 15) == 0)
+  if (g.log2w == 5 && p->has_xcd && g.var == 0 && ((uintptr_t)d_out & 15) == 0)
     a.xcd_code = p->d_code + p->dev_off_xcd;
-  hipError_t e =
-      fbg::launch_eval(fbg::EVAL_DNF, g.log2w, p->variant(tune), a, g.grid, g.block, g.lds, (hipStream_t)stream);
+  hipError_t e = fbg::launch_eval(fbg::EVAL_DNF, g.log2w, g.var, a, g.grid, g.block, g.lds, (hipStream_t)stream);
   return e == hipSuccess ? FBG_OK : hip_fail(e, "launch of the DNF kernel");
 }
 
@@ -1027,7 +1053,7 @@ fbg_status fbg_enumerate(const fbg_program *p, uint64_t *d_idx, uint64_t capacit
     return fail(FBG_E_INVAL, "d_idx is NULL with capacity %llu", (unsigned long long)capacity);
   Geometry g;
   if ((st = geometry(p, nullptr, fbg::EVAL_TILECNT, g))) return st;
-  const EvalPasses pass{p, g, p->variant(nullptr), (hipStream_t)stream};
+  const EvalPasses pass{p, g, g.var, (hipStream_t)stream};
   return enumerate_with(p->device, pass.args(), d_idx, capacity, d_total, pass.s, pass);
 }
 
@@ -1040,7 +1066,7 @@ fbg_status fbg_enumerate_noalloc(const fbg_program *p, uint64_t *d_idx, uint64_t
     return fail(FBG_E_INVAL, "d_idx is NULL with capacity %llu", (unsigned long long)capacity);
   Geometry g;
   if ((st = geometry(p, nullptr, fbg::EVAL_TILECNT, g))) return st;
-  const EvalPasses pass{p, g, p->variant(nullptr), (hipStream_t)stream};
+  const EvalPasses pass{p, g, g.var, (hipStream_t)stream};
   const fbg::EvalArgs a = pass.args();
   const size_t bytes = enum_temp(a.nunits, a.direct).bytes;
   if (a.ntiles > fbg::kNoallocMaxTiles || bytes > fbg::kNoallocScratchBytes)

@@ -291,7 +291,8 @@ typedef const __attribute__((address_space(4))) char *code_byte_ptr;
 // every lane, acc is zero on the whole tile, whatever the other clauses are:
 // false is returned and acc left unset.  Clauses made only of tile literals
 // come first, then those of group 0, so a tile without models mostly ends within
-// its first chunks.  Counting uses it; the DNF write-out of clause programs does
+// its first chunks.  Counting uses it, and the write-out of one general program
+// (posets with a special element, 2^30 bits: 49 us, 38 so); that of clause programs does
 // not (it waits for the stores, which the evaluation spreads out).  One count of
 // a 3-CNF system of 136 clauses over 35 letters: 398 us to the end of every
 // tile, 85 so, 58 with the tiles scattered over the waves (k_eval), 47 where a
@@ -969,7 +970,7 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_eval(EvalArgs a)
     if (alive) {
       bool live = MODE == MODE_DNF || VAR != 0 || !fk.any || !first_key_false(fk, U0, lane);
       if (live)
-        live = run_program<LOG2W, (VAR & 1) != 0, MODE != MODE_DNF>(
+        live = run_program<LOG2W, (VAR & 1) != 0, MODE != MODE_DNF || (VAR & 1) != 0>(
             a.code, a.nins, U0, lane, acc, st, regs, a.nregs * (W * 256u), nullptr, a.j16_any);
       if (MODE != MODE_DNF && !live) {
         if (MODE == MODE_TILECNT && lane < (1u << a.unit_shift)) a.tile_counts[(t << a.unit_shift) + lane] = 0u;
