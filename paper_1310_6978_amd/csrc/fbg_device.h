@@ -44,7 +44,9 @@ namespace dev {
 enum { MODE_COUNT = 0, MODE_DNF = 1, MODE_TILECNT = 2, MODE_ENUM = 3 };
 
 __device__ __forceinline__ uint32_t uni(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
-
+__device__ __forceinline__ uint64_t uni64(uint64_t x) {
+  return uni((uint32_t)x) | (uint64_t)uni((uint32_t)(x >> 32)) << 32;
+}
 
 // Truth table of v_bitop3_b32(a, b, c): the function applied to the masks
 // a = 0xF0, b = 0xCC, c = 0xAA.  kTT_AND_OR(T, acc, P) = acc & (T | P).
@@ -831,11 +833,11 @@ __device__ __forceinline__ void for_model_units(const EvalArgs &a, uint32_t lane
     n = *a.nlist;
   }
   for (; k < n; k += step) {
-    uint32_t u = (uint32_t)k;
+    uint64_t u = k;  // (beyond 2^32 units in large programs at few words per lane)
     if (!a.direct) {
-      const uint64_t e = a.list[k];
-      u = uni((uint32_t)e);
-      at = a.list_base[u / kListBlock] + (e >> 32);
+      const uint64_t e = uni64(a.list[k]);
+      u = list_tile(e);
+      at = a.list_base[u / kListBlock] + list_before(e);
     }
     body(u, at);
   }
@@ -938,9 +940,9 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_eval(EvalArgs a)
   __shared__ uint64_t part[4];
   if (MODE == MODE_ENUM) {
     // (the cofactor variant is not needed here: these tiles hold models)
-    for_model_units(a, lane, wib, wpb, part, [&](uint32_t u, uint64_t at) __attribute__((always_inline)) {
-      const uint64_t U0 = (uint64_t)(u >> a.unit_shift) << LOG2W;
-      const uint32_t rows = W >> a.unit_shift, r0 = (u & ((1u << a.unit_shift) - 1u)) * rows;
+    for_model_units(a, lane, wib, wpb, part, [&](uint64_t u, uint64_t at) __attribute__((always_inline)) {
+      const uint64_t U0 = u >> a.unit_shift << LOG2W;
+      const uint32_t rows = W >> a.unit_shift, r0 = ((uint32_t)u & ((1u << a.unit_shift) - 1u)) * rows;
       uint32_t acc[W];
       run_program<LOG2W, (VAR & 1) != 0, false>(a.code, a.nins, U0, lane, acc, st, regs, a.nregs * (W * 256u),
                                                 nullptr, a.j16_any);
@@ -1082,9 +1084,9 @@ __global__ __launch_bounds__(256) void k_dnf_scan(EvalArgs a) {
   };
   if (MODE == MODE_ENUM) {
     __shared__ uint16_t stage[4][kStageModels];
-    for_model_units(a, lane, wib, wpb, part, [&](uint32_t u, uint64_t at) __attribute__((always_inline)) {
+    for_model_units(a, lane, wib, wpb, part, [&](uint64_t u, uint64_t at) __attribute__((always_inline)) {
       uint32_t acc[W];
-      const uint64_t U0 = (uint64_t)u << LOG2W;
+      const uint64_t U0 = u << LOG2W;
       load(U0, acc);
       if (a.direct == ENUM_ONE_BLOCK) at = one_block_position<LOG2W>(acc, a, part, lane, wib, wpb);
       tile_compact<LOG2W>(acc, 0u, W, U0, lane, at, a.out_idx, a.capacity, stage[wib]);
@@ -1390,8 +1392,8 @@ __global__ __launch_bounds__(256) void k_batch_compact(BatchEnumArgs a) {
   // one tile with models per wave and step
   const uint64_t nlist = *a.nlist;
   for (uint64_t k = wave; k < nlist; k += nwaves) {
-    const uint64_t e = a.list[k];
-    const uint64_t g = uni((uint32_t)e);
+    const uint64_t e = uni64(a.list[k]);
+    const uint64_t g = list_tile(e);
     // the program owning global tile g: tile0 ascends with the program index
     uint32_t lo = 0, hi = a.np;
     while (hi - lo > 1) {
@@ -1410,7 +1412,7 @@ __global__ __launch_bounds__(256) void k_batch_compact(BatchEnumArgs a) {
       const uint64_t sidx = (U0 + i) * 64 + lane;
       acc[i] = sidx < p->nslices ? src[i * 64] : 0u;
     }
-    const uint64_t first = a.list_base[g / kListBlock] + (e >> 32) - a.prog_base[lo];
+    const uint64_t first = a.list_base[g / kListBlock] + list_before(e) - a.prog_base[lo];
     tile_compact<LOG2W>(acc, 0u, W, U0, lane, first, p->out, p->capacity, stage[wib]);
   }
 }
@@ -1500,9 +1502,8 @@ __global__ __launch_bounds__(LIST_THREADS) void k_tile_sums_scan(TileListArgs a,
   }
 }
 
-// The list of the tiles that hold models, ascending: entry = the tile and,
-// 32 bits up, the models before it in its block of kListBlock tiles (at most
-// 2^27); list_base[block] the models before the block.  A block adds up the
+// The list of the tiles that hold models, ascending: entry = the tile and the
+// models before it in its block of kListBlock tiles (list_entry); list_base[block] the models before the block.  A block adds up the
 // sums of the blocks before it itself (SCANNED: reads their scan), so one
 // launch does what a scan of the sums, their application to every tile and
 // the listing of the tiles would; only tiles with models are written.  The
@@ -1548,7 +1549,7 @@ __global__ __launch_bounds__(LIST_THREADS) void k_tile_list(TileListArgs a) {
 #pragma unroll
   for (int k = 0; k < 8; k++) {
     if (a.np) pre[tid * 8 + k] = rel;
-    if (c[k]) a.list[at_list++] = (at + k) | (uint64_t)rel << 32;
+    if (c[k]) a.list[at_list++] = list_entry(at + k, rel);
     rel += c[k];
   }
   if (tid == 0) {

@@ -119,11 +119,20 @@ constexpr uint32_t kListBlock = 2048;
 struct TilePair {
   uint64_t models, tiles;
 };
+// An entry of the list: the tile, and the models before it in its block.  Both
+// fit one word whatever the program: 2^37 tiles at most (48 letters at one word
+// per lane), and fewer than 2^27 models before the last tile of a block.
+constexpr uint32_t kListTileBits = FBG_MAX_VARS - FBG_TILE_BASE_BIT;
+static_assert(((uint64_t)(kListBlock - 1) << (FBG_TILE_BASE_BIT + 5)) >> (64 - kListTileBits) == 0,
+              "a tile has at most 2^16 valuations");
+constexpr uint64_t list_entry(uint64_t tile, uint32_t before) { return tile | (uint64_t)before << kListTileBits; }
+constexpr uint64_t list_tile(uint64_t e) { return e & ((1ull << kListTileBits) - 1); }
+constexpr uint32_t list_before(uint64_t e) { return (uint32_t)(e >> kListTileBits); }
 struct TileListArgs {
   const uint32_t *counts;  // n tile counts, 256-byte aligned
   uint64_t n;
   TilePair *sums;       // nb: per block (temporary)
-  uint64_t *list;       // up to n entries: tile | models before it in its block << 32
+  uint64_t *list;       // up to n entries (list_entry)
   uint64_t *list_base;  // nb: models before each block
   uint64_t *nlist;      // length of the list
   uint64_t *total;      // number of models (or null)

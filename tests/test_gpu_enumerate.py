@@ -226,3 +226,35 @@ def test_overlapping_enumerations(F):
                 assert np.array_equal(m, want)
         assert (np.diff(want) > 0).all()
         p.free()
+
+
+@pytest.mark.parametrize("general", [False, True])
+def test_more_than_2_32_tiles(F, general):
+    """2^33 tiles: 44 letters at one word per lane, and a program with a general
+    part over 48 letters at its own 16.  The models lie in tiles on both sides
+    of the 2^32nd, several in a block of the list."""
+    import itertools
+
+    import torch
+    n, low = (48, 15) if general else (44, 11)      # the tile's bits are low .. n - 1
+    if torch.cuda.mem_get_info()[0] < 120 << 30:
+        pytest.skip("the temporaries take 96 GiB")
+    free = [low, low + 3, n - 1]
+    text = "".join("x%d\n" % k for k in range(low, n) if k not in free)
+    text += "".join("x%d\n" % k for k in range(3, low)) + "x0 | x2\n"
+    if general:
+        text += "(x1 ^ x%d) | (x0 & x%d)\n" % (n - 1, low)
+    p = F.Program(text, n)
+    if not general:
+        p.set_tuning(1)
+    assert F.program_tiles(p, p.info["words_per_lane"]) == 1 << 33
+    want = []
+    for top in itertools.product((0, 1), repeat=3):
+        for x in range(8):
+            if not x & 5 or (general and not ((x >> 1 & 1) ^ top[2] or (x & 1 and top[0]))):
+                continue
+            v = x | sum(1 << k for k in range(3, n) if k not in free) | sum(b << k for b, k in zip(top, free))
+            want.append(v)
+    want = np.array(sorted(want), dtype=np.uint64)
+    print("2^33 tiles", n, len(want), flush=True)
+    lists(lambda cap, out, tot: F.enumerate_models(p, cap, out=out, total=tot), want, [len(want) + 1])
