@@ -241,7 +241,7 @@ fbg_status fbg_count(const fbg_program *p, uint64_t *d_count, void *stream);
  *             models (also when it exceeds capacity).
  * The per-tile counts and the list of the tiles that hold models take a block
  * of the device's scratch pool (at most 8 blocks of 16 MiB; all but one go back
- * with the device's last program) if one is free and large enough, else
+ * once the device has no program) if one is free and large enough, else
  * temporary memory allocated on `stream` (always so under stream capture).
  * Programs of at most four tiles (n <= 18) need none.
  */

@@ -15,6 +15,7 @@
 #include "../../include/fbg.h"
 #include "fbg_internal.h"
 #include "fbg_kernels.h"
+#include "scratch_pool.h"
 
 namespace {
 
@@ -132,117 +133,6 @@ class CodeArena {
   char *cur_ = nullptr;
   size_t used_ = 0;
   std::vector<void *> free_[64];
-};
-
-// Device scratch for the temporaries of an enumeration.  hipMallocAsync and
-// hipFreeAsync cost the host 11 us a call (whatever the pool's release
-// threshold); a block kept here costs an event record and a query.  A block is
-// handed out again only once the event recorded behind its last use has
-// completed, so calls on any streams and threads may overlap, each with its own
-// block; with every block in flight, under stream capture (a graph may replay
-// at any time) or beyond kBlock bytes the caller allocates on its stream as
-// before.  At most kBlocks blocks of a device; with its last program all but one
-// go back (stream-ordered: no call waits for the device).
-class ScratchPool {
- public:
-  static constexpr size_t kBlock = (size_t)16 << 20;
-  static constexpr int kBlocks = 8;
-
-  static ScratchPool &of(int dev) {
-    static std::mutex m;
-    static std::vector<ScratchPool *> pools;
-    std::lock_guard<std::mutex> g(m);
-    if ((size_t)dev >= pools.size()) pools.resize((size_t)dev + 1, nullptr);
-    if (!pools[(size_t)dev]) pools[(size_t)dev] = new ScratchPool(dev);
-    return *pools[(size_t)dev];
-  }
-
-  explicit ScratchPool(int dev) : dev_(dev) { b_.reserve(kBlocks); }
-
-  // A block for `bytes` of work on s, a stream of the current device, or -1.
-  int acquire(size_t bytes, hipStream_t s, char **out) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (bytes > kBlock || hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return -1;
-    std::lock_guard<std::mutex> g(mu_);
-    const RelaxedCapture relaxed;
-    for (size_t i = 0; i < b_.size(); i++) {
-      const size_t k = (next_ + i) % b_.size();
-      if (b_[k].taken) continue;
-      if (b_[k].used) {
-        const hipError_t e = hipEventQuery(b_[k].done);
-        if (e == hipErrorNotReady) (void)hipGetLastError();  // not an error of the launches that follow
-        if (e != hipSuccess) continue;
-      }
-      return take(k, out);
-    }
-    if (b_.size() >= (size_t)kBlocks) return -1;
-    Block n;
-    // on s, where its first use follows; later uses follow that one's event
-    if (hipMallocAsync((void **)&n.p, kBlock, s) != hipSuccess) return -1;
-    if (hipEventCreateWithFlags(&n.done, hipEventDisableTiming) != hipSuccess) {
-      (void)hipFreeAsync(n.p, s);
-      return -1;
-    }
-    b_.push_back(n);
-    return take(b_.size() - 1, out);
-  }
-
-  // The work using block k has been put on s.
-  hipError_t release(int k, hipStream_t s) {
-    std::lock_guard<std::mutex> g(mu_);
-    Block &b = b_[(size_t)k];
-    const hipError_t e = hipEventRecord(b.done, s);
-    b.used = true;
-    if (e == hipSuccess) b.taken = false;  // else it is never handed out again
-    return e;
-  }
-
-  void program_added() {
-    std::lock_guard<std::mutex> g(mu_);
-    programs_++;
-  }
-  void program_removed() {
-    std::lock_guard<std::mutex> g(mu_);
-    if (--programs_ > 0 || b_.size() < 2) return;
-    int cur = -1;
-    if (hipGetDevice(&cur) != hipSuccess || cur != dev_) return;  // (with a later program of the device)
-    const RelaxedCapture relaxed;
-    while (b_.size() > 1) {
-      const Block &n = b_.back();
-      if (n.taken) return;  // in use by another thread; the blocks before it keep their index
-      if (n.used && hipEventQuery(n.done) != hipSuccess) {
-        (void)hipGetLastError();
-        return;
-      }
-      (void)hipEventDestroy(n.done);
-      (void)hipFreeAsync(n.p, nullptr);
-      b_.pop_back();
-    }
-  }
-
- private:
-  // A query or an allocation does not disturb another stream's capture.
-  struct RelaxedCapture {
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-  };
-  struct Block {
-    char *p = nullptr;
-    hipEvent_t done = nullptr;
-    bool taken = false, used = false;
-  };
-  int take(size_t k, char **out) {
-    b_[k].taken = true;
-    next_ = k + 1;
-    *out = b_[k].p;
-    return (int)k;
-  }
-  const int dev_;
-  std::mutex mu_;
-  std::vector<Block> b_;
-  size_t next_ = 0;
-  int64_t programs_ = 0;
 };
 
 fbg_status parse_wpl(int w, int &log2w) {
@@ -716,10 +606,13 @@ fbg_status enumerate_with(int dev, const fbg::EvalArgs &a, uint64_t *d_idx, uint
   }
   const size_t bytes = enum_temp(a.nunits, a.direct).bytes;
   char *tmp = nullptr;
-  ScratchPool &pool = ScratchPool::of(dev);
+  fbg::ScratchPool &pool = fbg::ScratchPool::of(dev);
   const int block = pool.acquire(bytes, s, &tmp);
   if (block < 0) e = hipMallocAsync((void **)&tmp, bytes, s);
-  if (e != hipSuccess) return fail(FBG_E_NOMEM, "hipMallocAsync of %zu bytes: %s", bytes, hipGetErrorString(e));
+  if (e != hipSuccess) {
+    (void)hipGetLastError();  // not an error of a later call's launches
+    return fail(FBG_E_NOMEM, "hipMallocAsync of %zu bytes: %s", bytes, hipGetErrorString(e));
+  }
   e = enumerate_passes(a, tmp, d_idx, capacity, d_total, s, pass);
   const hipError_t e2 = block < 0 ? hipFreeAsync(tmp, s) : pool.release(block, s);
   if (e != hipSuccess) return hip_fail(e, "launch of an enumeration kernel");
@@ -880,7 +773,7 @@ fbg_status compile_common(const char *src, int32_t n_vars, const int32_t *subst,
     p->auto_log2w = pick_log2w(p->nslices, (uint32_t)p->c.nregs, p->general(), -1);
   }
   p->auto_log2w = nearest_tiling(p->tilings, p->auto_log2w);
-  if (p->d_code) ScratchPool::of(p->device).program_added();
+  if (p->d_code) fbg::ScratchPool::of(p->device).program_added();
   if (p->general() && p->has_tiling(FBG_J16_LOG2W))
     p->j16_cost = fbg::j16_general_cost(p->words[FBG_J16_LOG2W], p->nins[FBG_J16_LOG2W]);
   *out = p;
@@ -944,7 +837,7 @@ void fbg_program_free(fbg_program *p) {
   if (!p) return;
   if (p->d_code) {
     CodeArena::of(p->device).release(p->d_code, p->code_class);
-    ScratchPool::of(p->device).program_removed();
+    fbg::ScratchPool::of(p->device).program_removed();
   }
   delete p;
 }

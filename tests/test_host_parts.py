@@ -24,3 +24,7 @@ def build_and_run(tmp_path, name):
 
 def test_list_entry(tmp_path):
     build_and_run(tmp_path, "list_entry")
+
+
+def test_scratch_pool(tmp_path):
+    build_and_run(tmp_path, "scratch_pool")
