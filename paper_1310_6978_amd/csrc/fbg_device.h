@@ -927,7 +927,7 @@ constexpr int min_waves(int log2w, int var) {
 template <int LOG2W, int MODE, int VAR>
 __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_eval(EvalArgs a) {
   constexpr int W = 1 << LOG2W;
-  extern __shared__ uint32_t lds[];
+  extern __shared__ __align__(16) uint32_t lds[];  // (the static words come first)
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wib = uni(threadIdx.x) >> 6;
   const uint32_t wpb = blockDim.x >> 6;
@@ -1125,7 +1125,7 @@ __global__ __launch_bounds__(256) void k_dnf_scan(EvalArgs a) {
 template <int LOG2W, int VAR, int MODE>
 __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_batch(BatchArgs a) {
   constexpr int W = 1 << LOG2W;
-  extern __shared__ uint32_t lds[];
+  extern __shared__ __align__(16) uint32_t lds[];  // (the static words come first)
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wib = uni(threadIdx.x) >> 6;
   const uint32_t wpb = blockDim.x >> 6;
