@@ -732,6 +732,9 @@ __device__ __forceinline__ void wave_lds_fence() {
   asm volatile("" ::: "memory");
 }
 
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+typedef uint64_t u64x2 __attribute__((ext_vector_type(2), aligned(8)));
+
 // The models of rows [r0, r0 + rows) of a tile, ascending, to out[base ..]
 // (below capacity).  stage: this wave's kStageModels LDS entries.
 //
@@ -745,7 +748,7 @@ __device__ __forceinline__ void wave_lds_fence() {
 // rows, 3.5 M models): 17 us, with whole tiles of 16 rows 44 us (the models
 // crowd into few tiles, 12,626 in one), the scattered stores took 94 us.
 // Giving every lane one model a step instead (a search for the word that owns
-// it) measured slower: 21 us.  Units and rows past the capacity are left out: the
+// it) measured slower: 21 us.  Units past the capacity are left out: the
 // first 10 of the 45 M models of 3 clauses over 26 letters took 68 us with all of them
 // gathered, 18 so.
 template <int LOG2W>
@@ -754,10 +757,18 @@ __device__ __forceinline__ void tile_compact(const uint32_t (&acc)[1 << LOG2W], 
                                              uint64_t capacity, uint16_t *stage) {
   const uint64_t vbase = U0 * 2048;
   uint32_t fill = 0;
+  // two models a lane and step: a wave stores 1 KiB at once
   auto flush = [&]() __attribute__((always_inline)) {
     wave_lds_fence();
-    for (uint32_t k = lane; k < fill; k += 64)
-      if (base + k < capacity) out[base + k] = vbase + stage[k];
+    const uint32_t lim = (uint32_t)min((unsigned long long)fill, capacity > base ? capacity - base : 0ull);
+    uint64_t *dst = out + base;
+    for (uint32_t k = 2 * lane; k < lim; k += 128) {
+      const u16x2 o = *(const u16x2 *)(stage + k);
+      if (k + 1 < lim)
+        *(u64x2 *)(dst + k) = u64x2{vbase + o[0], vbase + o[1]};
+      else
+        dst[k] = vbase + o[0];
+    }
     wave_lds_fence();
     base += fill;
     fill = 0;
@@ -778,10 +789,7 @@ __device__ __forceinline__ void tile_compact(const uint32_t (&acc)[1 << LOG2W], 
       before = incl - c;
       row = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
     }
-    if (fill + row > kStageModels) {
-      flush();
-      if (base >= capacity) return;  // no room for this row
-    }
+    if (fill + row > kStageModels) flush();
     uint32_t pos = fill + before;
     while (x) {
       stage[pos++] = (uint16_t)((i * 64 + lane) * 32 + (uint32_t)__builtin_ctz(x));
@@ -1089,7 +1097,7 @@ __global__ __launch_bounds__(256) void k_dnf_scan(EvalArgs a) {
     }
   };
   if (MODE == MODE_ENUM) {
-    __shared__ uint16_t stage[4][kStageModels];
+    __shared__ __align__(4) uint16_t stage[4][kStageModels];
     for_model_units(a, lane, wib, wpb, part, [&](uint64_t u, uint64_t at) __attribute__((always_inline)) {
       uint32_t acc[W];
       const uint64_t U0 = u << LOG2W;
@@ -1389,7 +1397,7 @@ __global__ __launch_bounds__(256) void k_sum_tile_counts(BatchArgs a) {
 // and compact a tile's models into its program's list.
 template <int LOG2W>
 __global__ __launch_bounds__(256) void k_batch_compact(BatchEnumArgs a) {
-  __shared__ uint16_t stage[4][kStageModels];
+  __shared__ __align__(4) uint16_t stage[4][kStageModels];
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wib = uni(threadIdx.x) >> 6;
   const uint64_t wave = (uint64_t)blockIdx.x * (blockDim.x >> 6) + wib;
