@@ -243,7 +243,8 @@ fbg_status fbg_count(const fbg_program *p, uint64_t *d_count, void *stream);
  * of the device's scratch pool (at most 8 blocks of 16 MiB; all but one go back
  * once the device has no program) if one is free and large enough, else
  * temporary memory allocated on `stream` (always so under stream capture).
- * Programs of at most four tiles (n <= 18) need none.
+ * Programs of at most four tiles need none (n <= 18, if few of the clauses are
+ * long and few models expected; n <= 13 always).
  */
 fbg_status fbg_enumerate(const fbg_program *p, uint64_t *d_idx, uint64_t capacity, uint64_t *d_total,
                          void *stream);

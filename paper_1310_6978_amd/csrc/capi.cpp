@@ -165,6 +165,7 @@ struct fbg_program {
   uint32_t ncl = 0;  // leading clause instructions
   int auto_log2w = 0;
   bool tuned = false;  // auto_log2w was set by fbg_program_set_tuning
+  int one_count = 0, one_list = 0;  // tilings of a count and an enumeration unless tuned (one_block_log2w)
   uint64_t nslices = 1;
   bool cofactor = false;  // default evaluation variant (fbg_program_set_tuning)
   bool general() const { return c.code.size() > ncl; }
@@ -298,17 +299,47 @@ fbg_status check_tiling(const fbg_program *p, int l) {
 }
 
 // The words per lane at which a small program is one tile for each wave of one
-// block, or the program's own tiling: such a count or enumeration is a single
-// launch.  Only where a tile's work does not grow with its words: clauses (to
-// n = 18), general parts to 8 words (n = 16).
-int one_block_log2w(const fbg_program *p) {
-  int l = p->auto_log2w;
-  if (p->tuned) return l;
-  for (int k = 0; k <= (p->general() ? 3 : kMaxLog2W); k++)
-    if (p->has_tiling(k) && tiles_of(p->nslices, k) <= (uint64_t)kWavesPerBlock &&
-        lds_per_wave((uint32_t)p->c.nregs, k) * kWavesPerBlock <= kMaxLdsPerBlock)
-      return k;
-  return l;
+// block, so that a count (or with `list` an enumeration) is a single launch, or
+// the program's own tiling (more, narrower tiles and two launches) where that is
+// faster: only where a tile's work hardly grows with its words.  Figures: a call in
+// one block, then with the program's own tiling.
+//  - Clauses to 32 words (n <= 18), general parts to 8 (n <= 16).
+//  - A clause with two or more word literals (multi) takes a wave 0.1 to 0.2 us, any
+//    other 0.01 us.  Counts save 3 us, unless a tile ends at its first clauses all
+//    the same: 90 clauses of 5 literals over 18 letters (39 multi) 10.8 and 8.6 us, 75
+//    of 3 literals (13) 6.6 and 8.2; 1800 of 8 literals 324 and 32; 300 of 5 literals
+//    over 15 letters (28) 12.8 and 10.9; 714 of 3 literals over 18 letters (123, but none
+//    is reached) 5.4 and 8.3.
+//  - Enumerations save 7 us and evaluate a tile once, not twice; up to 4 words they are
+//    faster whatever the clauses (1400 of 8 literals over 14 letters 30 and 54 us, all
+//    2^15 valuations 19.5 and 20.1).  Beyond, multi clauses are waited for (16 letters, 45
+//    multi: 16 and 13) and so are many models, most of them in few waves (16 letters:
+//    7,714 models 12.2 and 12.0, 32,768 24 and 13; 17: 8,848 14.3 and 12.2; 18: 1,846
+//    16.3 and 11.8, 177 9.6 and 12.2, 131,072 86 and 13.5).
+int one_block_log2w(const fbg_program *p, bool list) {
+  const int own = p->auto_log2w;
+  for (int k = 0; k <= (p->general() ? 3 : kMaxLog2W); k++) {
+    if (!p->has_tiling(k) || tiles_of(p->nslices, k) > (uint64_t)kWavesPerBlock ||
+        lds_per_wave((uint32_t)p->c.nregs, k) * kWavesPerBlock > kMaxLdsPerBlock)
+      continue;
+    uint32_t multi = 0;
+    // log2 of the valuations expected to satisfy the clauses, of all (a general part
+    // taken as true on half) and of a block's at one word by those without word literals
+    double models = p->c.n - (p->general() ? 1.0 : 0.0), first = FBG_TILE_BASE_BIT + 2;
+    for (uint32_t c = 0; c < p->ncl; c++) {
+      const auto &lits = p->c.code[c].ls.lits;
+      int word = 0;
+      for (const fbg::Lit &x : lits) word += x.k >= FBG_TILE_BASE_BIT && x.k < FBG_TILE_BASE_BIT + k;
+      const double share = std::log2(1.0 - std::ldexp(1.0, -(int)std::min<size_t>(std::max<size_t>(lits.size(), 1), 50)));
+      models += share;
+      if (word == 0) first += share;
+      multi += word >= 2;
+    }
+    const bool one = list ? k <= 2 || (multi <= 40 && models + k <= 16)
+                          : first < 0 || multi + (p->ncl - multi) / 12 <= (k == 5 ? 24u : k == 4 ? 30u : 40u);
+    return one ? k : own;
+  }
+  return own;
 }
 
 double expected_live(const fbg_program *p, int l);
@@ -340,7 +371,9 @@ int kernel_variant(const fbg_program *p, const fbg_tune *tune, int mode, int l, 
 // blocks that can be resident at once (more would only queue behind them and
 // finish in a tail), each wave striding over the tiles.
 fbg_status geometry(const fbg_program *p, const fbg_tune *tune, int mode, Geometry &g) {
-  int l = mode == fbg::EVAL_DNF ? p->auto_log2w : one_block_log2w(p);
+  int l = mode == fbg::EVAL_DNF || p->tuned ? p->auto_log2w
+          : mode == fbg::EVAL_COUNT          ? p->one_count
+                                             : p->one_list;
   fbg_status st;
   if (tune && tune->words_per_lane && (st = parse_wpl(tune->words_per_lane, l))) return st;
   if ((st = check_tiling(p, l))) return st;
@@ -773,6 +806,8 @@ fbg_status compile_common(const char *src, int32_t n_vars, const int32_t *subst,
     p->auto_log2w = pick_log2w(p->nslices, (uint32_t)p->c.nregs, p->general(), -1);
   }
   p->auto_log2w = nearest_tiling(p->tilings, p->auto_log2w);
+  p->one_count = one_block_log2w(p, false);
+  p->one_list = one_block_log2w(p, true);
   if (p->d_code) fbg::ScratchPool::of(p->device).program_added();
   if (p->general() && p->has_tiling(FBG_J16_LOG2W))
     p->j16_cost = fbg::j16_general_cost(p->words[FBG_J16_LOG2W], p->nins[FBG_J16_LOG2W]);
