@@ -298,6 +298,17 @@ fbg_status check_tiling(const fbg_program *p, int l) {
   return FBG_OK;
 }
 
+// Clauses with two or more word literals at 2^l words per lane (multi clauses).
+uint32_t multi_clauses(const fbg_program *p, int l) {
+  uint32_t multi = 0;
+  for (uint32_t c = 0; c < p->ncl; c++) {
+    int word = 0;
+    for (const fbg::Lit &x : p->c.code[c].ls.lits) word += x.k >= FBG_TILE_BASE_BIT && x.k < FBG_TILE_BASE_BIT + l;
+    multi += word >= 2;
+  }
+  return multi;
+}
+
 // The words per lane at which a small program is one tile for each wave of one
 // block, so that a count (or with `list` an enumeration) is a single launch, or
 // the program's own tiling (more, narrower tiles and two launches) where that is
@@ -322,18 +333,17 @@ int one_block_log2w(const fbg_program *p, bool list) {
     if (!p->has_tiling(k) || tiles_of(p->nslices, k) > (uint64_t)kWavesPerBlock ||
         lds_per_wave((uint32_t)p->c.nregs, k) * kWavesPerBlock > kMaxLdsPerBlock)
       continue;
-    uint32_t multi = 0;
+    const uint32_t multi = multi_clauses(p, k);
     // log2 of the valuations expected to satisfy the clauses, of all (a general part
     // taken as true on half) and of a block's at one word by those without word literals
     double models = p->c.n - (p->general() ? 1.0 : 0.0), first = FBG_TILE_BASE_BIT + 2;
     for (uint32_t c = 0; c < p->ncl; c++) {
       const auto &lits = p->c.code[c].ls.lits;
-      int word = 0;
-      for (const fbg::Lit &x : lits) word += x.k >= FBG_TILE_BASE_BIT && x.k < FBG_TILE_BASE_BIT + k;
+      bool word = false;
+      for (const fbg::Lit &x : lits) word = word || (x.k >= FBG_TILE_BASE_BIT && x.k < FBG_TILE_BASE_BIT + k);
       const double share = std::log2(1.0 - std::ldexp(1.0, -(int)std::min<size_t>(std::max<size_t>(lits.size(), 1), 50)));
       models += share;
-      if (word == 0) first += share;
-      multi += word >= 2;
+      if (!word) first += share;
     }
     const bool one = list ? k <= 2 || (multi <= 40 && models + k <= 16)
                           : first < 0 || multi + (p->ncl - multi) / 12 <= (k == 5 ? 24u : k == 4 ? 30u : 40u);
@@ -1090,7 +1100,10 @@ fbg_status fbg_batch_create(const fbg_program *const *ps, int32_t np, const fbg_
     // or more while the tiles of all programs together still give half the
     // waves of a full device one each (a tile costs little more at twice the
     // words: 16 systems of 2^24 valuations took 352 us to count at the one word
-    // per lane that suits one of them, 36 at 32 words)
+    // per lane that suits one of them, 36 at 32 words); not 32 where two clauses in
+    // five have several word literals (16 systems of 1500 clauses of 10 literals over
+    // 26 letters, 66 % of them: 1135 us at 32 words, 909 at 16; of 300 of 8 literals, 50 %:
+    // 235 and 221; of 130 of 5 literals, 20 %: 88 and 104)
     int l = fixed_l;
     if (l < 0) {
       uint64_t best = 0;
@@ -1105,13 +1118,14 @@ fbg_status fbg_batch_create(const fbg_program *const *ps, int32_t np, const fbg_
         }
       }
       for (int up = kMaxLog2W; up > l && !tuned; up--) {
-        uint64_t tiles = 0;
+        uint64_t tiles = 0, clauses = 0, multi = 0;
         bool all = true;
         for (int32_t i : members) {
           tiles += tiles_of(ps[i]->nslices, up);
           all = all && ps[i]->has_tiling(up);
+          if (up == kMaxLog2W) clauses += ps[i]->ncl, multi += multi_clauses(ps[i], up);
         }
-        if (all && tiles >= (uint64_t)cus * 16) l = up;
+        if (all && tiles >= (uint64_t)cus * 16 && 5 * multi <= 2 * clauses) l = up;
       }
     }
     uint32_t max_regs = 0;
