@@ -535,6 +535,14 @@ void cut_tiles(uint32_t prog, uint32_t slot, uint64_t b, uint64_t e, uint64_t K,
     }
 }
 
+// Blocks that give each of nitems a taker, `per` of them to a block, in every queue:
+// with 100 blocks for 400 items four queues had two takers too few, and the launch
+// took as long as two items.
+uint64_t queue_blocks(uint64_t nitems, int per) {
+  const uint64_t longest = (nitems + fbg::kQueues - 1) / fbg::kQueues;
+  return (longest + per - 1) / per * fbg::kQueues;
+}
+
 fbg::BatchProg batch_prog(const fbg_program *p, int l) {
   fbg::BatchProg b;
   memset(&b, 0, sizeof b);
@@ -1224,7 +1232,7 @@ fbg_status fbg_batch_create(const fbg_program *const *ps, int32_t np, const fbg_
     if (tune && tune->direct_run > 0) pl.direct_run = (uint32_t)tune->direct_run;
     pl.max_regs = lds_keep;
     pl.gstride = gstride;
-    const uint64_t want = cofactor ? pl.nitems : (pl.nitems + wpb - 1) / wpb;
+    const uint64_t want = queue_blocks(pl.nitems, cofactor ? 1 : wpb);
     for (int mode : {fbg::EVAL_COUNT, fbg::EVAL_DNF}) {
       uint64_t maxb = (uint64_t)cus * (uint64_t)fbg::batch_blocks_per_cu(mode, l, var, pl.block, lds);
       if (tune && tune->grid_blocks > 0) maxb = (uint64_t)tune->grid_blocks;
@@ -1686,8 +1694,8 @@ fbg_status fbg_server_launch(fbg_server *sv, const fbg_program *const *ps, int32
   a.head = (uint32_t *)sl.d;
   a.counts = d_counts;
   a.j16_any = j16_any();
-  const int64_t blocks = (var & 2) ? npieces : (npieces + wpb - 1) / wpb;
-  const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(blocks, (int64_t)cus * occ));
+  const uint64_t blocks = queue_blocks((uint64_t)npieces, (var & 2) ? 1 : wpb);
+  const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>(blocks, (uint64_t)cus * (uint64_t)occ));
   e = fbg::launch_batch(fbg::EVAL_COUNT, l, var, a, grid, 64 * wpb, lds, s);
   if (e == hipSuccess) e = hipEventRecord(sl.done, s);
   sl.used = true;

@@ -1202,11 +1202,23 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_batch(BatchArgs 
     }
   };
   // Items come sorted by cost, largest first, dealt over kQueues queues:
-  // queue q holds items q, q + kQueues, ...  A wave pops from the queue of
-  // its XCD (workgroups go to the XCDs round-robin), then from the others
+  // queue q holds items q, q + kQueues, ...  A wave works on the queue of
+  // its XCD (workgroups go to the XCDs round-robin), then on the others
   // until all are drained; a drained queue is seen by a plain read before
-  // any atomic is spent on it.
+  // any atomic is spent on it.  The first items of a queue, one for each of its
+  // XCD's waves, are theirs by number, and the pops start behind them: a wave that
+  // popped its first item and the next one ahead left others without where there is
+  // about an item a wave (200 programs of 2^12 valuations and 300 clauses: 27.4
+  // us, so 17.8).
   const uint32_t q0 = blockIdx.x % kQueues;
+  constexpr bool BLOCKS = (VAR & 2) != 0;  // a block takes an item, not a wave
+  // items of queue q taken by number
+  auto taken = [&](uint32_t q) __attribute__((always_inline)) {
+    return (gridDim.x + kQueues - 1 - q) / kQueues * (BLOCKS ? 1u : wpb);
+  };
+  auto drained = [&](uint32_t q, uint32_t popped) __attribute__((always_inline)) {
+    return q + kQueues * (taken(q) + popped) >= a.nitems;
+  };
   if constexpr ((VAR & 2) != 0) {
     // Uniform cofactor: a block pops an item for all its waves, and the next
     // one while it works on it.  The live tiles of an item come many together
@@ -1216,22 +1228,17 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_batch(BatchArgs 
     // requests, 45,500 live tiles of 494,000: 119 us, with an item per wave 250 us.
     __shared__ uint32_t popped;
     uint32_t k = 0, q = q0;
-    bool first = true;
+    uint32_t item = q + kQueues * (blockIdx.x / kQueues);
     for (;;) {
-      // lane 0 of the block pops from queue q (~0: nothing left in any)
-      auto pop = [&]() __attribute__((always_inline)) { return q + kQueues * atomicAdd(a.head + q * kQueueStride, 1u); };
-      if (first) {
-        if (threadIdx.x == 0) popped = pop();
-        first = false;
-        __syncthreads();
-      }
-      uint32_t item = uni(popped);
-      __syncthreads();
+      // thread 0 pops from queue q (an item past the end: it is drained)
+      auto pop = [&]() __attribute__((always_inline)) {
+        return drained(q, 0) ? ~0u : q + kQueues * (taken(q) + atomicAdd(a.head + q * kQueueStride, 1u));
+      };
       if (item >= a.nitems) {  // the queue is drained: on to one that is not
         if (threadIdx.x == 0) {
           while (item >= a.nitems && ++k < kQueues) {
             q = (q0 + k) % kQueues;
-            if (q + kQueues * *(volatile uint32_t *)(a.head + q * kQueueStride) < a.nitems) item = pop();
+            if (!drained(q, *(volatile uint32_t *)(a.head + q * kQueueStride))) item = pop();
           }
           popped = item;
         }
@@ -1245,23 +1252,29 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_batch(BatchArgs 
       process(item);
       if (threadIdx.x == 0) popped = next;
       __syncthreads();
+      item = uni(popped);
+      __syncthreads();
     }
   } else {
     for (uint32_t k = 0; k < kQueues; ++k) {
       const uint32_t q = (q0 + k) % kQueues;
       uint32_t *head = a.head + q * kQueueStride;
-      if (k > 0 && q + kQueues * __builtin_amdgcn_readfirstlane(*(volatile uint32_t *)head) >= a.nitems) continue;
-      uint32_t r = 0;
-      if (lane == 0) r = atomicAdd(head, 1u);
+      const uint32_t first = taken(q);
+      const bool pops = !drained(q, 0);  // the queue has more
+      if (k > 0 && (!pops || drained(q, __builtin_amdgcn_readfirstlane(*(volatile uint32_t *)head)))) continue;
+      // lane 0 holds the number in the queue
+      uint32_t r = blockIdx.x / kQueues * wpb + wib;
+      if (k > 0 && lane == 0) r = first + atomicAdd(head, 1u);
       for (;;) {
-        const uint32_t item = q + kQueues * __builtin_amdgcn_readfirstlane(r);  // lane 0 took the item
+        const uint32_t item = q + kQueues * __builtin_amdgcn_readfirstlane(r);
         if (item >= a.nitems) break;  // this queue is drained
         // a.pop_ahead: the next item is popped while this one is worked on (92
         // DAGs with n <= 28: 63 us, without 96); not where items are long, as
         // one popped early waits while other waves end (4096 DAGs: 1.3 % slower)
-        if (a.pop_ahead && lane == 0) r = atomicAdd(head, 1u);
+        if (pops && a.pop_ahead && lane == 0) r = first + atomicAdd(head, 1u);
         process(item);
-        if (!a.pop_ahead && lane == 0) r = atomicAdd(head, 1u);
+        if (!pops) break;
+        if (!a.pop_ahead && lane == 0) r = first + atomicAdd(head, 1u);
       }
     }
   }

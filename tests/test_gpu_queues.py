@@ -1,0 +1,41 @@
+"""The work queues of the batch kernels: every item is taken once, whether by
+number, popped or popped from another queue, for grids that fill the eight
+queues evenly or not, with fewer and with more items than takers."""
+
+import random
+
+import pytest
+
+import oracle
+from formula_gen import random_cnf, random_program
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def F():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a HIP device")
+    from paper_1310_6978_amd import fbg
+    return fbg
+
+
+@pytest.mark.parametrize("cofactor", [False, True])
+@pytest.mark.parametrize("np_", [1, 3, 9, 50])
+def test_every_item_once(F, np_, cofactor):
+    rng = random.Random(np_)
+    texts = []
+    for i in range(np_):
+        n = rng.choice([6, 11, 14, 17])
+        texts.append((random_cnf(rng, n, 2 * n, (2, 4)) if i % 3 else random_program(rng, n)[1], n))
+    progs = [F.Program(t, n) for t, n in texts]
+    want = [oracle.count(t, n) for t, n in texts]
+    for wpl in (1, 16):
+        for grid in (0, 1, 3, 7, 8, 9, 17, 64):
+            print("queues", np_, cofactor, wpl, grid, flush=True)
+            b = F.Batch(progs, words_per_lane=wpl, grid_blocks=grid, cofactor=cofactor)
+            for _ in range(2):
+                assert b.count().cpu().tolist() == want
+            assert b.count(graph=True).cpu().tolist() == want
+            b.free()
