@@ -352,29 +352,33 @@ int one_block_log2w(const fbg_program *p, bool list) {
   return own;
 }
 
-double expected_live(const fbg_program *p, int l);
-
-// The kernel variant of a launch over one program's tiles.  The uniform-cofactor
-// test takes 64 tiles at a time but reads its whole table for every group, and the
-// live tiles of a group come many together; the plain kernel sees an empty tile
-// by its first key.  The results are the same, so a program that asks for the
-// test is run without it where that is faster:
-//   counts below 2^20 tiles, enumerations below 2^18 (3-CNF systems of 30 letters
-//   at 4 words per lane 9.9 us and with the test 32.8, of 32 at 32 words 14.6 and
-//   51.5, of 33 and 60 clauses 50.5 and 103; equivalence relations on 9
-//   elements, 2^20 tiles of which 825 are live: 80 and 41);
-//   enumerations with more than one tile in 32 expected to live (33 letters, 60
-//   clauses, 16 words: 203 us with the test, without it below 90);
-//   vectors of programs of up to 256 clauses, whose evaluation hides behind the
-//   stores or ends early (2^30 bits at 32 words per lane 27 and 35; a script of
-//   138 clauses and a general part at 16 words 38 and 71, at 32 words 135 and 119).
+// The kernel variant of a launch over one program's tiles.  The uniform-cofactor test
+// takes a wave 64 tiles at a time; without it a tile that holds no model mostly ends at
+// its first key, so a program that asks for the test is run without it where that is
+// faster (the results are the same).  Figures: without the test, then with it.
+//  - Counts and enumerations from 2^18 tiles on: a 3-CNF system of 30 letters and 130
+//    clauses at 8 words per lane (2^16 tiles) 10.3 us and 11.5, of 32 and 130 at 8 (2^18)
+//    23.1 and 18.1, of 33 and 150 at 4 (2^20) 39.8 and 17.6; equivalence relations on 8
+//    elements at 4 (2^15) 12.1 and 13.8, on 9 at 32 (2^20) 47.1 and 30.5; with a general
+//    part, posets with a special element at 4 (2^17) 52.5 and 67.7, 34 letters and 120
+//    clauses at 32 (2^18) 99.9 and 40.0.
+//  - Of the enumerations, those where fewer than one tile in 128 is expected to live have
+//    the test in a launch of its own, after which the live tiles are dealt over the
+//    waves (equivalence relations on 9 elements at 32 words, test in the wave 53.4,
+//    so 40.7; 3-CNF systems of 36 letters and 144 clauses at 4 words, one tile in 160,
+//    135 and 124; at 16, one in 37, 71.6 and 82.5).
+//  - Vectors from 13 clauses for each word per lane on, whose evaluation the stores
+//    no longer hide (2^32 bits: 60 clauses at 4 words 143 and 93, at 8 words 85 and 101;
+//    130 at 8 132 and 103, at 16 93 and 116; 250 at 16 115 and 108, at 32 86 and 113;
+//    600 at 32 149 and 114), and all of programs with a general part at 32 words (2^30
+//    bits, 60 clauses 57.5 and 35.9), unless they are small (2^12 tiles 5.8 and 6.7).
 int kernel_variant(const fbg_program *p, const fbg_tune *tune, int mode, int l, uint64_t ntiles) {
   const int var = p->variant(tune);
   if (!(var & 2)) return var;
-  const bool plain = mode == fbg::EVAL_DNF    ? p->ncl <= 256 && !(var == 3 && l == 5)
-                     : mode == fbg::EVAL_COUNT ? ntiles < 1ull << 20
-                                               : ntiles < 1ull << 18 || expected_live(p, l) > 1.0 / 32;
-  return plain ? var & 1 : var;
+  const bool test = mode == fbg::EVAL_DNF ? ntiles >= 1ull << 13 && (p->ncl >= 13u << l || (var == 3 && l == 5))
+                                          : ntiles >= 1ull << 18;
+  if (!test) return var & 1;
+  return mode == fbg::EVAL_TILECNT && p->live[l] <= 1.0 / 128 ? var | 4 : var;
 }
 
 // Launch shape of an evaluator kernel: a persistent grid of exactly the
@@ -440,18 +444,6 @@ fbg::EvalArgs base_args(const fbg_program *p, int log2w) {
   a.ntiles = tiles_of(p->nslices, log2w);
   a.j16_any = j16_any();
   return a;
-}
-
-// log2 of the waves that share a group of 64 tiles in a uniform-cofactor
-// launch: about eight (group, part) pairs for every wave, so that the live tiles
-// of a group (up to 12 of the 64 for equivalence relations on 9 elements, 56 for
-// triangle-free graphs on 8 vertices) are not one wave's chain; every part
-// repeats the test, which costs a few clauses.
-uint32_t cofactor_parts(uint64_t ntiles, const Geometry &g) {
-  const uint64_t groups = (ntiles + 63) / 64, want = 8 * (uint64_t)g.grid * (uint64_t)(g.block / 64);
-  uint32_t s = 0;
-  while (s < 6 && (groups << (s + 1)) <= want) s++;
-  return s;
 }
 
 // Share of a program's tiles expected to pass the uniform-cofactor test at
@@ -586,11 +578,6 @@ EnumTemp enum_temp(uint64_t nu, bool direct) {
   return t;
 }
 
-// From this many tiles on, the uniform-cofactor test of an enumeration has a
-// launch of its own (launch_cofactor_masks): below it there are few enough groups
-// for several waves to repeat a group's test.
-constexpr uint64_t kMaskTiles = 1ull << 18;
-
 // Two-pass enumeration given the pass launcher and the temporaries `tmp`
 // (enum_temp(a.nunits, a.direct).bytes of device memory): counts per unit, the
 // list of the units that hold models unless direct, compaction.  Every
@@ -611,11 +598,11 @@ hipError_t enumerate_passes(fbg::EvalArgs a, char *tmp, uint64_t *d_idx, uint64_
     a.out_count = d_total;
     return pass(fbg::EVAL_ENUM, a);
   }
-  if (pass.zero_counts() && a.ntiles >= kMaskTiles && !a.direct) {
+  if (pass.masks()) {
     // the masks lie where the list comes later; a group set per 64 groups, its
     // live tiles over the waves of the device
     uint64_t *masks = (uint64_t *)(tmp + t.list);
-    e = fbg::launch_cofactor_masks(a.code, a.ntiles / 64, masks, a.tile_counts, a.unit_shift, pass.fill_grid(), s);
+    e = fbg::launch_cofactor_masks(a.code, a.ntiles / 64, masks, a.tile_counts, pass.fill_grid(), s);
     a.masks = masks;
     a.part_shift = 0;
     while (a.part_shift < 6 && (a.ntiles >> 12 << a.part_shift) < (uint64_t)pass.fill_grid() * kWavesPerBlock)
@@ -680,6 +667,7 @@ struct EvalPasses {
   Geometry g;
   int var;
   hipStream_t s;
+  bool masks() const { return (var & 4) != 0; }
   bool zero_counts() const { return (var & 2) != 0; }
   int fill_grid() const { return cu_count(p->device) * 8; }
   // Tiles are cut into units of at least four rows while there are fewer than
@@ -689,8 +677,7 @@ struct EvalPasses {
     fbg::EvalArgs a = base_args(p, g.log2w);
     while (g.log2w - (int)a.unit_shift > 2 && (a.ntiles << a.unit_shift) < 32768) a.unit_shift++;
     a.nunits = a.ntiles << a.unit_shift;
-    a.part_shift = cofactor_parts(a.ntiles, g);
-    if (a.nunits <= kDirectUnits) a.direct = fbg::ENUM_DIRECT;
+      if (a.nunits <= kDirectUnits) a.direct = fbg::ENUM_DIRECT;
     if (a.ntiles <= (uint64_t)(g.block / 64)) {
       a.direct = fbg::ENUM_ONE_BLOCK;
       a.unit_shift = 0;
@@ -718,6 +705,7 @@ struct ScanPasses {
   static constexpr bool block_sums = true;
   int dev, log2w;
   hipStream_t s;
+  bool masks() const { return false; }
   bool zero_counts() const { return false; }
   int fill_grid() const { return 1; }
   hipError_t operator()(int mode, const fbg::EvalArgs &a) const {
@@ -952,7 +940,6 @@ fbg_status fbg_count_tuned(const fbg_program *p, uint64_t *d_count, const fbg_tu
   if ((st = geometry(p, tune, fbg::EVAL_COUNT, g))) return st;
   fbg::EvalArgs a = base_args(p, g.log2w);
   a.out_count = d_count;
-  a.part_shift = cofactor_parts(a.ntiles, g);
   // (one block stores the count; more add to it)
   e = g.grid > 1 ? fbg::launch_set_u64(d_count, 0, s) : hipSuccess;
   if (e != hipSuccess) return hip_fail(e, "launch");
@@ -978,7 +965,6 @@ fbg_status fbg_eval_dnf_tuned(const fbg_program *p, uint64_t *d_out, uint64_t ou
   fbg::EvalArgs a = base_args(p, g.log2w);
   a.out32 = (uint32_t *)d_out;
   a.out_slices = 2 * need;
-  a.part_shift = cofactor_parts(a.ntiles, g);
   // the XCD-local layout (fbg_kernels.h) on the grid of one tile per wave
   if (g.log2w == 5 && p->has_xcd && g.var == 0 && ((uintptr_t)d_out & 15) == 0)
     a.xcd_code = p->d_code + p->dev_off_xcd;

@@ -1408,10 +1408,7 @@ uint32_t encode_program(const Compiled &c, int log2w, std::vector<uint32_t> &wor
   for (int within = 0; within < 2; within++)
     for (const BlockClause &b : stat) {
       if (!b.tile_only || (within != 0) != ((b.s.sel & low) != 0)) continue;
-      uint64_t tiles = 0;  // tiles of a group that satisfy it through their low bits
-      for (uint64_t t = 0; t < 64; t++)
-        if (((t << log2w) & b.s.sel) != (b.s.neg & low)) tiles |= 1ull << t;
-      for (const uint64_t v : {b.s.sel >> (log2w + 6), b.s.neg >> (log2w + 6), tiles, (uint64_t)0}) {
+      for (const uint64_t v : {b.s.sel >> log2w, b.s.neg >> log2w}) {
         block.push_back((uint32_t)v);
         block.push_back((uint32_t)(v >> 32));
       }
@@ -1419,7 +1416,7 @@ uint32_t encode_program(const Compiled &c, int log2w, std::vector<uint32_t> &wor
     }
   // up to a multiple of eight entries with clauses that hold everywhere
   for (uint32_t k = ncof; k % 8; k++)
-    for (const uint32_t v : {0u, 0u, 0u, 0u, ~0u, ~0u, 0u, 0u}) block.push_back(v);
+    for (const uint32_t v : {0u, 0u, 1u, 0u}) block.push_back(v);
   if (nstat > 0) block[FBG_CB_HDR + 4] = ncof;
   block[0] = (uint32_t)block.size();
   block[1] = nstat;
@@ -1768,8 +1765,7 @@ uint32_t clause_block_value(const uint32_t *cb, const uint32_t *table, int log2w
     for (uint32_t c = 0; c < ncof; c++, td += FBG_CB_COF_WORDS) {
       const uint64_t sel = (uint64_t)td[0] | ((uint64_t)td[1] << 32);
       const uint64_t neg = (uint64_t)td[2] | ((uint64_t)td[3] << 32);
-      const uint64_t tiles = (uint64_t)td[4] | ((uint64_t)td[5] << 32);
-      if (((t >> 6) & sel) == neg && !((tiles >> (t & 63)) & 1u)) return 0u;
+      if ((t & sel) == neg) return 0u;
     }
   }
   uint32_t extra = ~0u;  // the multi keys' factors of word i

@@ -30,6 +30,8 @@ hipError_t launch_mode(int log2w, int var, const EvalArgs &a, int grid, int bloc
   if constexpr (MODE != dev::MODE_ENUM) {  // the tiles of the compaction pass hold models: no cofactor variant
     if (var == 2) return launch_w<MODE, 2>(log2w, a, grid, block, lds, s);
     if (var == 3) return launch_w<MODE, 3>(log2w, a, grid, block, lds, s);
+    if (var == 6) return launch_w<MODE, 6>(log2w, a, grid, block, lds, s);
+    if (var == 7) return launch_w<MODE, 7>(log2w, a, grid, block, lds, s);
   }
   return hipErrorInvalidValue;
 }
@@ -61,6 +63,8 @@ int occ_mode(int log2w, int var, int block, size_t lds) {
   if constexpr (MODE != dev::MODE_ENUM) {
     if (var == 2) return occ_w<MODE, 2>(log2w, block, lds);
     if (var == 3) return occ_w<MODE, 3>(log2w, block, lds);
+    if (var == 6) return occ_w<MODE, 6>(log2w, block, lds);
+    if (var == 7) return occ_w<MODE, 7>(log2w, block, lds);
   }
   return 1;
 }

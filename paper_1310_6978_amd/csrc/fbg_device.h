@@ -14,7 +14,8 @@
 //                         MODE_TILECNT per-tile model counts (enumeration 1)
 //                         MODE_ENUM    ascending model indices (enumeration 2)
 //                         VAR bit 0 (GEN): programs with more than clauses
-//                         VAR bit 1 (COF): the uniform-cofactor variant
+//                         VAR bit 1 (COF): the uniform-cofactor variant, bit 2 (model
+//                         counts per tile): its test in a launch before (k_cofactor_masks)
 //   k_dnf_scan<MODE>      the two enumeration passes over a stored DNF vector
 //   k_batch<LOG2W, VAR, MODE>  many programs, persistent waves popping work
 //                         items (program, tiles t0 + k step) from eight
@@ -469,37 +470,40 @@ __device__ __forceinline__ bool first_key_false(const FirstKey &f, uint64_t U0, 
   return __ballot((A >> (f.top & 31u) & 1u) == 0u) == 0ull;
 }
 
-// The uniform-cofactor test of the tiles 64 g .. 64 g + 63: a bit per tile, clear
-// where a clause made only of tile literals is false, which makes the program
-// false on the whole tile (acc only loses bits after the clause block).  The
-// table at the end of the clause block (fbg_isa.h) is read as scalars and the
-// test runs on the scalar unit alone, four instructions per clause for 64
-// tiles; the clauses that do not depend on the tile within the group come first
-// and most groups end after a few of them (equivalence relations on 9 elements:
-// 9 of the 90 clauses on average).
-// STEP entries are fetched and tested between two looks at the result.
-template <uint32_t STEP>
-__device__ __forceinline__ uint64_t group_alive(const uint32_t *__restrict__ cb_g, uint64_t g) {
+// The uniform-cofactor test of 64 tiles, lane l's is t (Tile: 32 bits where they hold
+// every tile): a bit per lane, clear where a clause made only of tile literals is
+// false, which makes the program false on the whole tile (acc only loses bits after
+// the clause block), and on lanes that are not `valid`.  The table at the end of the
+// clause block (fbg_isa.h) is read as scalars: three instructions per clause, eight
+// clauses between two looks at the result, and the end as soon as no tile is left.
+template <typename Tile>
+__device__ __forceinline__ uint64_t tiles_alive(const uint32_t *__restrict__ cb_g, Tile t, uint64_t valid) {
   const code_ptr cb = (code_ptr)cb_g;
-  uint64_t alive = ~0ull;
+  uint64_t alive = valid;
   if (cb[1] == 0) return alive;
   const uint32_t k = (cb[FBG_CB_HDR + 4] + 7) / 8 * 8;
   const code_ptr td = cb + cb[0] - FBG_CB_COF_WORDS * k;
-  for (uint32_t c = 0; c < k && alive != 0ull; c += STEP) {
-    u32x16 e[STEP / 2];
+  for (uint32_t c = 0; c < k && alive != 0ull; c += 8) {
+    u32x16 e[2];
 #pragma unroll
-    for (uint32_t j = 0; j < STEP / 2; j++)
-      e[j] = *(const __attribute__((address_space(4))) u32x16 *)(td + FBG_CB_COF_WORDS * (c + 2 * j));
-#define FBG_U64(v, i) ((uint64_t)v[i] | ((uint64_t)v[(i) + 1] << 32))
-#define FBG_TEST(v, i) alive &= (g & FBG_U64(v, i)) != FBG_U64(v, (i) + 2) ? ~0ull : FBG_U64(v, (i) + 4);
+    for (uint32_t j = 0; j < 2; j++)
+      e[j] = *(const __attribute__((address_space(4))) u32x16 *)(td + FBG_CB_COF_WORDS * (c + 4 * j));
 #pragma unroll
-    for (uint32_t j = 0; j < STEP / 2; j++) {
-      FBG_TEST(e[j], 0) FBG_TEST(e[j], 8)
+    for (uint32_t j = 0; j < 8; j++) {
+      const u32x16 &v = e[j >> 2];
+      const uint32_t i = 4 * (j & 3);
+      const Tile sel = (Tile)((uint64_t)v[i] | (uint64_t)v[i + 1] << 32);
+      const Tile neg = (Tile)((uint64_t)v[i + 2] | (uint64_t)v[i + 3] << 32);
+      alive &= __ballot((t & sel) != neg);
     }
-#undef FBG_TEST
-#undef FBG_U64
   }
   return alive;
+}
+
+// The same for a program of ntiles tiles.
+__device__ __forceinline__ uint64_t tiles_alive(const uint32_t *__restrict__ cb_g, uint64_t t, uint64_t valid,
+                                                uint64_t ntiles) {
+  return ntiles <= 1ull << 32 ? tiles_alive<uint32_t>(cb_g, (uint32_t)t, valid) : tiles_alive<uint64_t>(cb_g, t, valid);
 }
 
 // A bijection of [0, n): cycle-walking over a bijection of the bits-bit
@@ -534,14 +538,14 @@ __device__ __forceinline__ uint64_t scatter_tile(uint64_t k, uint32_t bits) {
 // That many waves share the group: its surviving tiles often come many
 // together.  Returns the next running number.
 template <bool ALL, typename Body>
-__device__ __forceinline__ uint32_t visit_group(const uint32_t *__restrict__ code, uint64_t g, uint64_t t0,
-                                                uint64_t t1, uint32_t r, uint32_t part, uint32_t mask,
-                                                Body &&body) {
+__device__ __forceinline__ uint32_t visit_group(const uint32_t *__restrict__ code, uint64_t ntiles, uint32_t lane,
+                                                uint64_t g, uint64_t t0, uint64_t t1, uint32_t r, uint32_t part,
+                                                uint32_t mask, Body &&body) {
   const uint64_t first = g * 64;
   uint64_t valid = ~0ull;
   if (first < t0) valid &= ~0ull << (t0 - first);            // t0 < first + 64
   if (first + 64 > t1) valid &= ~0ull >> (first + 64 - t1);  // first < t1
-  const uint64_t alive = group_alive<4>(code, g) & valid;
+  const uint64_t alive = tiles_alive(code, first + lane, valid, ntiles);
   for (uint64_t todo = ALL ? valid : alive; todo; r++, todo &= todo - 1) {
     if ((r & mask) != part) continue;
     const uint32_t l = (uint32_t)__builtin_ctzll(todo);
@@ -1009,11 +1013,7 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_eval(EvalArgs a)
     }
   };
   if constexpr ((VAR & 2) != 0) {
-    // uniform cofactor: 2^part_shift waves to a group of 64 tiles.  The k-th
-    // (group, part) of the launch is taken at a hash of k: live groups share
-    // their low index bits, and a power-of-two stride would give them all to a
-    // few waves.
-    if (MODE == MODE_TILECNT && a.masks) {
+    if constexpr ((VAR & 4) != 0) {
       // The tests are done (k_cofactor_masks).  A wave looks at 64 groups, a mask
       // per lane, and takes every 2^part_shift-th of their live
       // tiles: mostly one tile or none.  Equivalence relations on 9 elements (825
@@ -1037,16 +1037,25 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_eval(EvalArgs a)
               tile((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)g, l) * 64 + (uint32_t)__builtin_ctzll(todo), true);
         }
       }
-      return;
-    }
-    const uint64_t n = ((a.ntiles + 63) / 64) << a.part_shift;
-    uint32_t bits = 0;
-    while ((1ull << bits) < n) bits++;
-    const uint64_t hmask = (1ull << bits) - 1;
-    const uint32_t pmask = (1u << a.part_shift) - 1u;
-    for (uint64_t k = wave; k < n; k += nwaves) {
-      const uint64_t x = tile_hash(k, n, bits, hmask);
-      visit_group<ALL>(a.code, x >> a.part_shift, 0, a.ntiles, 0u, (uint32_t)x & pmask, pmask, tile);
+    } else {
+      // 64 tiles of the wave at a time, one per lane.  The k-th tile of the launch is taken
+      // at a hash of k: live tiles share their low index bits, and a power-of-two stride
+      // would give them all to a few waves.
+      uint32_t bits = 0;
+      while ((1ull << bits) < a.ntiles) bits++;
+      const uint64_t hmask = (1ull << bits) - 1;
+      for (uint64_t k = wave; k < a.ntiles; k += nwaves * 64) {
+        const uint64_t kl = k + lane * nwaves;
+        const uint64_t valid = __ballot(kl < a.ntiles);
+        const uint64_t tl = kl < a.ntiles ? tile_hash(kl, a.ntiles, bits, hmask) : 0ull;
+        const uint64_t alive = tiles_alive(a.code, tl, valid, a.ntiles);
+        for (uint64_t todo = ALL ? valid : alive; todo; todo &= todo - 1) {
+          const uint32_t l = (uint32_t)__builtin_ctzll(todo);
+          const uint64_t t = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)tl, l) |
+                             (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(tl >> 32), l) << 32;
+          tile(t, ((alive >> l) & 1ull) != 0);
+        }
+      }
     }
   } else if constexpr (MODE != MODE_DNF) {
     // tiles that hold models share index bits too, and evaluating one takes
@@ -1196,7 +1205,7 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_batch(BatchArgs 
       const uint32_t n = wpb << (part & 0xFFu), mine = (part >> 8) * wpb + wib;
       uint32_t r = 0;
       for (uint64_t g = t0 >> 6; g * 64 < t1; g += step)
-        r = visit_group<MODE == MODE_DNF>(p->code, g, t0, t1, r, mine, n - 1u, tile);
+        r = visit_group<MODE == MODE_DNF>(p->code, p->ntiles, lane, g, t0, t1, r, mine, n - 1u, tile);
     } else {
       for (uint64_t t = t0; t < t1; t += step) tile(t, true);
     }
@@ -1453,18 +1462,18 @@ static_assert(LIST_PER_THREAD == 8, "two 16-byte loads a thread");
 
 #ifdef FBG_DEVICE_MISC_KERNELS  // defined once, in misc.hip
 
-// The uniform-cofactor test of every group of 64 tiles (ntiles a multiple of
-// 64): the live tiles' mask, and zeros for the model counts of the group's
-// units.  A wave per group and step.
+// The uniform-cofactor test of every group of 64 tiles (ngroups of them, no tiles
+// beside): the live tiles' mask, and zeros for the model counts of the group's
+// tiles.  A wave per group and step.
 __global__ __launch_bounds__(256) void k_cofactor_masks(const uint32_t *code, uint64_t ngroups, uint64_t *masks,
-                                                        uint32_t *counts, uint32_t unit_shift) {
+                                                        uint32_t *counts) {
   const uint32_t lane = threadIdx.x & 63u;
   const uint64_t wave = (uint64_t)blockIdx.x * (blockDim.x >> 6) + (uni(threadIdx.x) >> 6);
   const uint64_t nwaves = (uint64_t)gridDim.x * (blockDim.x >> 6);
   for (uint64_t g = wave; g < ngroups; g += nwaves) {
-    const uint64_t alive = group_alive<8>(code, g);
+    const uint64_t alive = tiles_alive(code, g * 64 + lane, ~0ull, ngroups * 64);
     if (lane == 0) masks[g] = alive;
-    for (uint32_t j = 0; j < (1u << unit_shift); j++) counts[((g << unit_shift) + j) * 64 + lane] = 0u;
+    counts[g * 64 + lane] = 0u;
   }
 }
 

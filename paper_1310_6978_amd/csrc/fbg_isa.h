@@ -81,16 +81,12 @@
  *     half
  *     zero padding to a multiple of 4 words
  *   then the uniform-cofactor table at the very end of the block: an entry
- *   of FBG_CB_COF_WORDS words for every clause made only of tile literals (such
- *   a clause is constant on a tile; where it is false the whole tile is).  The
- *   64 tiles 64 g .. 64 g + 63 are tested at once: the entry holds (sel lo, sel
- *   hi, neg lo, neg hi) of the clause's literals on g, the tile bits from the
- *   seventh up, then the tiles of the group (a 64-bit mask) that satisfy the
- *   clause through the six low tile bits, then two zero words.  The clause holds
- *   on the whole group when (g & sel) != neg, else on the tiles of the mask.
- *   Clauses whose mask is empty come first: one of them that is false ends the
- *   whole group.  h[4] entries, padded to a multiple of eight with entries that
- *   hold everywhere
+ *   of FBG_CB_COF_WORDS words (sel lo, sel hi, neg lo, neg hi) for every clause made
+ *   only of tile literals (such a clause is constant on a tile; where it is false
+ *   the whole tile is), here over the bits of the tile number t: the clause holds when
+ *   (t & sel) != neg.  Clauses without a literal on the six low bits come first: one
+ *   that is false ends all of 64 neighbouring tiles.  h[4] entries, padded to a
+ *   multiple of eight with entries that hold everywhere
  *
  * Instruction: 8 x uint32.
  *   w0 bits 0..3   opcode
@@ -224,7 +220,7 @@
 #define FBG_CB_HDR 4        /* words of the clause-block header */
 #define FBG_CB_CHUNK 32     /* clauses per chunk */
 #define FBG_CB_CHUNK_HDR 16 /* words of a chunk header */
-#define FBG_CB_COF_WORDS 8  /* words of a uniform-cofactor entry */
+#define FBG_CB_COF_WORDS 4  /* words of a uniform-cofactor entry */
 #define FBG_LANE_BITS 6  /* 64 lanes per wave */
 #define FBG_SLICE_BITS 5 /* 32 valuations per word */
 #define FBG_TILE_BASE_BIT (FBG_SLICE_BITS + FBG_LANE_BITS) /* 11 */

@@ -36,8 +36,10 @@ struct EvalArgs {
   uint64_t out_slices;    // MODE_DNF: words written (>= nslices, >= 2)
   const uint32_t *xcd_code;  // MODE_DNF at 32 words per lane: the XCD-local encoding, or null
   uint32_t *tile_counts;  // per unit: MODE_TILECNT (out), MODE_ENUM (in)
-  uint32_t part_shift;    // uniform cofactor: 2^part_shift waves share a group of 64 tiles
-  const uint64_t *masks;  // MODE_TILECNT with it: the groups' live tiles (launch_cofactor_masks), or null
+  // MODE_TILECNT after launch_cofactor_masks: the live tiles of the groups of 64 tiles, a
+  // mask each; 2^part_shift waves share 64 groups
+  const uint64_t *masks;
+  uint32_t part_shift;
   // Units of the enumeration passes: 2^unit_shift to a tile (fbg_device.h).
   // MODE_ENUM: with `direct` a wave takes one unit; its block finds their
   // positions from tile_counts (or block_sums), the last block writing the
@@ -194,9 +196,9 @@ int eval_blocks_per_cu(int mode, int log2w, int var, int block, size_t lds);
 int batch_blocks_per_cu(int mode, int log2w, int var, int block, size_t lds);
 hipError_t launch_batch_compact(int log2w, const BatchEnumArgs &a, int grid, int block, hipStream_t s);
 // The uniform-cofactor masks of a program's ngroups groups of 64 tiles, and
-// zeros for their units' counts (2^unit_shift per tile).
-hipError_t launch_cofactor_masks(const uint32_t *code, uint64_t ngroups, uint64_t *masks, uint32_t *counts,
-                                 uint32_t unit_shift, int grid, hipStream_t s);
+// zeros for their tiles' counts.
+hipError_t launch_cofactor_masks(const uint32_t *code, uint64_t ngroups, uint64_t *masks, uint32_t *counts, int grid,
+                                 hipStream_t s);
 hipError_t launch_tile_list(const TileListArgs &a, hipStream_t s);
 uint64_t tile_list_blocks(uint64_t n);
 // p[0..n) = 0 and head[0..nhead) = 0.

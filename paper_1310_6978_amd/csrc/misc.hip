@@ -4,6 +4,8 @@
 #define FBG_DEVICE_MISC_KERNELS
 #include "fbg_device.h"
 
+#include <algorithm>
+
 namespace fbg {
 
 hipError_t launch_eval_count(int log2w, int var, const EvalArgs &a, int grid, int block, size_t lds, hipStream_t s);
@@ -47,9 +49,9 @@ hipError_t launch_dnf_scan(int mode, int log2w, const EvalArgs &a, int grid, int
   return hipGetLastError();
 }
 
-hipError_t launch_cofactor_masks(const uint32_t *code, uint64_t ngroups, uint64_t *masks, uint32_t *counts,
-                                 uint32_t unit_shift, int grid, hipStream_t s) {
-  hipLaunchKernelGGL(dev::k_cofactor_masks, dim3(grid), dim3(256), 0, s, code, ngroups, masks, counts, unit_shift);
+hipError_t launch_cofactor_masks(const uint32_t *code, uint64_t ngroups, uint64_t *masks, uint32_t *counts, int grid,
+                                 hipStream_t s) {
+  hipLaunchKernelGGL(dev::k_cofactor_masks, dim3(grid), dim3(256), 0, s, code, ngroups, masks, counts);
   return hipGetLastError();
 }
 
@@ -70,9 +72,15 @@ hipError_t launch_tile_list(const TileListArgs &a, hipStream_t s) {
 
 hipError_t launch_zero(uint64_t *p, uint64_t n, uint32_t *head, uint32_t nhead, hipStream_t s) {
   if (!head) nhead = 0;
-  const uint64_t threads = std::max<uint64_t>(std::max<uint64_t>(n, nhead), 1);
-  const unsigned grid = (unsigned)((threads + 255) / 256);
-  hipLaunchKernelGGL(dev::k_zero_u64, dim3(grid), dim3(256), 0, s, p, n, head, nhead);
+  // (a launch has fewer than 2^32 threads)
+  constexpr uint64_t kMost = 1ull << 30;
+  do {
+    const uint64_t k = n < kMost ? n : kMost, m = std::max<uint64_t>(std::max<uint64_t>(k, nhead), 1);
+    hipLaunchKernelGGL(dev::k_zero_u64, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, p, k, head, nhead);
+    p += k;
+    n -= k;
+    nhead = 0;
+  } while (n > 0);
   return hipGetLastError();
 }
 
