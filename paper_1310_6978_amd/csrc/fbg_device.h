@@ -937,9 +937,11 @@ __device__ __forceinline__ void store_tile(const uint32_t (&acc)[1 << LOG2W], ui
 // as many as fit without spilling: programs made of clauses alone fit 8
 // (<= 64 VGPRs), the uniform-cofactor variant 7 at W = 32; the general
 // interpreter 6 at W <= 8, 4 at W = 16 (124 VGPRs: cur, acc and four
-// registers per word) and is left unconstrained above.
+// registers per word) and 2 at W = 32 (left unconstrained it takes a few registers
+// more than two waves have: posets with a special element 78 us, so 56; the batched
+// write-out would spill).
 constexpr int min_waves(int log2w, int var) {
-  return (var & 1) ? (log2w <= 3 ? 6 : (log2w == 4 ? 4 : 1)) : ((var & 2) && log2w == 5 ? 7 : 8);
+  return (var & 1) ? (log2w <= 3 ? 6 : (log2w == 4 ? 4 : 2)) : ((var & 2) && log2w == 5 ? 7 : 8);
 }
 
 template <int LOG2W, int MODE, int VAR>
@@ -1146,7 +1148,8 @@ __global__ __launch_bounds__(256) void k_dnf_scan(EvalArgs a) {
 // tables are read-only during the launch: scalar loads, so tile indices and
 // code pointers stay wave-uniform.
 template <int LOG2W, int VAR, int MODE>
-__global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_batch(BatchArgs a) {
+__global__ __launch_bounds__(256, (VAR & 1) && LOG2W == 5 && MODE == MODE_DNF ? 1 : min_waves(LOG2W, VAR)) void k_batch(
+    BatchArgs a) {
   constexpr int W = 1 << LOG2W;
   extern __shared__ __align__(16) uint32_t lds[];  // (the static words come first)
   const uint32_t lane = threadIdx.x & 63u;
