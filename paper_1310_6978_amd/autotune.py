@@ -8,7 +8,10 @@ program with clauses the uniform-cofactor test is a second dimension: it
 skips every tile on which a clause made only of tile variables is false,
 which pays where such clauses kill most tiles (the theories) and costs a
 little where they do not.  The tuner times fbg_count on the candidate
-tilings, with and without the test, with HIP events, keeps the fastest, and
+tilings with HIP events, with and without the test where the library would
+run it (a count of COFACTOR_TILES tiles or more; below, the flag makes no
+difference to a count, and a program tuned with it would put every batch that
+holds it on the kernels with the test).  It keeps the fastest and
 caches the choice per (device architecture, n, program-size bucket,
 clause-only or not) in a JSON file (FBG_TUNE_CACHE, default
 ~/.cache/fbg/tune.json).  It then makes the choice the program's default
@@ -24,6 +27,7 @@ import os
 from . import fbg
 
 CANDIDATES = (4, 8, 16, 32)
+COFACTOR_TILES = 1 << 18   # counts of fewer tiles run without the uniform-cofactor test
 
 
 def _cache_path():
@@ -42,7 +46,8 @@ def key_of(prog):
     info = prog.info
     size = max(1, int(info["n_instr"]))
     general = int(info["n_instr"]) > int(info["n_clause_instr"])
-    return "%s|n=%d|L=%d|gen=%d" % (_arch(), prog.n, int(math.log2(size)), int(general))
+    # (cof: choices made where the flag made no difference are not taken over)
+    return "%s|n=%d|L=%d|gen=%d|cof=2" % (_arch(), prog.n, int(math.log2(size)), int(general))
 
 
 class Tuner:
@@ -61,13 +66,18 @@ class Tuner:
 
     def measure(self, prog):
         """{(words_per_lane, cofactor): ms} for one count of `prog` at each
-        candidate (the cofactor only for programs with clauses)."""
+        candidate (the cofactor only for programs with clauses; where a count
+        would not run the test, the time without it)."""
         import torch
         out = torch.empty(1, dtype=torch.int64, device="cuda")
         res = {}
         cofs = (False, True) if int(prog.info["n_clause_instr"]) > 0 else (False,)
         for w in self.candidates:
             for cof in cofs:
+                if cof and fbg.program_tiles(prog, w) < COFACTOR_TILES:
+                    if (w, False) in res:
+                        res[(w, True)] = res[(w, False)]
+                    break
                 try:
                     fbg.count(prog, out=out, words_per_lane=w, cofactor=cof)  # warm-up
                 except fbg.FbgError:
@@ -92,7 +102,7 @@ class Tuner:
         cof = bool(entry.get("cofactor", False))
         if w is None:
             times = self.measure(prog)
-            w, cof = min(times, key=times.get)
+            w, cof = min(times, key=lambda k: (times[k], k[1]))   # equal times: without the cofactor
             self.table[k] = {"words_per_lane": w, "cofactor": cof,
                              "ms": {"%d%s" % (x, "c" if c else ""): t for (x, c), t in times.items()}}
             if save:

@@ -398,3 +398,38 @@ def test_run_of_four_literal_sets_is_one_chain():
     p = fbg.Program(text, 18)
     assert [op for _, op in instructions(p.disasm(16))][:4] == ["XYF", "XYM", "XYM", "XYL"]
     check(text, 18, wpl=[16])
+
+
+def test_autotuner_leaves_the_cofactor_off_where_it_makes_no_difference(tmp_path, monkeypatch):
+    """A count of few tiles runs without the test whatever the flag: jitter between two
+    runs of one kernel must not choose it (a batch would then run with the test)."""
+    import types
+
+    from paper_1310_6978_amd import autotune
+
+    clock = iter(range(1000, 0, -1))       # every measurement is faster than the one before
+
+    class Event:
+        def __init__(self, enable_timing=False):
+            pass
+
+        def record(self):
+            pass
+
+        def elapsed_time(self, other):
+            return float(next(clock))
+
+    import torch
+    monkeypatch.setattr(torch, "empty", lambda *a, **k: None)
+    monkeypatch.setattr(torch.cuda, "Event", Event)
+    monkeypatch.setattr(torch.cuda, "synchronize", lambda: None)
+    monkeypatch.setattr(autotune.fbg, "count", lambda *a, **k: None)
+    for tiles, want in ((1 << 17, False), (1 << 18, True)):
+        monkeypatch.setattr(autotune.fbg, "program_tiles", lambda p, w: tiles)
+        chosen = []
+        prog = types.SimpleNamespace(n=30, info={"n_instr": 90, "n_clause_instr": 90},
+                                     set_tuning=lambda w, cofactor: chosen.append((w, cofactor)))
+        t = autotune.Tuner(path=str(tmp_path / ("t%d.json" % tiles)))
+        t.apply(prog)
+        assert chosen == [(32, want)]
+        assert len(t.table[autotune.key_of(prog)]["ms"]) == 2 * len(autotune.CANDIDATES)
