@@ -323,8 +323,9 @@ uint32_t multi_clauses(const fbg_program *p, int l) {
 //    is reached) 5.4 and 8.3.
 //  - Enumerations save 7 us and evaluate a tile once, not twice; up to 4 words they are
 //    faster whatever the clauses (1400 of 8 literals over 14 letters 30 and 54 us, all
-//    2^15 valuations 19.5 and 20.1).  Beyond, multi clauses are waited for (16 letters, 45
-//    multi: 16 and 13) and so are many models, most of them in few waves (16 letters:
+//    2^15 valuations 19.5 and 20.1).  Beyond, multi clauses are waited for (16 letters:
+//    300 clauses of 6 literals, 91 multi, 19.5 and 22.4, 320 of 8, 160 multi, 33 and 26; 17
+//    letters: 663 of 3, 80 multi, 21 and 13) and so are many models, most of them in few waves (16 letters:
 //    7,714 models 12.2 and 12.0, 32,768 24 and 13; 17: 8,848 14.3 and 12.2; 18: 1,846
 //    16.3 and 11.8, 177 9.6 and 12.2, 131,072 86 and 13.5).
 int one_block_log2w(const fbg_program *p, bool list) {
@@ -345,8 +346,8 @@ int one_block_log2w(const fbg_program *p, bool list) {
       models += share;
       if (!word) first += share;
     }
-    const bool one = list ? k <= 2 || (multi <= 40 && models + k <= 16)
-                          : first < 0 || multi + (p->ncl - multi) / 12 <= (k == 5 ? 24u : k == 4 ? 30u : 40u);
+    const bool one = list ? k <= 2 || (multi <= (k == 3 ? 96u : 40u) && models + k <= 16)
+                          : first < 0 || multi + (p->ncl - multi) / 12 <= (k == 5 ? 24u : k == 4 ? 30u : 48u);
     return one ? k : own;
   }
   return own;
@@ -368,14 +369,16 @@ int one_block_log2w(const fbg_program *p, bool list) {
 //    so 40.7; 3-CNF systems of 36 letters and 144 clauses at 4 words, one tile in 160,
 //    135 and 124; at 16, one in 37, 71.6 and 82.5).
 //  - Vectors from 13 clauses for each word per lane on, whose evaluation the stores
-//    no longer hide (2^32 bits: 60 clauses at 4 words 143 and 93, at 8 words 85 and 101;
+//    no longer hide, from 24 with a general part (2^32 bits: 60 clauses at 4 words 143 and 93, at 8 words 85 and 101;
 //    130 at 8 132 and 103, at 16 93 and 116; 250 at 16 115 and 108, at 32 86 and 113;
-//    600 at 32 149 and 114), and all of programs with a general part at 32 words (2^30
-//    bits, 60 clauses 57.5 and 35.9), unless they are small (2^12 tiles 5.8 and 6.7).
+//    600 at 32 149 and 114; with a general part 2^28 bits and 80 clauses at 4 words 10.5
+//    and 12.6, 2^30 and 138 at 4 77 and 70), and all of programs with a general part at 32 words (2^30
+//    bits, 60 clauses 43 and 32), unless they are small (2^12 tiles 5.8 and 6.7).
 int kernel_variant(const fbg_program *p, const fbg_tune *tune, int mode, int l, uint64_t ntiles) {
   const int var = p->variant(tune);
   if (!(var & 2)) return var;
-  const bool test = mode == fbg::EVAL_DNF ? ntiles >= 1ull << 13 && (p->ncl >= 13u << l || (var == 3 && l == 5))
+  const uint32_t clauses = ((var & 1) ? 24u : 13u) << l;
+  const bool test = mode == fbg::EVAL_DNF ? ntiles >= 1ull << 13 && (p->ncl >= clauses || (var == 3 && l == 5))
                                           : ntiles >= 1ull << 18;
   if (!test) return var & 1;
   return mode == fbg::EVAL_TILECNT && p->live[l] <= 1.0 / 128 ? var | 4 : var;
