@@ -1217,7 +1217,9 @@ fbg_status fbg_batch_create(const fbg_program *const *ps, int32_t np, const fbg_
     pl.block = 64 * wpb;
     pl.lds = lds;
     pl.nitems = (uint32_t)sorted.size();
-    pl.pop_ahead = target < ((var & 1) ? 1200.0 : 7200.0);  // about 100 us
+    // popped ahead where items are short, about 100 us: one popped early waits while
+    // other waves end
+    pl.pop_ahead = (cofactor ? target / wpb : target) < ((var & 1) ? 1200.0 : 7200.0);
     if (tune && tune->direct_run > 0) pl.direct_run = (uint32_t)tune->direct_run;
     pl.max_regs = lds_keep;
     pl.gstride = gstride;
@@ -1679,7 +1681,10 @@ fbg_status fbg_server_launch(fbg_server *sv, const fbg_program *const *ps, int32
   a.items = (const fbg::BatchItem *)(sl.d + items_at);
   a.nitems = (uint32_t)npieces;
   a.max_regs = lds_regs(max_regs, l);
-  a.pop_ahead = 1;
+  // (about four items a wave, fewer than a batch's: popping ahead pays for shorter ones
+  // only; 60 systems of 300 clauses of 8 literals, 5,700 steps an item, 1216 us without it,
+  // 1373 with it)
+  a.pop_ahead = (sv->cofactor ? target / wpb : target) < 1200.0;
   a.head = (uint32_t *)sl.d;
   a.counts = d_counts;
   a.j16_any = j16_any();

@@ -360,9 +360,10 @@ __device__ __forceinline__ bool run_clauses(const uint32_t *__restrict__ cb_g, c
         G[g] = __builtin_amdgcn_bitop3_b32(G[g], km[1], x, kTT_KEY);
       }
     };
+    const bool some = off < hd[5];  // clauses without word literals (they come first)
     keys(0);
     ch += hd[1];
-    if (STOP) {
+    if (STOP && some) {
       if (__ballot(G[0] != 0u) == 0ull) return false;
       if (off >= hd[5 + NG - 1]) continue;  // a chunk of group 0 alone, as the first ones are
     }
@@ -500,10 +501,10 @@ __device__ __forceinline__ uint64_t tiles_alive(const uint32_t *__restrict__ cb_
   return alive;
 }
 
-// The same for a program of ntiles tiles.
+// The same where the valid lanes' tiles are below `end`.
 __device__ __forceinline__ uint64_t tiles_alive(const uint32_t *__restrict__ cb_g, uint64_t t, uint64_t valid,
-                                                uint64_t ntiles) {
-  return ntiles <= 1ull << 32 ? tiles_alive<uint32_t>(cb_g, (uint32_t)t, valid) : tiles_alive<uint64_t>(cb_g, t, valid);
+                                                uint64_t end) {
+  return end <= 1ull << 32 ? tiles_alive<uint32_t>(cb_g, (uint32_t)t, valid) : tiles_alive<uint64_t>(cb_g, t, valid);
 }
 
 // A bijection of [0, n): cycle-walking over a bijection of the bits-bit
@@ -538,14 +539,14 @@ __device__ __forceinline__ uint64_t scatter_tile(uint64_t k, uint32_t bits) {
 // That many waves share the group: its surviving tiles often come many
 // together.  Returns the next running number.
 template <bool ALL, typename Body>
-__device__ __forceinline__ uint32_t visit_group(const uint32_t *__restrict__ code, uint64_t ntiles, uint32_t lane,
-                                                uint64_t g, uint64_t t0, uint64_t t1, uint32_t r, uint32_t part,
-                                                uint32_t mask, Body &&body) {
+__device__ __forceinline__ uint32_t visit_group(const uint32_t *__restrict__ code, uint32_t lane, uint64_t g,
+                                                uint64_t t0, uint64_t t1, uint32_t r, uint32_t part, uint32_t mask,
+                                                Body &&body) {
   const uint64_t first = g * 64;
   uint64_t valid = ~0ull;
   if (first < t0) valid &= ~0ull << (t0 - first);            // t0 < first + 64
   if (first + 64 > t1) valid &= ~0ull >> (first + 64 - t1);  // first < t1
-  const uint64_t alive = tiles_alive(code, first + lane, valid, ntiles);
+  const uint64_t alive = tiles_alive(code, first + lane, valid, t1);
   for (uint64_t todo = ALL ? valid : alive; todo; r++, todo &= todo - 1) {
     if ((r & mask) != part) continue;
     const uint32_t l = (uint32_t)__builtin_ctzll(todo);
@@ -1208,7 +1209,7 @@ __global__ __launch_bounds__(256, (VAR & 1) && LOG2W == 5 && MODE == MODE_DNF ? 
       const uint32_t n = wpb << (part & 0xFFu), mine = (part >> 8) * wpb + wib;
       uint32_t r = 0;
       for (uint64_t g = t0 >> 6; g * 64 < t1; g += step)
-        r = visit_group<MODE == MODE_DNF>(p->code, p->ntiles, lane, g, t0, t1, r, mine, n - 1u, tile);
+        r = visit_group<MODE == MODE_DNF>(p->code, lane, g, t0, t1, r, mine, n - 1u, tile);
     } else {
       for (uint64_t t = t0; t < t1; t += step) tile(t, true);
     }
@@ -1232,8 +1233,8 @@ __global__ __launch_bounds__(256, (VAR & 1) && LOG2W == 5 && MODE == MODE_DNF ? 
     return q + kQueues * (taken(q) + popped) >= a.nitems;
   };
   if constexpr ((VAR & 2) != 0) {
-    // Uniform cofactor: a block pops an item for all its waves, and the next
-    // one while it works on it.  The live tiles of an item come many together
+    // Uniform cofactor: a block pops an item for all its waves, and with a.pop_ahead the
+    // next one while it works on it.  The live tiles of an item come many together
     // or not at all, and a wave alone took up to 44 evaluations one after the
     // other (6 us each) where it expected five; four times as many pops, 13 ns
     // each at one address, were a quarter of the launch.  A server slice of 48
@@ -1260,9 +1261,9 @@ __global__ __launch_bounds__(256, (VAR & 1) && LOG2W == 5 && MODE == MODE_DNF ? 
         if (item >= a.nitems) break;  // the same for the whole block
       }
       uint32_t next = 0;
-      if (threadIdx.x == 0) next = pop();
+      if (a.pop_ahead && threadIdx.x == 0) next = pop();
       process(item);
-      if (threadIdx.x == 0) popped = next;
+      if (threadIdx.x == 0) popped = a.pop_ahead ? next : pop();
       __syncthreads();
       item = uni(popped);
       __syncthreads();
