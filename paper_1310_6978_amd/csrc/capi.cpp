@@ -1169,16 +1169,23 @@ fbg_status fbg_batch_create(const fbg_program *const *ps, int32_t np, const fbg_
     // Items of about equal cost T, never below one tile.  Pops are atomics at
     // eight addresses, about 3 ns each over all (65,536 items: 197 us whatever
     // the work), and the queues end unevenly by about T steps of 40 to 60 ns: for
-    // the S steps of a batch the sum is least at T = sqrt(S / 16), S / T items.
-    // Large batches of general programs do better with finer items (up to 65,536,
-    // a sixteenth of a wave's share); a step of clauses is shorter (2.7 VALU
-    // instructions, 16 in the general part, and most tiles stop early), which
-    // puts T at sqrt(S / 6).  In items of S / 65,536 throughout: 92 DAGs with
-    // n <= 28 338 us, now 65; 256 DAGs 400, now 328; 1024 DAGs 945, now 926;
-    // 16 systems of 2^24 valuations 351, now 32 (with more words per lane,
-    // above), of 2^32 204, now 180.  Items of falling size, half the work first,
-    // bring more programs at a time into the scalar cache (the 1024: 1014).  With
-    // the uniform cofactor an item is a block's: about eight per block.
+    // the S steps of a batch the sum is least near T = sqrt(S / 16) with a general
+    // part, but no more than 550 (256 DAGs: T = 275 362 us, 550 318, 997 320) and no
+    // finer than a sixteenth of a wave's share (1024 DAGs: T = 986 1056 us, 2009
+    // 1098); a step of clauses is shorter (2.7 VALU instructions, 16 in the general
+    // part, and most tiles stop early), which puts T at sqrt(S / 6) (64 systems of
+    // 2^26 valuations: sqrt(S / 3) 43.5 us, so 36.9).
+    // All that holds for items that are popped.  The first ones, one for each wave of a
+    // full grid, are taken without a pop (k_batch): where T gives more than that, clause
+    // plans keep to them (16 systems of 2^28 valuations: 7,296 items of 8,192 26.9 us,
+    // 10,928 items 86; of 2^30 15,424 items 115, so 56; of 2^32 157 and 102; 40 systems
+    // of 2^14 to 2^33 219 and 176), general ones while an item is below 1,200 steps (92
+    // DAGs with n <= 28: 5,566 items 61.7, so 42; 256 DAGs, 4,030 steps, 314 and 382).
+    // Items of falling size, half the work first, bring more programs at a time into
+    // the scalar cache (the 1024: 5 % slower).  With the uniform cofactor an item is a
+    // block's: about eight per block.  A clause program has an odd number of items, if they
+    // are long enough to differ little: tiles that do not end early share low index
+    // bits (16 systems of 2^30 valuations in 512 items each 92 us, in 511 56).
     // A program's items interleave, so the waves working on neighbouring items
     // at the same time write neighbouring tiles (DNF vectors), which keeps the
     // HBM writes close together.
@@ -1187,14 +1194,33 @@ fbg_status fbg_batch_create(const fbg_program *const *ps, int32_t np, const fbg_
       target = std::max(1.0, total_cost / (double)(cus * 64));
     else if (var & 1)
       target = std::max(total_cost / (double)(cus * 256), std::min(std::sqrt(total_cost / 16.0), 550.0));
+    auto chunk_of = [&](double w, double t) { return (uint64_t)std::max(1.0, t / w); };
+    auto items_at = [&](double t) {
+      uint64_t n = 0;
+      for (int32_t i : members) {
+        const uint64_t nt = b->host_progs[(size_t)i].ntiles, chunk = chunk_of(per_tile(i), t);
+        n += (nt + chunk - 1) / chunk;
+      }
+      return n;
+    };
+    uint64_t full = (uint64_t)cus * (uint64_t)fbg::batch_blocks_per_cu(fbg::EVAL_COUNT, l, var, 64 * wpb, lds);
+    if (tune && tune->grid_blocks > 0) full = (uint64_t)tune->grid_blocks;
+    full *= (uint64_t)wpb;
+    if (!cofactor && members.size() < full && items_at(target) > full) {
+      double each = std::max(target, total_cost / (double)full);
+      while (items_at(each) > full) each *= 1.02;  // (every program has one item in the end)
+      if (!(var & 1) || each < 1200.0) target = each;
+    }
     std::vector<fbg::BatchItem> items;
     std::vector<double> cost;
     for (int32_t i : members) {
       const fbg::BatchProg &q = b->host_progs[(size_t)i];
       const double w = per_tile(i);
-      const uint64_t chunk = (uint64_t)std::max(1.0, target / w);
-      cut_tiles((uint32_t)i, (uint32_t)i, 0, q.ntiles, (q.ntiles + chunk - 1) / chunk, cofactor,
-                ps[i]->live[l], [&](const fbg::BatchItem &it, double tiles) {
+      const uint64_t chunk = chunk_of(w, target);
+      uint64_t K = (q.ntiles + chunk - 1) / chunk;
+      if (!(var & 1) && chunk >= 16 && K > 2 && !(K & 1)) K--;
+      cut_tiles((uint32_t)i, (uint32_t)i, 0, q.ntiles, K, cofactor, ps[i]->live[l],
+                [&](const fbg::BatchItem &it, double tiles) {
                   items.push_back(it);
                   cost.push_back(tiles * w);
                 });
