@@ -74,7 +74,7 @@ PAPER_CONTEXT = {"valuations_per_s": 2.0 ** 30, "node_bit_ops_per_s": 2.0 ** 47,
 # (their code, comments left out) the counters were taken on.  The bench line
 # reports the bytes only while the sources still have that digest, and null
 # otherwise.
-C1_TRAFFIC = {"bytes": 8604137472, "kernel_sources_sha1": "4b40a9932c8fd2403df5fada0f293f8d92fa7f84"}
+C1_TRAFFIC = {"bytes": 8603993984, "kernel_sources_sha1": "4ea30291106de4fe2aa359d43184fec31484f23d"}
 KERNEL_SOURCES = ("fbg_device.h", "fbg_asm16.h", "fbg_isa.h", "fbg_kernels.h", "batch.hip")
 
 
