@@ -1176,11 +1176,14 @@ fbg_status fbg_batch_create(const fbg_program *const *ps, int32_t np, const fbg_
     // part, and most tiles stop early), which puts T at sqrt(S / 6) (64 systems of
     // 2^26 valuations: sqrt(S / 3) 43.5 us, so 36.9).
     // All that holds for items that are popped.  The first ones, one for each wave of a
-    // full grid, are taken without a pop (k_batch): where T gives more than that, clause
-    // plans keep to them (16 systems of 2^28 valuations: 7,296 items of 8,192 26.9 us,
-    // 10,928 items 86; of 2^30 15,424 items 115, so 56; of 2^32 157 and 102; 40 systems
-    // of 2^14 to 2^33 219 and 176), general ones while an item is below 1,200 steps (92
-    // DAGs with n <= 28: 5,566 items 61.7, so 42; 256 DAGs, 4,030 steps, 314 and 382).
+    // full grid, are taken without a pop (k_batch): where T gives more than that, a plan
+    // keeps to them while they are short: below 5,000 steps of clauses (16 systems of 2^28
+    // valuations: 7,296 items of 8,192 26.9 us, 10,928 items 86; of 2^30, 4,500 steps,
+    // 15,424 items 115, so 56; 30 systems of 2^20 to 2^29 77 and 38), below 1,200 with a
+    // general part (92 DAGs with n <= 28: 5,566 items 61.7, so 42; 256 DAGs, 4,030 steps,
+    // 314 and 382).  Longer ones leave waves without work where programs or their tiles
+    // differ (13 theories, equivalence relations on 9 elements the largest, 35,000 steps:
+    // 207 us, so 513; 256 layerings of posets, 200,000 steps: 1545 and 4010).
     // Items of falling size, half the work first, bring more programs at a time into
     // the scalar cache (the 1024: 5 % slower).  With the uniform cofactor an item is a
     // block's: about eight per block.  A clause program has an odd number of items, if they
@@ -1209,7 +1212,7 @@ fbg_status fbg_batch_create(const fbg_program *const *ps, int32_t np, const fbg_
     if (!cofactor && members.size() < full && items_at(target) > full) {
       double each = std::max(target, total_cost / (double)full);
       while (items_at(each) > full) each *= 1.02;  // (every program has one item in the end)
-      if (!(var & 1) || each < 1200.0) target = each;
+      if (each < ((var & 1) ? 1200.0 : 5000.0)) target = each;
     }
     std::vector<fbg::BatchItem> items;
     std::vector<double> cost;
@@ -1244,8 +1247,9 @@ fbg_status fbg_batch_create(const fbg_program *const *ps, int32_t np, const fbg_
     pl.lds = lds;
     pl.nitems = (uint32_t)sorted.size();
     // popped ahead where items are short, about 100 us: one popped early waits while
-    // other waves end
-    pl.pop_ahead = (cofactor ? target / wpb : target) < ((var & 1) ? 1200.0 : 7200.0);
+    // other waves end; clauses alone always, whose many short items pops hold up most (the
+    // 13 theories 302 us, so 212; 16 systems of 2^35 valuations 646 and 545)
+    pl.pop_ahead = !(cofactor || (var & 1)) || (cofactor ? target / wpb : target) < ((var & 1) ? 1200.0 : 7200.0);
     if (tune && tune->direct_run > 0) pl.direct_run = (uint32_t)tune->direct_run;
     pl.max_regs = lds_keep;
     pl.gstride = gstride;

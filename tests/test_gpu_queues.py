@@ -39,3 +39,18 @@ def test_every_item_once(F, np_, cofactor):
                 assert b.count().cpu().tolist() == want
             assert b.count(graph=True).cpu().tolist() == want
             b.free()
+
+
+@pytest.mark.parametrize("np_,n", [(1, 20), (1, 22), (4, 18), (4, 22), (40, 17)])
+def test_clause_plans_on_both_sides_of_the_pops(F, np_, n):
+    """A grid of 8 blocks: short items, one for each wave, then long ones, popped."""
+    rng = random.Random(7 * n + np_)
+    texts = [(random_cnf(rng, n - i % 3, 4 * n, (3, 3)), n - i % 3) for i in range(np_)]
+    progs = [F.Program(t, m) for t, m in texts]
+    want = [oracle.count(t, m) for t, m in texts]
+    for wpl in (1, 4):
+        print("clause plans", np_, n, wpl, flush=True)
+        b = F.Batch(progs, words_per_lane=wpl, grid_blocks=8)
+        for _ in range(2):
+            assert b.count().cpu().tolist() == want
+        b.free()
