@@ -369,17 +369,19 @@ int one_block_log2w(const fbg_program *p, bool list) {
 //    so 40.7; 3-CNF systems of 36 letters and 144 clauses at 4 words, one tile in 160,
 //    135 and 124; at 16, one in 37, 71.6 and 82.5).
 //  - Vectors from 13 clauses for each word per lane on, whose evaluation the stores
-//    no longer hide, from 24 with a general part (2^32 bits: 60 clauses at 4 words 143 and 93, at 8 words 85 and 101;
+//    no longer hide (2^32 bits: 60 clauses at 4 words 143 and 93, at 8 words 85 and 101;
 //    130 at 8 132 and 103, at 16 93 and 116; 250 at 16 115 and 108, at 32 86 and 113;
-//    600 at 32 149 and 114; with a general part 2^28 bits and 80 clauses at 4 words 10.5
-//    and 12.6, 2^30 and 138 at 4 77 and 70), and all of programs with a general part at 32 words (2^30
-//    bits, 60 clauses 43 and 32), unless they are small (2^12 tiles 5.8 and 6.7).
+//    600 at 32 149 and 114), if they are not small (2^12 tiles 5.8 and 6.7).  With a
+//    general part from 24 clauses (2^28 bits and 80 clauses at 4 words 10.5 and 12.6, 2^30
+//    and 138 at 4 77 and 70) and 2^16 tiles (118 clauses over 27 letters at 4 words, 2^14
+//    tiles, 14.2 and 21.0, at 1, 2^16, 24.2 and 23.5); at 32 words all (2^30 bits, 60
+//    clauses 43 and 32).
 int kernel_variant(const fbg_program *p, const fbg_tune *tune, int mode, int l, uint64_t ntiles) {
   const int var = p->variant(tune);
   if (!(var & 2)) return var;
   const uint32_t clauses = ((var & 1) ? 24u : 13u) << l;
-  const bool test = mode == fbg::EVAL_DNF ? ntiles >= 1ull << 13 && (p->ncl >= clauses || (var == 3 && l == 5))
-                                          : ntiles >= 1ull << 18;
+  const uint64_t few = mode != fbg::EVAL_DNF ? 1ull << 18 : var == 3 && l < 5 ? 1ull << 16 : 1ull << 13;
+  const bool test = ntiles >= few && (mode != fbg::EVAL_DNF || p->ncl >= clauses || (var == 3 && l == 5));
   if (!test) return var & 1;
   return mode == fbg::EVAL_TILECNT && p->live[l] <= 1.0 / 128 ? var | 4 : var;
 }

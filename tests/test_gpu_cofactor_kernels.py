@@ -1,7 +1,7 @@
 """The kernels with the uniform-cofactor test, at sizes where the library runs
 them: counts and lists from 2^18 tiles on, with the test in the wave or (fewer
 than one tile in 128 expected to live) in a launch of its own, vectors from
-2^13 tiles and 13 clauses for each word per lane (24 with a general part) on.  Against the oracle where it
+2^13 tiles and 13 clauses for each word per lane (with a general part 2^16 and 24) on.  Against the oracle where it
 is quick, else against the same program without the test."""
 
 import itertools
@@ -67,14 +67,16 @@ def test_counts_and_lists(F, wpl, sparse, general):
 def test_vectors(F, wpl, general):
     rng = random.Random(wpl + 100)
     log2w = wpl.bit_length() - 1
-    n, lo = 24 + log2w, 11 + log2w          # 2^13 tiles
+    tiles = 1 << 16 if general and wpl < 32 else 1 << 13
+    lo = 11 + log2w
+    n = lo + tiles.bit_length() - 1
     need = (24 if general else 13) * wpl
     m = need + wpl                          # (a few of them may be implied and go)
     text = tile_clauses(rng, lo, n, 7, 3) + random_cnf(rng, n, m, (3 + log2w, 4 + log2w))
     if general:
         text += "(x1 ^ x9 ^ x%d) | (x4 & ~x13)\n" % (n - 1)
     p = F.Program(text, n)
-    assert p.info["n_clause_instr"] >= need and F.program_tiles(p, wpl) == 1 << 13
+    assert p.info["n_clause_instr"] >= need and F.program_tiles(p, wpl) == tiles
     got = F.eval_dnf(p, words_per_lane=wpl, cofactor=True).cpu().numpy().view(np.uint64)
     want = oracle.dnf(text, n) if n <= 26 else F.eval_dnf(p, words_per_lane=wpl).cpu().numpy().view(np.uint64)
     assert want.any() and np.array_equal(got, want)
