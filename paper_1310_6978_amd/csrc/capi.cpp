@@ -161,6 +161,7 @@ struct fbg_program {
   uint64_t dev_off_xcd = 0;
   bool has_xcd = false;
   double live[kMaxLog2W + 1] = {1, 1, 1, 1, 1, 1};  // share of tiles expected to pass the uniform-cofactor test
+  uint32_t multi[kMaxLog2W + 1] = {};               // clauses with two or more word literals (multi_clauses)
   double j16_cost = 0;  // per tile at 16 words per lane, from the jump-table form (0: none)
   uint32_t ncl = 0;  // leading clause instructions
   int auto_log2w = 0;
@@ -334,7 +335,7 @@ int one_block_log2w(const fbg_program *p, bool list) {
     if (!p->has_tiling(k) || tiles_of(p->nslices, k) > (uint64_t)kWavesPerBlock ||
         lds_per_wave((uint32_t)p->c.nregs, k) * kWavesPerBlock > kMaxLdsPerBlock)
       continue;
-    const uint32_t multi = multi_clauses(p, k);
+    const uint32_t multi = p->multi[k];
     // log2 of the valuations expected to satisfy the clauses, of all (a general part
     // taken as true on half) and of a block's at one word by those without word literals
     double models = p->c.n - (p->general() ? 1.0 : 0.0), first = FBG_TILE_BASE_BIT + 2;
@@ -765,7 +766,7 @@ fbg_status compile_common(const char *src, int32_t n_vars, const int32_t *subst,
   }
   p->nslices = slices_of(p->c.n);
   p->ncl = fbg::leading_clauses(p->c);
-  for (int l = 0; l <= kMaxLog2W; l++) p->live[l] = expected_live(p, l);
+  for (int l = 0; l <= kMaxLog2W; l++) p->live[l] = expected_live(p, l), p->multi[l] = multi_clauses(p, l);
   size_t total = 0;
   std::string enc_err;
   for (int l = 0; l <= kMaxLog2W; l++) {
@@ -1122,7 +1123,7 @@ fbg_status fbg_batch_create(const fbg_program *const *ps, int32_t np, const fbg_
         for (int32_t i : members) {
           tiles += tiles_of(ps[i]->nslices, up);
           all = all && ps[i]->has_tiling(up);
-          if (up == kMaxLog2W) clauses += ps[i]->ncl, multi += multi_clauses(ps[i], up);
+          if (up == kMaxLog2W) clauses += ps[i]->ncl, multi += ps[i]->multi[up];
         }
         if (all && tiles >= (uint64_t)cus * 16 && 5 * multi <= 2 * clauses) l = up;
       }
@@ -1249,9 +1250,13 @@ fbg_status fbg_batch_create(const fbg_program *const *ps, int32_t np, const fbg_
     pl.lds = lds;
     pl.nitems = (uint32_t)sorted.size();
     // popped ahead where items are short, about 100 us: one popped early waits while
-    // other waves end; clauses alone always, whose many short items pops hold up most (the
-    // 13 theories 302 us, so 212; 16 systems of 2^35 valuations 646 and 545)
-    pl.pop_ahead = !(cofactor || (var & 1)) || (cofactor ? target / wpb : target) < ((var & 1) ? 1200.0 : 7200.0);
+    // other waves end; of clauses alone always, whose tiles mostly end early, unless a
+    // quarter have several word literals (the 13 theories 302 us, so 212; 16 systems of
+    // 2^35 valuations 646 and 545; systems of 2 to 7 literals, 27 %, 776 and 855)
+    uint64_t clauses = 0, multi = 0;
+    for (int32_t i : members) clauses += ps[i]->ncl, multi += ps[i]->multi[l];
+    pl.pop_ahead = cofactor || (var & 1) ? (cofactor ? target / wpb : target) < ((var & 1) ? 1200.0 : 7200.0)
+                                         : 4 * multi < clauses;
     if (tune && tune->direct_run > 0) pl.direct_run = (uint32_t)tune->direct_run;
     pl.max_regs = lds_keep;
     pl.gstride = gstride;
@@ -1713,10 +1718,14 @@ fbg_status fbg_server_launch(fbg_server *sv, const fbg_program *const *ps, int32
   a.items = (const fbg::BatchItem *)(sl.d + items_at);
   a.nitems = (uint32_t)npieces;
   a.max_regs = lds_regs(max_regs, l);
-  // (about four items a wave, fewer than a batch's: popping ahead pays for shorter ones
-  // only; 60 systems of 300 clauses of 8 literals, 5,700 steps an item, 1216 us without it,
-  // 1373 with it)
-  a.pop_ahead = (sv->cofactor ? target / wpb : target) < 1200.0;
+  // (two to four items a wave, fewer than a batch's: popping ahead pays where they are
+  // short.  Without it, then with it: 30 DAGs and 13 theories, 2,300 steps an item, 210 us
+  // and 185, 60 DAGs, 3,600, 1022 and 1075; of clauses alone, as in a batch, 25 3-CNF systems,
+  // 7,400, 296 and 225, 40 of 150 clauses of 5 literals 364 and 317, 60 of 300 of 8, 36 %
+  // with several word literals, 1962 and 2134)
+  uint64_t clauses = 0, multi = 0;
+  for (int32_t i = 0; i < np; i++) clauses += ps[i]->ncl, multi += ps[i]->multi[l];
+  a.pop_ahead = sv->cofactor ? target / wpb < 1200.0 : (var & 1) ? target < 3000.0 : 4 * multi < clauses;
   a.head = (uint32_t *)sl.d;
   a.counts = d_counts;
   a.j16_any = j16_any();
