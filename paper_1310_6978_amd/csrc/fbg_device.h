@@ -342,9 +342,11 @@ __device__ __forceinline__ bool run_clauses(const uint32_t *__restrict__ cb_g, c
         return;
       }
       if (BATCH) {
-        // the batched write-out: pairs, then the odd key by itself.  More code,
-        // which costs a lone vector up to 2^29 bits a microsecond (2^28: 11.0, so
-        // 11.9), but 16 vectors of 2^32 bits take 1309 us and not 1330
+        // the batched write-out in the XCD-local layout: pairs, then the odd key by
+        // itself.  More code, which costs a lone vector up to 2^29 bits a microsecond
+        // (2^28: 11.0, so 11.9) and the batched one at fewer words per lane a tenth (16
+        // vectors of 2^32 bits at 16 words 1523 us, 1744), but the 16 at 32 words take
+        // 1282 us and not 1315
         for (; off + 16 <= hd[5 + g]; off += 16) {
           const u32x4 km = *(const __attribute__((address_space(4))) u32x4 *)(hb + off);
 #pragma unroll
@@ -1371,7 +1373,7 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, 0)) void k_batch_direct(Batch
       // block fill 32 contiguous bytes
       if (lane == 0) *(uint2 *)(p->chunk_counts + 2 * t) = make_uint2(c0, c1);
     } else {
-      run_program<LOG2W, false, false, true>(p->code, p->nins, U0, lane, acc, st, nullptr);
+      run_program<LOG2W, false, false>(p->code, p->nins, U0, lane, acc, st, nullptr);
       const uint32_t c = store_count_tile<LOG2W>(acc, U0, lane, p->nslices, p->n, p->out32, p->out_slices);
       const uint32_t tc = wave_sum_u32(c);
       if (lane == 0) p->tile_counts[t] = tc;
