@@ -1160,6 +1160,18 @@ fbg_status fbg_batch_create(const fbg_program *const *ps, int32_t np, const fbg_
       fbg_batch_free(b);
       return st;
     }
+    // Without the test where it would spare less than half of the work: an item is a wave's
+    // then, not a block's, and a tile whose clauses leave no model ends early anyhow (share
+    // spared, us with the test, without: 40 DAGs 0, 105 and 15; 92 DAGs 0.14, 181 and 43; 60
+    // larger ones 0.11, 1956 and 1685; 40 systems of 150 clauses of 5 literals 0.05, 381 and
+    // 286; 14 3-CNF systems of 2 clauses a letter 0.6, 169 and 153, at 32 words 160 and
+    // 117; 25 of 4 a letter 0.96, 127 and 332; scripts 0.98, 77 and 84).
+    double all = 0, dead = 0;
+    for (int32_t i : members) {
+      const double cost = (double)tiles_of(ps[i]->nslices, l) * tile_cost(ps[i], l);
+      all += cost, dead += cost * (1.0 - ps[i]->live[l]);
+    }
+    if (2.0 * dead < all) var &= ~2;
     const bool cofactor = (var & 2) != 0;
     auto per_tile = [&](int32_t i) { return cofactor ? cofactor_tile_cost(ps[i], l) : tile_cost(ps[i], l); };
     double total_cost = 0;
@@ -1659,7 +1671,22 @@ fbg_status fbg_server_launch(fbg_server *sv, const fbg_program *const *ps, int32
   size_t lds;
   if ((st = block_shape(max_regs, l, wpb, lds))) return st;
   const int cus = cu_count(sv->device);
-  const int occ = fbg::batch_blocks_per_cu(fbg::EVAL_COUNT, l, var, 64 * wpb, lds);
+  int occ = fbg::batch_blocks_per_cu(fbg::EVAL_COUNT, l, var & 1, 64 * wpb, lds);
+  // Without the uniform cofactor where its test would spare less than half of the work (as in
+  // a batch), items are long and the staging has room for a wave's each (60 DAGs 1164 us,
+  // so 1025, 1088 and 956; 40 small ones 90 and 94).
+  double all = 0, dead = 0;
+  for (int32_t k = 0; k < nitems; k++) {
+    const fbg_program *q = ps[items[k].prog];
+    const double cost = (double)(items[k].tile_end - items[k].tile_begin) * tile_cost(q, l);
+    all += cost, dead += cost * (1.0 - q->live[l]);
+  }
+  const int64_t waves = (int64_t)cus * occ * wpb;
+  if (2.0 * dead < all && sv->max_items - (int64_t)nitems >= 2 * waves && all >= 2400.0 * (double)waves)
+    var &= ~2;
+  else if (var & 2)
+    occ = fbg::batch_blocks_per_cu(fbg::EVAL_COUNT, l, var, 64 * wpb, lds);
+  const bool cofactor = sv->cofactor && (var & 2);
   fbg_server::Slot &sl = sv->slots[(size_t)sv->next];
   sv->next = (sv->next + 1) % sv->nbuf;
   hipError_t e;
@@ -1677,14 +1704,14 @@ fbg_status fbg_server_launch(fbg_server *sv, const fbg_program *const *ps, int32
   // the batch plans do cost more host time per slice than it saved.)
   auto per_tile = [&](int32_t i) {
     const fbg_program *q = ps[i];
-    return sv->cofactor ? cofactor_tile_cost(q, l) : tile_cost(q, l);
+    return cofactor ? cofactor_tile_cost(q, l) : tile_cost(q, l);
   };
   double total = 0;
   for (int32_t k = 0; k < nitems; k++)
     total += (double)(items[k].tile_end - items[k].tile_begin) * per_tile(items[k].prog);
-  const int64_t spare = (sv->cofactor ? sv->max_items / 2 : sv->max_items) - (int64_t)nitems;
+  const int64_t spare = (cofactor ? sv->max_items / 2 : sv->max_items) - (int64_t)nitems;
   const uint64_t room = (uint64_t)std::max<int64_t>(0, spare);
-  const uint64_t want = std::min<uint64_t>(room, (uint64_t)cus * occ * (sv->cofactor ? 1 : wpb) * 4);
+  const uint64_t want = std::min<uint64_t>(room, (uint64_t)cus * occ * (cofactor ? 1 : wpb) * 4);
   const double target = want > 0 ? total / (double)want * (1.0 + 1e-9) : 0.0;
   int32_t npieces = 0;
   bool full = false;
@@ -1692,7 +1719,7 @@ fbg_status fbg_server_launch(fbg_server *sv, const fbg_program *const *ps, int32
     const uint64_t b = items[k].tile_begin, e = items[k].tile_end;
     if (b == e) continue;
     const uint64_t chunk = want > 0 ? std::max<uint64_t>(1, (uint64_t)std::ceil(target / per_tile(items[k].prog))) : ~0ull;
-    if (!sv->cofactor) {
+    if (!cofactor) {
       for (uint64_t t = b; t < e; t += std::min(chunk, e - t)) {
         if (npieces >= sv->max_items) return fail(FBG_E_INVAL, "internal: more pieces than staging room");
         hi[npieces++] = {(uint32_t)items[k].prog, (uint32_t)items[k].slot, t, t + std::min(chunk, e - t), 1u, 0u};
@@ -1725,7 +1752,7 @@ fbg_status fbg_server_launch(fbg_server *sv, const fbg_program *const *ps, int32
   // with several word literals, 1962 and 2134)
   uint64_t clauses = 0, multi = 0;
   for (int32_t i = 0; i < np; i++) clauses += ps[i]->ncl, multi += ps[i]->multi[l];
-  a.pop_ahead = sv->cofactor ? target / wpb < 1200.0 : (var & 1) ? target < 3000.0 : 4 * multi < clauses;
+  a.pop_ahead = cofactor ? target / wpb < 1200.0 : (var & 1) ? target < 3000.0 : 4 * multi < clauses;
   a.head = (uint32_t *)sl.d;
   a.counts = d_counts;
   a.j16_any = j16_any();
