@@ -74,7 +74,7 @@ PAPER_CONTEXT = {"valuations_per_s": 2.0 ** 30, "node_bit_ops_per_s": 2.0 ** 47,
 # (their code, comments left out) the counters were taken on.  The bench line
 # reports the bytes only while the sources still have that digest, and null
 # otherwise.
-C1_TRAFFIC = {"bytes": 8603993984, "kernel_sources_sha1": "4ea30291106de4fe2aa359d43184fec31484f23d"}
+C1_TRAFFIC = {"bytes": 8603613056, "kernel_sources_sha1": "5a12a1aba681f7bd8b4b1b1f22a0f13919ab48c3"}
 KERNEL_SOURCES = ("fbg_device.h", "fbg_asm16.h", "fbg_isa.h", "fbg_kernels.h", "batch.hip")
 
 

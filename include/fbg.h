@@ -106,7 +106,8 @@ typedef struct {
   int32_t direct_run;      /* fbg_batch_eval_dnf of clause-only programs (one
                               wave per run of tiles on fresh blocks): tiles
                               per run, 1..64; 0: the library's choice (1 when
-                              a program takes the XCD-local layout, else 4) */
+                              a program takes the XCD-local layout, else 4,
+                              fewer where there are few tiles) */
 } fbg_tune;
 
 /* Uniform-cofactor evaluation: the index bits above the lane and word bits
@@ -114,7 +115,11 @@ typedef struct {
    a clause made only of false tile literals ends the tile.  Same results;
    data-dependent (usually much smaller) work.  (Counts and enumerations also
    end a tile early without it, once its clauses leave no model on the tile;
-   the test finds such tiles 64 at a time.) */
+   the test finds such tiles 64 at a time.)  A call over one program that asks
+   for it is run without it where the library knows that to be faster: counts
+   and enumerations of few tiles, vectors of few clauses.  So are
+   batches, and slices of a server, of programs that the test would spare
+   less than half of the work. */
 #define FBG_TUNE_COFACTOR 1
 
 /* Compile flags: the tilings to encode.  A program is encoded once per
@@ -203,10 +208,11 @@ fbg_status fbg_program_info(const fbg_program *p, struct fbg_program_info *out);
 fbg_status fbg_program_get_info(const fbg_program *p, struct fbg_program_info *out);
 
 /* Make tune->words_per_lane (non-zero) the program's default tiling, and
-   tune->flags (FBG_TUNE_COFACTOR) its default evaluation variant, for
-   fbg_count, fbg_eval_dnf, fbg_enumerate and new batches (the autotuner's
-   hook).  FBG_E_RANGE if the program's registers do not fit in LDS at that
-   tiling.  Not synchronised with launches in flight on other threads. */
+   tune->flags (FBG_TUNE_COFACTOR, set aside where it is slower, above) its
+   default evaluation variant, for fbg_count, fbg_eval_dnf, fbg_enumerate and
+   new batches (the autotuner's hook).  FBG_E_RANGE if the program's registers
+   do not fit in LDS at that tiling.  Not synchronised with launches in flight
+   on other threads. */
 fbg_status fbg_program_set_tuning(fbg_program *p, const fbg_tune *tune);
 
 /*

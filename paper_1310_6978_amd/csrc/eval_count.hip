@@ -1,4 +1,4 @@
-// eval_count.hip -- the single-program evaluator kernels of counting (popcount, wave sum, one atomic per wave):
+// eval_count.hip -- the single-program evaluator kernels of counting (popcount, block sum, one atomic per block):
 // k_eval<W, MODE_COUNT, VAR> for every tiling and variant, their launches and
 // occupancy queries.
 #include "fbg_device.h"

@@ -300,7 +300,8 @@ typedef const __attribute__((address_space(4))) char *code_byte_ptr;
 // a 3-CNF system of 136 clauses over 35 letters: 398 us to the end of every
 // tile, 85 so, 58 with the tiles scattered over the waves (k_eval), 47 where a
 // chunk of group 0 alone does not look for keys of the other groups, 27 where the
-// waves of k_eval hold the first key (FirstKey).
+// waves of k_eval hold the first key (FirstKey; 32 to 42 with the host's part of a
+// call, over several GPUs).
 template <int LOG2W, bool STOP, bool BATCH = false>
 __device__ __forceinline__ bool run_clauses(const uint32_t *__restrict__ cb_g, const code_ptr table, uint64_t U0,
                                             uint32_t lane, uint32_t (&acc)[1 << LOG2W]) {
@@ -439,8 +440,8 @@ __device__ __forceinline__ bool run_clauses(const uint32_t *__restrict__ cb_g, c
 // waits for the chunk's header, its lane words and the key, one after the other).
 // Lane l holds one half of the tile selector of clause l mod 32, the low one
 // below lane 32, the high one above.
-// One count of 3-CNF systems: 35 letters, 136 clauses 46.8 us, with the key held
-// 26.6; 32 letters, 60 clauses (8 tiles a wave) 37.7, 36.6; the models over 33
+// One count of 3-CNF systems (the launch alone): 35 letters, 136 clauses 46.8 us, with
+// the key held 26.6; 32 letters, 60 clauses (8 tiles a wave) 37.7, 36.6; the models over 33
 // letters, 150 clauses 39.4, 34.7.  Below kFirstKeyTiles tiles a wave its own loads
 // cost what they save.  Not with a general part (posets with a special element, 8
 // tiles a wave: 26.0, with it 27.0), nor in batches, where the item's program
@@ -1023,8 +1024,8 @@ __global__ __launch_bounds__(256, min_waves(LOG2W, VAR)) void k_eval(EvalArgs a)
       // The tests are done (k_cofactor_masks).  A wave looks at 64 groups, a mask
       // per lane, and takes every 2^part_shift-th of their live
       // tiles: mostly one tile or none.  Equivalence relations on 9 elements (825
-      // live tiles of 2^20, up to 12 in a group): 12 us and 11, 40 with the test in
-      // the wave, whose three evaluations in a row took 9 us each.
+      // live tiles of 2^20, up to 12 in a group): the enumeration 40.7 us, with the test
+      // in the wave, whose three evaluations in a row took 9 us each, 53.4.
       // (2^18 <= ntiles <= 2^38, a power of two)
       const uint32_t nsets = (uint32_t)(a.ntiles >> 12), sets = 31u - (uint32_t)__builtin_clz(nsets);
       const uint32_t pm = (1u << a.part_shift) - 1u;
@@ -1241,7 +1242,8 @@ __global__ __launch_bounds__(256, (VAR & 1) && LOG2W == 5 && MODE == MODE_DNF ? 
     // or not at all, and a wave alone took up to 44 evaluations one after the
     // other (6 us each) where it expected five; four times as many pops, 13 ns
     // each at one address, were a quarter of the launch.  A server slice of 48
-    // requests, 45,500 live tiles of 494,000: 119 us, with an item per wave 250 us.
+    // requests, 45,500 live tiles of 494,000: 119 us, with an item per wave 250 us (on
+    // one GPU; 109 to 139 over several now).
     __shared__ uint32_t popped;
     uint32_t k = 0, q = q0;
     uint32_t item = q + kQueues * (blockIdx.x / kQueues);
@@ -1471,7 +1473,9 @@ static_assert(LIST_PER_THREAD == 8, "two 16-byte loads a thread");
 
 // The uniform-cofactor test of every group of 64 tiles (ngroups of them, no tiles
 // beside): the live tiles' mask, and zeros for the model counts of the group's
-// tiles.  A wave per group and step.
+// tiles.  A wave per group and step: two for each wave where there are 2^20 tiles,
+// which wait for the scalar loads of the table (90 clauses 7 to 9 us; with a test of 64
+// tiles on the scalar unit, eight words a clause, 12).
 __global__ __launch_bounds__(256) void k_cofactor_masks(const uint32_t *code, uint64_t ngroups, uint64_t *masks,
                                                         uint32_t *counts) {
   const uint32_t lane = threadIdx.x & 63u;
