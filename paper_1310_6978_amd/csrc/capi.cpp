@@ -766,7 +766,11 @@ fbg_status compile_common(const char *src, int32_t n_vars, const int32_t *subst,
   }
   p->nslices = slices_of(p->c.n);
   p->ncl = fbg::leading_clauses(p->c);
-  for (int l = 0; l <= kMaxLog2W; l++) p->live[l] = expected_live(p, l), p->multi[l] = multi_clauses(p, l);
+  for (int l = 0; l <= kMaxLog2W; l++) {
+    if (!p->has_tiling(l)) continue;
+    p->live[l] = expected_live(p, l);
+    p->multi[l] = multi_clauses(p, l);
+  }
   size_t total = 0;
   std::string enc_err;
   for (int l = 0; l <= kMaxLog2W; l++) {
